@@ -419,7 +419,7 @@ scan_status scan_query_modularity(const scan_index *ix, const int32_t *membershi
   SCAN_TRY(tmp.alloc(&terms, 3));
   zero64(dsum, ix->n, s);
   zero64(terms, 3, s);
-  launch_modularity_terms(ix, memberships, dsum, terms, s);
+  launch_modularity_terms(ix, memberships, 1, dsum, terms, s);
   int64_t h[3];
   SCAN_HIP_TRY(hipMemcpyAsync(h, terms, sizeof(h), hipMemcpyDeviceToHost, s));
   SCAN_HIP_TRY(hipStreamSynchronize(s));
@@ -447,14 +447,27 @@ scan_status scan_sweep_modularity(const scan_index *ix, int32_t count, const int
   int32_t *memb;
   int64_t *dsum, *terms;
   SCAN_TRY(tmp.alloc(&memb, (int64_t)B * n));
-  SCAN_TRY(tmp.alloc(&dsum, n));
+  // Degree sums for a whole batch of clusterings, and the workspace that
+  // scores many at once, where memory allows; else one clustering at a time.
+  ModularitySweep ms;
+  int32_t D = B;
+  if (tmp.alloc(&dsum, (int64_t)D * n) != SCAN_OK) {
+    D = 1;
+    SCAN_TRY(tmp.alloc(&dsum, n));
+  }
   SCAN_TRY(tmp.alloc(&terms, (int64_t)3 * count));
-  zero64(dsum, n, s);
+  const bool many = D > 1 && plan_modularity_sweep(ix, tmp, s, &ms) == SCAN_OK;
+  zero64(dsum, (int64_t)D * n, s);
   zero64(terms, (int64_t)3 * count, s);
   for (int32_t i = 0; i < count; i += B) {
     const int32_t c = std::min(B, count - i);
     SCAN_TRY(query_impl(ix, c, mu + i, eps + i, memb, nullptr, 1, s));
-    for (int32_t j = 0; j < c; ++j) launch_modularity_terms(ix, memb + (int64_t)j * n, dsum, terms + 3 * (int64_t)(i + j), s);
+    if (many) {
+      launch_modularity_sweep(ix, ms, memb, c, dsum, terms + 3 * (int64_t)i, s);
+    } else {
+      for (int32_t j = 0; j < c; j += D)
+        launch_modularity_terms(ix, memb + (int64_t)j * n, std::min(D, c - j), dsum, terms + 3 * (int64_t)(i + j), s);
+    }
     SCAN_HIP_TRY(hipGetLastError());
   }
   std::vector<int64_t> h((size_t)3 * count);

@@ -206,11 +206,21 @@ scan_status alloc_query_slot(const scan_index *ix, QuerySlot *slot, hipStream_t 
 
 // Enqueues the four query kernels for `count` device descriptors.
 void launch_query_kernels(const scan_index *ix, QueryDesc *d, int32_t count, hipStream_t s);
-// Modularity terms (quality.hip): terms[0] += s_in, terms[1] += sd2 for one
-// clustering; dsum (int64[n]) must be zero on entry and is zero on return.
+// Modularity terms (quality.hip) of `count` clusterings (memb[i * n ...]):
+// terms[3 i] += s_in, terms[3 i + 1] += sd2; dsum (int64[count * n]) must be
+// zero on entry and is zero on return.
 void zero64(int64_t *p, int64_t count, hipStream_t s);
-void launch_modularity_terms(const scan_index *ix, const int32_t *memb, int64_t *dsum, int64_t *terms,
-                             hipStream_t s);
+void launch_modularity_terms(const scan_index *ix, const int32_t *memb, int32_t count, int64_t *dsum,
+                             int64_t *terms, hipStream_t s);
+// The same for the clusterings of a sweep, kModLanes at a time, with the
+// sweep's workspace (plan_modularity_sweep, allocated from tmp).
+struct ModularitySweep {
+  int32_t *T = nullptr;       // labels of up to 32 clusterings, transposed
+  int32_t *row_of = nullptr;  // the row holding every 128th slot
+};
+scan_status plan_modularity_sweep(const scan_index *ix, DevArena &tmp, hipStream_t s, ModularitySweep *p);
+void launch_modularity_sweep(const scan_index *ix, const ModularitySweep &p, const int32_t *memb, int32_t count,
+                             int64_t *dsum, int64_t *terms, hipStream_t s);
 double modularity_value(int64_t s_in, int64_t sd2, int64_t nnz);
 
 // Hub / outlier roles of the unclustered vertices of one query's memberships.
