@@ -293,7 +293,7 @@ scan_status scan_query_ex(const scan_index *ix, int32_t mu, double eps, int32_t 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the query of
  * scan_query_ex with device outputs, whose workspace (union-find parents,
- * state bytes and the query descriptor, 5 * n + 256 bytes) lives in a
+ * state bytes and the query's state, 5 * n + 256 bytes) lives in a
  * file-scope device array of the library (40 MiB + 256 bytes, held on each
  * device the library runs on until the process ends) instead of allocated
  * memory. It calls no allocator and never waits for the device.

@@ -175,7 +175,7 @@ static scan_status acquire_slots(scan_index *ix, int count, hipStream_t s,
   for (auto *p : ix->pool) {
     if ((int)got.size() == count) break;
     if (p->busy) continue;
-    bool ok = p->last_stream == s || !p->done || hipEventQuery(p->done) == hipSuccess;
+    bool ok = p->last_stream == s || !p->done || hipEventQuery(p->done->ev) == hipSuccess;
     if (ok) {
       p->busy = true;
       got.push_back(p);
@@ -190,7 +190,6 @@ static scan_status acquire_slots(scan_index *ix, int count, hipStream_t s,
       got.clear();
       return st;
     }
-    if (hipEventCreateWithFlags(&p->done, hipEventDisableTiming) != hipSuccess) p->done = nullptr;
     p->busy = true;
     ix->pool.push_back(p);
     got.push_back(p);
@@ -200,8 +199,24 @@ static scan_status acquire_slots(scan_index *ix, int count, hipStream_t s,
 
 static void release_slots(scan_index *ix, std::vector<scan_index::PooledSlot *> &got, hipStream_t s) {
   std::lock_guard<std::mutex> lk(ix->pool_mu);
+  if (got.empty()) return;
+  // One event for the call's slots: their last one again where they, and no
+  // other slot, all had it.
+  std::shared_ptr<scan_index::Done> done = got[0]->done;
+  for (auto *p : got)
+    if (p->done != done) done.reset();
+  if (done && (size_t)done.use_count() != got.size() + 1) done.reset();
+  if (!done) {
+    done = std::make_shared<scan_index::Done>();
+    if (hipEventCreateWithFlags(&done->ev, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      done.reset();
+    }
+  }
+  if (done) (void)hipEventRecord(done->ev, s);
+  else (void)hipStreamSynchronize(s);  // no event to be had: the slots are free once s is
   for (auto *p : got) {
-    if (p->done) (void)hipEventRecord(p->done, s);
+    p->done = done;
     p->last_stream = s;
     p->busy = false;
   }
@@ -215,8 +230,8 @@ static scan_status query_impl(const scan_index *cix, int32_t count, const int32_
   const int64_t n = ix->n;
   std::vector<scan_index::PooledSlot *> got;
   SCAN_TRY(acquire_slots(ix, count, s, got));
-  std::vector<QuerySlot> slots(count);
-  for (int i = 0; i < count; ++i) slots[i] = got[i]->slot;
+  std::vector<QuerySlot *> slots(count);
+  for (int i = 0; i < count; ++i) slots[i] = &got[i]->slot;
   std::vector<int32_t *> mptr(count);
   std::vector<uint8_t *> cptr(count, nullptr);
   DevArena tmp(s);
@@ -540,10 +555,7 @@ void scan_index_free(scan_index *ix) {
   {
     std::lock_guard<std::mutex> lk(ix->pool_mu);
     for (auto *p : ix->pool) {
-      if (p->done) {
-        (void)hipEventSynchronize(p->done);
-        (void)hipEventDestroy(p->done);
-      }
+      if (p->done) (void)hipEventSynchronize(p->done->ev);
       free_query_slot(&p->slot, ix->stream);
       delete p;
     }

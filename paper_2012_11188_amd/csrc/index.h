@@ -94,20 +94,29 @@ scan_status lsh_overwrite(const LshSpec &spec, int64_t n, int64_t nnz, const int
 // SCAN_EGRAPH unless every weight is finite (waits for the stream).
 scan_status check_weights(const double *w, int64_t nnz, DevArena &tmp, hipStream_t s);
 
-// Per-query device workspace (one slot of a batch).
+// What k_q_cores finds out about a query, for the kernels after it.
+struct QueryState {
+  int64_t base;  // co_off[mu] (0 if mu > dmax + 1)
+  int64_t K;     // number of cores
+};
+
+// Per-query device workspace (one slot of a batch): one allocation of
+// kSlotStateBytes + 5 n bytes.
+constexpr size_t kSlotStateBytes = 64;
 struct QuerySlot {
+  QueryState *st = nullptr;
   int32_t *parent = nullptr;  // int32[n] union-find parents (read for cores only)
-  uint8_t *flag = nullptr;    // uint8[n] state: 2 core, 1 candidate border; all zero between queries
+  uint8_t *flag = nullptr;    // uint8[n] marks of epochs up to `epoch` (query.hip)
+  int32_t epoch = 0;          // the epoch of the slot's last query
   size_t bytes = 0;
 };
 
-// Device-side descriptor of one query of a batch (query.hip).
+// Descriptor of one query of a batch (query.hip).
 struct QueryDesc {
   int32_t mu;
-  int32_t pad;
+  int32_t epoch;
   double eps;
-  int64_t base;  // co_off[mu] (0 if mu > dmax + 1)
-  int64_t K;     // number of cores
+  QueryState *st;
   int32_t *parent;
   uint8_t *flag;
   int32_t *memb;  // nullptr: unused batch entry
@@ -170,10 +179,17 @@ struct scan_index {
   std::shared_ptr<scan::BuildProfileEvents> prof;  // SCAN_PROFILE only
   int64_t bytes = 0;                               // device bytes of this index's arrays
   // Query workspace pool: a slot may be reused once its last use completed
-  // (event) or when the new use is on the same stream.
+  // (event) or when the new use is on the same stream. The slots of one call
+  // share its event.
+  struct Done {
+    hipEvent_t ev = nullptr;
+    ~Done() {
+      if (ev) (void)hipEventDestroy(ev);
+    }
+  };
   struct PooledSlot {
     scan::QuerySlot slot;
-    hipEvent_t done = nullptr;
+    std::shared_ptr<Done> done;
     hipStream_t last_stream = nullptr;
     bool busy = false;
   };
@@ -197,14 +213,14 @@ scan_status build_index_batch(const scan_csr *gs, int32_t count, int32_t kind, u
 
 // Runs `count` queries. mu/eps host arrays; memberships[i] / is_core[i] are
 // device pointers (is_core may hold nulls). Slots are workspaces, one per
-// query.
+// query; nothing is allocated and nothing waited for.
 scan_status run_queries(const scan_index *ix, int32_t count, const int32_t *mu, const double *eps,
-                        int32_t *const *memberships, uint8_t *const *is_core,
-                        const QuerySlot *slots, hipStream_t s);
+                        int32_t *const *memberships, uint8_t *const *is_core, QuerySlot *const *slots,
+                        hipStream_t s);
 
 scan_status alloc_query_slot(const scan_index *ix, QuerySlot *slot, hipStream_t s);
 
-// Enqueues the four query kernels for `count` device descriptors.
+// Enqueues the query kernels for `count` descriptors in device memory.
 void launch_query_kernels(const scan_index *ix, QueryDesc *d, int32_t count, hipStream_t s);
 // Modularity terms (quality.hip) of `count` clusterings (memb[i * n ...]):
 // terms[3 i] += s_in, terms[3 i + 1] += sd2; dsum (int64[count * n]) must be
@@ -229,8 +245,10 @@ void launch_roles(const scan_index *ix, const int32_t *memb, uint8_t *roles, hip
 // allocation); memberships / is_core are device pointers.
 scan_status query_noalloc(const scan_index *ix, int32_t mu, double eps, int32_t *memberships, uint8_t *is_core,
                           hipStream_t s);
-QueryDesc make_query_desc(int32_t mu, double eps, const QuerySlot &slot, int32_t *memb,
-                          uint8_t *is_core);
+// The descriptor of the slot's next query, which runs on s (memb null: an
+// unused entry).
+QueryDesc make_query_desc(const scan_index *ix, int32_t mu, double eps, QuerySlot &slot, int32_t *memb,
+                          uint8_t *is_core, hipStream_t s);
 void free_query_slot(QuerySlot *slot, hipStream_t s);
 
 IntersectConfig default_config();

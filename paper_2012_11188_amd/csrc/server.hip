@@ -4,7 +4,7 @@
 // slots (union-find parents, border flags, a device result array and a pinned
 // host result array per slot), its own stream and event. A launcher thread
 // takes queued requests whenever a batch buffer is free and submits up to
-// max_batch of them as one batch: the four query kernels run once for all of
+// max_batch of them as one batch: the query kernels run once for all of
 // them (unused entries are inactive descriptors) and every result is copied to
 // its slot's pinned array. With use_graph the whole batch (descriptor upload,
 // kernels, result copies) is a HIP graph captured once per buffer and
@@ -136,9 +136,9 @@ void launcher_loop(scan_server *s) {
     for (int32_t i = 0; i < s->opts.max_batch; ++i) {
       if (i < count) {
         const Request &r = b.reqs[i];
-        b.h_desc[i] = make_query_desc(r.mu, r.eps, b.slots[i], r.dst_on_device ? r.dst : b.d_memb[i], nullptr);
+        b.h_desc[i] = make_query_desc(s->ix, r.mu, r.eps, b.slots[i], r.dst_on_device ? r.dst : b.d_memb[i], nullptr, b.stream);
       } else {
-        b.h_desc[i] = make_query_desc(2, 0.0, b.slots[i], nullptr, nullptr);  // inactive
+        b.h_desc[i] = make_query_desc(s->ix, 2, 0.0, b.slots[i], nullptr, nullptr, b.stream);  // inactive
       }
     }
     hipError_t e = b.exec ? hipGraphLaunch(b.exec, b.stream) : enqueue_batch_kernels(s, b);
@@ -233,10 +233,10 @@ scan_status scan_server_create(const scan_index *ix, const scan_server_opts *opt
     if (!b.d_desc ||
         hipHostMalloc((void **)&b.h_desc, sizeof(QueryDesc) * s->opts.max_batch, hipHostMallocDefault) != hipSuccess)
       return bail(fail(SCAN_ENOMEM, "descriptor allocation failed"));
-    for (int32_t i = 0; i < s->opts.max_batch; ++i) b.h_desc[i] = make_query_desc(2, 0.0, b.slots[i], nullptr, nullptr);
+    for (int32_t i = 0; i < s->opts.max_batch; ++i) b.h_desc[i] = make_query_desc(ix, 2, 0.0, b.slots[i], nullptr, nullptr, b.stream);
     if (hipStreamSynchronize(b.stream) != hipSuccess) return bail(fail(SCAN_EDEVICE, "server set-up failed"));
     if (opts->use_graph) {
-      // The graph holds no memset node; flags are cleared by the kernels.
+      // The graph holds no memset node: the slots' marks count epochs.
       if (hipStreamBeginCapture(b.stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return bail(fail(SCAN_EDEVICE, "graph capture failed to start"));
       hipError_t e = enqueue_batch_kernels(s, b);
