@@ -18,7 +18,7 @@
 //                into LDS, then one of them adds them in ascending x (lane i:
 //                direction g * 64 + i); the signs form one 64-bit word by
 //                ballot.
-//   k_minhash    one wavefront per high vertex: k bins in LDS, atomicMin of
+//   k_minhash    one workgroup per high vertex: k bins in LDS, atomicMin of
 //                perm[x] over N[v].
 //   k_estimate   one wavefront per piece of 64 slots of a high vertex's row
 //                (pieces numbered by a prefix over the vertices): the slots
@@ -42,6 +42,8 @@ constexpr int kShThreads = 256;
 constexpr int kShUnroll = 8;     // entries whose LDS values the summing wave reads ahead
 constexpr int kShWaves = kShThreads / kWave;
 constexpr int kMhGroup = 16;   // lanes comparing one pair of MinHash sketches
+constexpr int kMhHeld = 256;   // bins of u's sketch that a group keeps in registers
+constexpr int kMhPairs = 2;    // pairs whose sketches a group reads at once
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -55,16 +57,40 @@ __device__ __forceinline__ bool high(int kind, int64_t deg, int64_t k) {
   return kind == SCAN_SIM_JACCARD ? 2 * deg > 3 * k : deg > k;
 }
 
-// big[] = the high vertices, *nbig their number.
-__global__ void k_simhash_list(const int64_t *off, int64_t n, int32_t k, int32_t *big, int32_t *nbig) {
-  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t d = off[v + 1] - off[v];
-    if (high(SCAN_SIM_COSINE, d, k)) big[atomicAdd(nbig, 1)] = (int32_t)v;
+// The high vertices: those of degree above kLshLong to big[0, nhigh[0]), the
+// others to big[n - nhigh[1], n), one reservation per wavefront and class.
+constexpr int64_t kLshLong = 4096;
+__global__ __launch_bounds__(256) void k_high_list(const int64_t *off, int64_t n, int kind, int32_t k, int32_t *big,
+                                                   int32_t *nhigh) {
+  const int lane = lane_id();
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t v0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) - lane; v0 < n; v0 += stride) {
+    const int64_t v = v0 + lane;
+    const int64_t d = v < n ? off[v + 1] - off[v] : 0;
+    const bool in = v < n && high(kind, d, k);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const bool mine = in && (d > kLshLong) == (c == 0);
+      const uint64_t m = __ballot(mine);
+      int32_t at = 0;
+      if (m && lane == 0) at = atomicAdd(&nhigh[c], __popcll(m));
+      at = uniform(at) + __popcll(m & ((1ull << lane) - 1));
+      if (mine) big[c == 0 ? at : n - 1 - at] = (int32_t)v;
+    }
   }
+}
+__device__ __forceinline__ int32_t high_vertex(const int32_t *big, int64_t n, int64_t nlong, int64_t i) {
+  return i < nlong ? big[i] : big[n - 1 - (i - nlong)];
 }
 
 // SimHash words, words[v * (k / 64) + g] with bit i for direction g * 64 + i:
-// one item per (high vertex, group of 64 directions). The grid is what the
+// one item per (high vertex, group of 64 directions). The long rows' items
+// come first (their sums are the longest serial chains); the others go group
+// by group, so that at any time the gathers fall into one group's 512 bytes
+// per vertex, whose often-met rows stay in the
+// last-level cache. R-MAT-20, k = 256 (41 GB of gathers): 8.1 ms vertex by
+// vertex, 7.0 group by group, 5.95 with each round's gathers requested before
+// the sum of the round before it. The grid is what the
 // CUs hold at once, and each workgroup claims its next item from *claim as
 // soon as it is done (item sizes follow the degrees, so a static split would
 // leave most workgroups idle behind the longest lists). Per round, all waves
@@ -73,52 +99,72 @@ __global__ void k_simhash_list(const int64_t *off, int64_t n, int32_t k, int32_t
 // adds them in ascending order, lane i for direction g * 64 + i, with the
 // self term at its place.
 __global__ __launch_bounds__(kShThreads) void k_simhash_big(const int64_t *off, const int32_t *adj, const double *w,
-                                                            const double *gauss, int32_t k, const int32_t *big,
-                                                            const int32_t *nbig, unsigned long long *claim,
-                                                            uint64_t *words) {
+                                                            const double *gauss, int64_t n, int32_t k,
+                                                            const int32_t *big, const int32_t *nhigh,
+                                                            unsigned long long *claim, uint64_t *words) {
   extern __shared__ double st[];           // [kShChunk][64] coordinates
   __shared__ int32_t sid[kShChunk];        // the entries' ids
   __shared__ double sw[kShChunk];          // and weights
   __shared__ int64_t s_item;
   const int lane = lane_id(), wave = threadIdx.x / kWave;
   const int32_t groups = k / kWave;
-  const int64_t items = (int64_t)uniform(*nbig) * groups;
+  const int64_t nlong = uniform(nhigh[0]), nrest = uniform(nhigh[1]);
+  const int64_t items = (nlong + nrest) * groups;
   for (;;) {
     if (threadIdx.x == 0) s_item = (int64_t)atomicAdd(claim, 1ull);
     __syncthreads();
     const int64_t t = s_item;
     if (t >= items) break;  // uniform across the block
-    const int64_t v = big[t / groups];
-    const int32_t g = (int32_t)(t % groups);
+    const int64_t r = t - nlong * groups;
+    const int64_t v = high_vertex(big, n, nlong, r < 0 ? t / groups : nlong + r % nrest);
+    const int32_t g = (int32_t)(r < 0 ? t % groups : r / nrest);
     const int64_t o = uniform64(off[v]), d = uniform64(off[v + 1]) - o;
     const double *col = gauss + g * kWave + lane;
+    const double gself = col[v * (int64_t)k];  // the self term's coordinate
     double acc = 0.0;
     bool self = false;
+    // Entries wave, wave + kShWaves, ... of a round: ids by one vector load
+    // (and weights), then every gather of the wave. A round's gathers are
+    // requested before the round before it is summed, its ids one round
+    // earlier still, so that the sums wait for neither.
+    constexpr int kPer = kShChunk / kShWaves;
+    const int jl = wave + kShWaves * lane;  // the entry whose id this lane loads (lanes below kPer)
+    auto fetch_ids = [&](int64_t c, int32_t &x, double &wx) {
+      const int64_t p = lane < kPer && c + jl < d ? c + jl : d - 1;  // (past the row: its last entry again)
+      x = adj[o + p];
+      wx = w ? w[o + p] : 1.0;
+    };
+    auto gather = [&](int32_t x, double gv[kPer]) {
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) gv[q] = col[(int64_t)__builtin_amdgcn_readlane(x, q) * k];
+    };
+    int32_t x0, x1;
+    double w0, w1, gv[kPer];
+    fetch_ids(0, x0, w0);
+    gather(x0, gv);
+    fetch_ids(kShChunk, x1, w1);
     for (int64_t c = 0; c < d; c += kShChunk) {
       const int m = (int)(d - c < kShChunk ? d - c : kShChunk);
       __syncthreads();  // the previous round's readers are done
-      // entries wave, wave + kShWaves, ...: ids first (one vector load), then
-      // every gather of the wave, then the LDS stores
-      constexpr int kPer = kShChunk / kShWaves;
-      const int jl = wave + kShWaves * lane;  // the entry whose id this lane loads
-      const int32_t xl = jl < m ? adj[o + c + jl] : 0;
-      if (lane < kPer && jl < m) {
-        sid[jl] = xl;
-        sw[jl] = w ? w[o + c + jl] : 1.0;
+      if (lane < kPer) {
+        sid[jl] = x0;
+        sw[jl] = w0;
       }
-      double gv[kPer];
 #pragma unroll
-      for (int q = 0; q < kPer; ++q) gv[q] = col[(int64_t)__builtin_amdgcn_readlane(xl, q) * k];
-#pragma unroll
-      for (int q = 0; q < kPer; ++q)
-        if (wave + kShWaves * q < m) st[(wave + kShWaves * q) * kWave + lane] = gv[q];
+      for (int q = 0; q < kPer; ++q) st[(wave + kShWaves * q) * kWave + lane] = gv[q];
+      x0 = x1;
+      w0 = w1;
+      if (c + kShChunk < d) {
+        gather(x0, gv);
+        fetch_ids(c + 2 * kShChunk, x1, w1);
+      }
       __syncthreads();
       if (wave == 0) {
         for (int j0 = 0; j0 < m; j0 += kShUnroll) {
           int32_t xs[kShUnroll];
           double ws[kShUnroll], gs[kShUnroll];
 #pragma unroll
-          for (int u = 0; u < kShUnroll; ++u) {  // entries past m read stale LDS and are not added
+          for (int u = 0; u < kShUnroll; ++u) {  // entries past m are not added
             xs[u] = sid[j0 + u];
             ws[u] = sw[j0 + u];
             gs[u] = st[(j0 + u) * kWave + lane];
@@ -127,7 +173,7 @@ __global__ __launch_bounds__(kShThreads) void k_simhash_big(const int64_t *off, 
           for (int u = 0; u < kShUnroll; ++u) {
             if (j0 + u < m) {
               if (!self && xs[u] > v) {
-                acc += 1.0 * col[v * (int64_t)k];
+                acc += 1.0 * gself;
                 self = true;
               }
               acc += ws[u] * gs[u];
@@ -137,7 +183,7 @@ __global__ __launch_bounds__(kShThreads) void k_simhash_big(const int64_t *off, 
       }
     }
     if (wave == 0) {
-      if (!self) acc += 1.0 * col[v * (int64_t)k];
+      if (!self) acc += 1.0 * gself;
       const uint64_t bits = __ballot(acc >= 0.0);
       if (lane == 0) words[v * groups + g] = bits;
     }
@@ -145,26 +191,46 @@ __global__ __launch_bounds__(kShThreads) void k_simhash_big(const int64_t *off, 
   }
 }
 
-// sk[v * k + b]; the block's waves take one vertex each, bins in LDS.
-__global__ __launch_bounds__(kLshThreads) void k_minhash(const int64_t *off, const int32_t *adj, const uint32_t *perm,
-                                                         int64_t n, int32_t k, uint32_t *sk) {
-  extern __shared__ uint32_t bins[];  // [kLshWaves][k]
-  const int lane = lane_id(), wave = threadIdx.x / kWave;
-  uint32_t *mine = bins + (size_t)wave * k;
-  const int64_t waves = (int64_t)gridDim.x * kLshWaves;
-  for (int64_t v = uniform64((int64_t)blockIdx.x * kLshWaves + wave); v < n; v += waves) {
-    const int64_t o = uniform64(off[v]), d = uniform64(off[v + 1]) - o;
-    if (!high(SCAN_SIM_JACCARD, d, k)) continue;
-    for (int32_t b = lane; b < k; b += kWave) mine[b] = 0xffffffffu;
-    for (int64_t c = -1; c < d; c += kWave) {  // position -1 is v itself
-      const int64_t p = c + lane;
-      if (p < d) {
-        const int64_t x = p < 0 ? v : adj[o + p];
-        const uint32_t px = perm[x];
-        atomicMin(&mine[(uint64_t)px * (uint64_t)k / (uint64_t)n], px);
+// sk[v * k + b]: a workgroup per high vertex, its bins in LDS (minima: any
+// order gives the same sketch), so that a hub's row is read by all of its
+// wavefronts. (With a wavefront per vertex the longest row, 65k entries, held
+// the kernel: 830 us on R-MAT-20 with k = 256; this takes
+// 280.)
+constexpr int kMhThreads = 512;
+constexpr int kMhSteps = 4;  // entries per thread requested together
+__global__ __launch_bounds__(kMhThreads) void k_minhash(const int64_t *off, const int32_t *adj, const uint32_t *perm,
+                                                        int64_t n, int32_t k, const int32_t *big,
+                                                        const int32_t *nhigh, unsigned long long *claim,
+                                                        uint32_t *sk) {
+  extern __shared__ uint32_t bins[];  // [k]
+  __shared__ int64_t s_item;
+  const int64_t nlong = uniform(nhigh[0]), items = nlong + uniform(nhigh[1]);
+  for (;;) {
+    if (threadIdx.x == 0) s_item = (int64_t)atomicAdd(claim, 1ull);
+    for (int32_t b = threadIdx.x; b < k; b += kMhThreads) bins[b] = 0xffffffffu;
+    __syncthreads();
+    const int64_t t = s_item;
+    if (t >= items) break;  // uniform across the block
+    const int64_t v = high_vertex(big, n, nlong, t);
+    const int64_t o = off[v], d = off[v + 1] - o;
+    for (int64_t c = threadIdx.x; c <= d; c += kMhSteps * kMhThreads) {  // position d is v itself
+      int64_t x[kMhSteps];
+      uint32_t px[kMhSteps];
+#pragma unroll
+      for (int j = 0; j < kMhSteps; ++j) {
+        const int64_t p = c + j * kMhThreads;
+        x[j] = p < d ? adj[o + p] : v;
+      }
+#pragma unroll
+      for (int j = 0; j < kMhSteps; ++j) px[j] = perm[x[j]];  // (past the row: v again, which is in the set)
+#pragma unroll
+      for (int j = 0; j < kMhSteps; ++j) {
+        if (c + j * kMhThreads <= d) atomicMin(&bins[(uint64_t)px[j] * (uint64_t)k / (uint64_t)n], px[j]);
       }
     }
-    for (int32_t b = lane; b < k; b += kWave) sk[v * k + b] = mine[b];
+    __syncthreads();
+    for (int32_t b = threadIdx.x; b < k; b += kMhThreads) sk[v * k + b] = bins[b];
+    __syncthreads();  // the bins and s_item are reused
   }
 }
 
@@ -185,15 +251,21 @@ __global__ __launch_bounds__(kLshThreads) void k_estimate(const int64_t *off, co
                                                           int kind, int32_t k, const int64_t *P,
                                                           const uint64_t *words, const uint32_t *sk,
                                                           const double *table, double *sims) {
-  const int lane = lane_id();
+  __shared__ int32_t list[kLshWaves][kWave];
+  const int lane = lane_id(), wave = threadIdx.x / kWave;
   const int64_t waves = (int64_t)gridDim.x * kLshWaves;
   const int64_t T = uniform64(P[n]);
   for (int64_t t = uniform64(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave); t < T; t += waves) {
-    int64_t lo = 0, hi = n;  // the u with P[u] <= t < P[u + 1]
-    while (hi - lo > 1) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (uniform64(P[mid]) <= t) lo = mid;
-      else hi = mid;
+    // the u with P[u] <= t < P[u + 1]: the last one with P[u] <= t, by a
+    // 64-way search (every lane samples one position)
+    int64_t lo = 0, cnt = n;
+    while (cnt > 1) {
+      const int64_t step = (cnt + kWave - 1) / kWave;
+      const int64_t q = lo + lane * step;
+      const int c = __popcll(__ballot(q < lo + cnt && P[q] <= t));  // >= 1: lane 0
+      const int64_t nlo = lo + (c - 1) * step;
+      cnt = min(step, lo + cnt - nlo);
+      lo = nlo;
     }
     const int64_t u = lo, o = uniform64(off[u]), d = uniform64(off[u + 1]) - o;
     const int64_t p0 = (t - uniform64(P[u])) * kLshPiece;
@@ -210,33 +282,55 @@ __global__ __launch_bounds__(kLshThreads) void k_estimate(const int64_t *off, co
       }
       continue;
     }
+    // The slots to compare, listed in lane order. u's sketch stays in
+    // registers for the piece where it fits (kMhHeld bins).
+    const int32_t v = p0 + lane < d ? adj[o + p0 + lane] : 0;
+    const bool on = p0 + lane < d && high(kind, off[v + 1] - off[v], k);
+    const uint64_t todo = __ballot(on);
+    const int count = __popcll(todo);
+    if (on) list[wave][__popcll(todo & ((1ull << lane) - 1))] = lane;
     const int grp = lane / kMhGroup, gl = lane % kMhGroup;
-    for (int r = 0; r < kLshPiece / (kWave / kMhGroup); ++r) {
-      const int64_t p = p0 + r * (kWave / kMhGroup) + grp;
-      bool on = p < d;
-      int64_t v = 0;
-      if (on) {
-        v = adj[o + p];
-        on = high(kind, off[v + 1] - off[v], k);
-      }
-      int32_t match = 0, empty = 0;
-      if (on) {
-        const uint4 *a = (const uint4 *)(sk + u * k), *b = (const uint4 *)(sk + v * k);
-        for (int32_t i = gl; i < k / 4; i += kMhGroup) {
-          const uint4 ea = a[i], eb = b[i];
-          const uint32_t av[4] = {ea.x, ea.y, ea.z, ea.w}, bv[4] = {eb.x, eb.y, eb.z, eb.w};
+    const uint4 *a = (const uint4 *)(sk + u * k);
+    constexpr int kHeld = kMhHeld / 4 / kMhGroup;
+    uint4 ha[kHeld];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (av[j] == 0xffffffffu && bv[j] == 0xffffffffu) ++empty;
-            else if (av[j] == bv[j]) ++match;
-          }
+    for (int i = 0; i < kHeld; ++i) ha[i] = a[min(gl + i * kMhGroup, k / 4 - 1)];
+    auto compare = [](const uint4 &ea, const uint4 &eb, int32_t &match, int32_t &empty) {
+      const uint32_t av[4] = {ea.x, ea.y, ea.z, ea.w}, bv[4] = {eb.x, eb.y, eb.z, eb.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool same = av[j] == bv[j];
+        empty += same && av[j] == 0xffffffffu ? 1 : 0;
+        match += same ? 1 : 0;  // (the empty ones come off below)
+      }
+    };
+    for (int r = 0; r < count; r += kWave / kMhGroup * kMhPairs) {
+      const uint4 *b[kMhPairs];
+      int src[kMhPairs];
+      uint4 eb[kMhPairs][kHeld];
+      int32_t match[kMhPairs], empty[kMhPairs];
+#pragma unroll
+      for (int q = 0; q < kMhPairs; ++q) {
+        src[q] = list[wave][min(r + q * (kWave / kMhGroup) + grp, count - 1)];
+        b[q] = (const uint4 *)(sk + (int64_t)__shfl(v, src[q], kWave) * k);
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i) eb[q][i] = b[q][min(gl + i * kMhGroup, k / 4 - 1)];
+      }
+#pragma unroll
+      for (int q = 0; q < kMhPairs; ++q) {
+        match[q] = empty[q] = 0;
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i)
+          if (gl + i * kMhGroup < k / 4) compare(ha[i], eb[q][i], match[q], empty[q]);
+        for (int32_t i = gl + kHeld * kMhGroup; i < k / 4; i += kMhGroup) compare(a[i], b[q][i], match[q], empty[q]);
+#pragma unroll
+        for (int m = kMhGroup / 2; m > 0; m >>= 1) {  // sums over the group (all lanes take part)
+          match[q] += __shfl_xor(match[q], m, kWave);
+          empty[q] += __shfl_xor(empty[q], m, kWave);
         }
+        if (gl == 0 && r + q * (kWave / kMhGroup) + grp < count)
+          sims[o + p0 + src[q]] = (double)(match[q] - empty[q]) / (double)(k - empty[q]);
       }
-      for (int m = kMhGroup / 2; m > 0; m >>= 1) {  // sums over the group (all lanes take part)
-        match += __shfl_xor(match, m, kWave);
-        empty += __shfl_xor(empty, m, kWave);
-      }
-      if (on && gl == 0) sims[o + p] = (double)match / (double)(k - empty);
     }
   }
 }
@@ -256,6 +350,17 @@ scan_status lsh_overwrite(const LshSpec &spec, int64_t n, int64_t nnz, const int
   uint64_t *words = nullptr;
   uint32_t *sk = nullptr;
   double *table = nullptr;
+  int device = 0, cus = 256;
+  (void)hipGetDevice(&device);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
+  int32_t *big, *nhigh;  // the high vertices, and the numbers of long and other ones
+  unsigned long long *claim;
+  SCAN_TRY(tmp.alloc(&big, n));
+  SCAN_TRY(tmp.alloc(&nhigh, 2));
+  SCAN_TRY(tmp.alloc(&claim, 1));
+  SCAN_HIP_TRY(hipMemsetAsync(nhigh, 0, 8, s));
+  SCAN_HIP_TRY(hipMemsetAsync(claim, 0, 8, s));
+  k_high_list<<<grid_for(n, 256, 2048), 256, 0, s>>>(off, n, kind, k, big, nhigh);
   if (kind == SCAN_SIM_JACCARD) {
     int32_t *d_err;
     SCAN_TRY(tmp.alloc(&d_err, 1));
@@ -266,36 +371,23 @@ scan_status lsh_overwrite(const LshSpec &spec, int64_t n, int64_t nnz, const int
     SCAN_HIP_TRY(hipStreamSynchronize(s));
     if (herr) return fail(SCAN_EINVAL, "MinHash permutation values must lie in [0, n)");
     SCAN_TRY(tmp.alloc(&sk, n * (int64_t)k));
-    const size_t lds = (size_t)kLshWaves * k * 4;
-    if (lds > 65536)
-      SCAN_HIP_TRY(hipFuncSetAttribute((const void *)k_minhash, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    k_minhash<<<grid_for(n, kLshWaves), kLshThreads, lds, s>>>(off, adj, spec.perm, n, k, sk);
+    k_minhash<<<cus * 4, kMhThreads, (size_t)k * 4, s>>>(off, adj, spec.perm, n, k, big, nhigh, claim, sk);
   } else {
     std::vector<double> t(k + 1);
     for (int32_t h = 0; h <= k; ++h) t[h] = std::cos(M_PI * (double)h / (double)k);
     SCAN_TRY(tmp.alloc(&table, k + 1));
     SCAN_HIP_TRY(hipMemcpyAsync(table, t.data(), t.size() * 8, hipMemcpyHostToDevice, s));
     SCAN_TRY(tmp.alloc(&words, n * (int64_t)(k / kWave)));
-    int32_t *big, *nbig;
-    unsigned long long *claim;
-    SCAN_TRY(tmp.alloc(&big, n));
-    SCAN_TRY(tmp.alloc(&nbig, 1));
-    SCAN_TRY(tmp.alloc(&claim, 1));
-    SCAN_HIP_TRY(hipMemsetAsync(nbig, 0, 4, s));
-    SCAN_HIP_TRY(hipMemsetAsync(claim, 0, 8, s));
-    k_simhash_list<<<grid_for(n, 256), 256, 0, s>>>(off, n, k, big, nbig);
     const size_t lds = (size_t)kShChunk * kWave * 8;
     SCAN_HIP_TRY(hipFuncSetAttribute((const void *)k_simhash_big, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    int device = 0, cus = 256, per_cu = 0;
-    (void)hipGetDevice(&device);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
+    int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)k_simhash_big, kShThreads, lds) !=
             hipSuccess ||
         per_cu < 1) {
       (void)hipGetLastError();
       per_cu = 1;
     }
-    k_simhash_big<<<cus * per_cu, kShThreads, lds, s>>>(off, adj, w, spec.gauss, k, big, nbig, claim, words);
+    k_simhash_big<<<cus * per_cu, kShThreads, lds, s>>>(off, adj, w, spec.gauss, n, k, big, nhigh, claim, words);
   }
   int32_t *cnt;
   int64_t *P, *ws;

@@ -206,3 +206,23 @@ def test_lsh_weighted_host_inputs_int64_validated():
     gix = scan.scan_build_index_lsh(off, g.adj.astype(np.int32), scan.WEIGHTED_COSINE, k, gauss, None, w,
                                     FLAGS | scan.SCAN_VALIDATE)
     assert_same(gix, oix)
+
+
+# rows past the long-row limit (4096), one high and one low neighbour count
+# around it, sketches within and past what a lane group holds (256 bins)
+@pytest.mark.parametrize("kind,k", [(scan.COSINE, 64), (scan.COSINE, 320), (scan.JACCARD, 64), (scan.JACCARD, 256),
+                                    (scan.JACCARD, 320), (scan.JACCARD, 448)])
+def test_long_rows_and_wide_sketches(kind, k):
+    n = 4300
+    base = graphgen.sbm(n, 2, 0.25, 0.08, 17)
+    hubs = [100, 2000, 4000]
+    edges = np.stack([np.repeat(np.arange(n), base.degrees()), base.adj], 1)
+    pairs = [edges[~np.isin(edges, hubs).any(1)]]
+    rest = np.setdiff1d(np.arange(n), hubs)
+    for hub, others in ((100, rest[:4095]), (2000, rest[:4096]), (4000, np.delete(np.arange(n), 4000))):
+        pairs.append(np.stack([np.full(len(others), hub), others], 1))
+    g = graphgen.from_edges(n, np.concatenate(pairs).astype(np.int32))
+    assert [int(g.degrees()[h]) for h in hubs] == [4096, 4097, n - 1]
+    gauss, perm = draws(g, kind, k, 23)
+    gix = lsh_gpu(g, kind, k, gauss, perm)
+    assert_same(gix, oracle.build_index_lsh(g, kind, k, gauss=gauss, perm=perm, threads=8))
