@@ -121,6 +121,13 @@ hipStream_t helper_stream(int k) {
   return g_helper[at];
 }
 
+hipError_t poll_event(hipEvent_t e) {
+  hipError_t r;
+  do r = hipEventQuery(e);
+  while (r == hipErrorNotReady);
+  return r;
+}
+
 scan_status stream_wait(hipStream_t waiter, hipStream_t signaller) {
   if (waiter == signaller) return SCAN_OK;
   hipEvent_t e;

@@ -349,6 +349,98 @@ __global__ void k_co_tiles(const RTile *rt, int64_t nrt, const RankInfo *sv_all,
                       : 0;
 }
 
+// All of the above for one graph of up to kPrepOneN vertices and degrees up to
+// kPrepOneDeg, in one workgroup and one launch: the counts, offsets, ranks and
+// tiles of a small graph are a few microseconds of work, and the twelve
+// launches of the general way, with the upload of their tables, were most of a
+// small build (2,000 vertices: 200 us under the profiler, this kernel 8). Past these sizes they run beside a longer
+// intersection, and one workgroup would not.
+constexpr int kPrepOneN = 32768, kPrepOneDeg = 4096, kPrepOneThreads = 1024;
+
+// Exclusive sum over the workgroup of one value per thread.
+__device__ __forceinline__ int64_t prep_excl_sum(int64_t v, int64_t *wsum) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  int64_t incl = v;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int64_t t = (int64_t)(((uint64_t)(uint32_t)__shfl_up((int32_t)(incl >> 32), d, kWave) << 32) |
+                                (uint32_t)__shfl_up((int32_t)(uint32_t)incl, d, kWave));
+    if (lane >= d) incl += t;
+  }
+  __syncthreads();  // wsum is reused
+  if (lane == kWave - 1) wsum[wave] = incl;
+  __syncthreads();
+  int64_t base = 0;
+  for (int w = 0; w < wave; ++w) base += wsum[w];
+  return base + incl - v;
+}
+
+__global__ __launch_bounds__(kPrepOneThreads) void k_co_prep_one(const int32_t *deg, const int64_t *off, int32_t n,
+                                                                 int64_t nnz, int32_t dmax, int64_t *co, int64_t *seg,
+                                                                 int64_t *nz, RankInfo *sv, int32_t nrt,
+                                                                 int64_t *tile_first) {
+  __shared__ int32_t E[kPrepOneDeg + 2];    // vertices of degree < d
+  __shared__ int32_t cur[kPrepOneDeg + 2];  // per degree: its vertices, then its next rank
+  __shared__ int32_t tl[kPrepOneN / kFillRanks];
+  __shared__ int64_t wsum[kPrepOneThreads / kWave];
+  const int t = threadIdx.x;
+  for (int i = t; i <= dmax; i += kPrepOneThreads) cur[i] = 0;
+  for (int i = t; i < nrt; i += kPrepOneThreads) tl[i] = 0;
+  __syncthreads();
+  for (int v = t; v < n; v += kPrepOneThreads) atomicAdd(&cur[max(deg[v], 0)], 1);
+  __syncthreads();
+  constexpr int kPer = (kPrepOneDeg + 2 + kPrepOneThreads - 1) / kPrepOneThreads;  // degrees per thread
+  {
+    int64_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) sum += t * kPer + k <= dmax ? cur[t * kPer + k] : 0;
+    int64_t e = prep_excl_sum(sum, wsum);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int d = t * kPer + k;
+      if (d <= dmax + 1) E[d] = (int32_t)e;
+      if (d <= dmax) e += cur[d];
+    }
+  }
+  __syncthreads();
+  {
+    // |CO[j + 2]| = n - E[j + 1], j < dmax
+    int64_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) sum += t * kPer + k < dmax ? n - E[t * kPer + k + 1] : 0;
+    int64_t x = prep_excl_sum(sum, wsum);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int j = t * kPer + k;
+      if (j <= dmax) co[j + 2] = x;
+      if (j < dmax) {
+        seg[j] = x;
+        x += n - E[j + 1];
+      }
+    }
+  }
+  if (t == 0) {
+    co[0] = co[1] = 0;
+    seg[dmax] = nnz;
+    *nz = n - E[1];
+  }
+  for (int d = t; d <= dmax; d += kPrepOneThreads) cur[d] = n - E[d + 1];
+  __syncthreads();
+  for (int v = t; v < n; v += kPrepOneThreads) {
+    const int32_t d = deg[v];
+    if (d <= 0) continue;
+    const int32_t r = atomicAdd(&cur[d], 1);
+    sv[r] = RankInfo{v, d, off[v]};
+    if (r % kFillRanks == 0) tl[r / kFillRanks] = (d + kFillMu - 1) / kFillMu;  // its first rank has the top degree
+  }
+  __syncthreads();
+  static_assert(kPrepOneN / kFillRanks <= kPrepOneThreads, "a thread per rank tile");
+  const int32_t mine = t < nrt ? tl[t] : 0;
+  const int64_t first = prep_excl_sum(mine, wsum);
+  if (t < nrt) tile_first[t] = first;
+  if (t == nrt - 1) tile_first[nrt] = first + mine;
+}
+
 // One workgroup per (rank tile, mu tile): kFillRanks consecutive ranks x
 // kFillMu consecutive mu, read row-contiguously from NO_SIM into LDS and
 // written segment-contiguously into the unsorted core order. With one graph,
@@ -468,6 +560,23 @@ void index_release(scan_index *ix) {
 }
 
 namespace {
+
+// A pinned block and the event after its last use by the device; waits for
+// that use before the block goes back to the pool.
+struct PinnedHold {
+  PinnedBlock block;
+  hipEvent_t ready = nullptr;
+  explicit PinnedHold(size_t bytes) : block(pinned_take(bytes)) {}
+  PinnedHold(const PinnedHold &) = delete;
+  PinnedHold &operator=(const PinnedHold &) = delete;
+  ~PinnedHold() {
+    if (ready) {
+      (void)hipEventSynchronize(ready);
+      (void)hipEventDestroy(ready);
+    }
+    pinned_give(block);
+  }
+};
 
 scan_status check_csr(const scan_csr *g) {
   if (!g) return fail(SCAN_EINVAL, "null graph");
@@ -615,10 +724,21 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
   // a1: union offsets (and adjacency), degrees, per-graph max degree.
   int64_t *off_u;
   int32_t *deg, *adj_u;
-  unsigned *d_dmax;
   SCAN_TRY(arena_alloc(*arena, &off_u, N + 1));
   SCAN_TRY(tmp.alloc(&deg, N));
-  SCAN_TRY(tmp.alloc(&d_dmax, G));
+  // Counters of the whole build, zeroed by one fill: the class sizes of the
+  // two sorts, 64 bytes that stay zero, then the plan's counts and the graphs' maximum degrees, which
+  // come back to the host together.
+  unsigned char *ctl;
+  const size_t ctl_back = kPlanCountBytes + (size_t)G * 4, ctl_bytes = 2 * kSortStatsBytes + 64 + ctl_back;
+  SCAN_TRY(tmp.alloc(&ctl, (int64_t)ctl_bytes));
+  void *const ctl_no = ctl, *const ctl_co = ctl + kSortStatsBytes, *const ctl_zero = ctl + 2 * kSortStatsBytes,
+             *const ctl_plan = ctl + 2 * kSortStatsBytes + 64;
+  unsigned *const d_dmax = (unsigned *)((unsigned char *)ctl_plan + kPlanCountBytes);
+  SCAN_HIP_TRY(hipMemsetAsync(ctl, 0, ctl_bytes, s));
+  PinnedHold back(ctl_back);  // the host's copy
+  if (!back.block.p) return fail(SCAN_ENOMEM, "pinned host allocation failed");
+  SCAN_HIP_TRY(hipEventCreateWithFlags(&back.ready, hipEventDisableTiming));
   if (copy_adj) SCAN_TRY(tmp.alloc(&adj_u, NNZ));
   else adj_u = const_cast<int32_t *>(hd[0].adj);
   GraphDesc *d_gd;
@@ -648,8 +768,6 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     SCAN_TRY(to_device(*arena, tmp, &d_gd, fix, s));
   }
   SCAN_TRY(to_device(*arena, tmp, &d_ptiles, ptiles, s));
-  SCAN_HIP_TRY(hipMemsetAsync(d_dmax, 0, (size_t)G * 4, s));
-  SCAN_HIP_TRY(hipMemsetAsync(off_u, 0, 8, s));
   {
     const int64_t total = item_base[G];
     if (total > 0)
@@ -685,11 +803,19 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
   if (ns && stream_wait(ns, s) != SCAN_OK) ns = nullptr;
   JoinOnExit join_ns{s, ns};
   SortClasses no_cls;
-  if (NNZ > 0) SCAN_TRY(sort_classify(off_u, N, tmp, ns ? ns : s, no_cls));
+  if (NNZ > 0) SCAN_TRY(sort_classify(off_u, N, NNZ, tmp, ctl_no, ns ? ns : s, no_cls));
   // a2: the ownership plan needs only the degrees; its counts come back with
-  // the maximum degrees below.
+  // the maximum degrees. (The classification before it runs beside it; after
+  // it, it ran into the placement of the intersection's persistent workgroups:
+  // R-MAT-20 7.08 instead of 6.96 ms a build.)
   IntersectPlan plan;
-  if (NNZ > 0 && !weighted) SCAN_TRY(intersect_plan(cfg, N, NNZ, off_u, deg, adj_u, device, tmp, s, plan));
+  if (NNZ > 0 && !weighted) {
+    SCAN_TRY(intersect_plan(cfg, N, NNZ, off_u, deg, adj_u, device, tmp, s, ctl_plan, (int32_t)(ctl_back / 4),
+                            back.block.p, back.ready, plan));
+  } else {
+    SCAN_HIP_TRY(hipMemcpyAsync(back.block.p, ctl_plan, ctl_back, hipMemcpyDeviceToHost, s));
+    SCAN_HIP_TRY(hipEventRecord(back.ready, s));
+  }
   // The small-owner kernels' helper streams wait for the plan now, off the
   // path between the read-back and the first intersection launch.
   JoinOnExit join_h0{s, nullptr}, join_h1{s, nullptr};
@@ -768,16 +894,9 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
   }
   // The one wait of the build that stalls the device: the maximum degrees
   // (with the plan counts) size everything after.
-  std::vector<unsigned> hdmax(G);
-  {
-    const PinnedBlock hb = pinned_take((size_t)G * 4);
-    if (!hb.p) return fail(SCAN_ENOMEM, "pinned host allocation failed");
-    hipError_t e = hipMemcpyAsync(hb.p, d_dmax, (size_t)G * 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e == hipSuccess) std::memcpy(hdmax.data(), hb.p, (size_t)G * 4);
-    pinned_give(hb);
-    SCAN_HIP_TRY(e);
-  }
+  SCAN_HIP_TRY(poll_event(back.ready));
+  const unsigned *const hdmax_p = (const unsigned *)((const unsigned char *)back.block.p + kPlanCountBytes);
+  const std::vector<unsigned> hdmax(hdmax_p, hdmax_p + G);
   SCAN_HIP_TRY(hipGetLastError());
   mark(1);
 
@@ -838,9 +957,23 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     SortClasses co_cls;
     const int64_t nrt = (int64_t)rt.size();
     auto co_prep = [&]() -> scan_status {  // cs is ordered after the degrees
+      if (G == 1 && N <= kPrepOneN && hdmax[0] <= kPrepOneDeg) {
+        SCAN_TRY(arena_alloc(*arena, &d_corel, cobase[G]));
+        SCAN_TRY(tmp.alloc(&d_seg, segbase[G] + 1));
+        SCAN_TRY(tmp.alloc(&d_nz, 1));
+        SCAN_TRY(tmp.alloc(&d_sv, N));
+        SCAN_TRY(tmp.alloc(&d_tile_first, nrt + 1));
+        SCAN_TRY(tmp.alloc(&co_key, NNZ));
+        SCAN_TRY(tmp.alloc(&co_id, NNZ));
+        // one graph: every base is zero
+        d_vbase = d_ebase = d_cobase = (const int64_t *)ctl_zero;
+        k_co_prep_one<<<1, kPrepOneThreads, 0, cs>>>(deg, off_u, (int32_t)N, NNZ, (int32_t)hdmax[0], d_corel, d_seg,
+                                                     d_nz, d_sv, (int32_t)nrt, d_tile_first);
+        return sort_classify(d_seg, segbase[G], NNZ, tmp, ctl_co, cs, co_cls);
+      }
       SCAN_TRY(upload_tables(cs));
-      SCAN_TRY(tmp.alloc(&d_hist, hbase[G]));
-      SCAN_TRY(tmp.alloc(&d_cursor, hbase[G]));
+      SCAN_TRY(tmp.alloc(&d_hist, 2 * hbase[G]));  // and the cursors
+      d_cursor = d_hist + hbase[G];
       SCAN_TRY(tmp.alloc(&d_E, Ebase[G]));
       SCAN_TRY(tmp.alloc(&d_seg, segbase[G] + 1));
       SCAN_TRY(tmp.alloc(&d_nz, G));
@@ -850,8 +983,7 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
       SCAN_TRY(tmp.alloc(&scan_ws, scan_workspace_elems(std::max<int64_t>(nrt, 1))));
       SCAN_TRY(tmp.alloc(&co_key, NNZ));
       SCAN_TRY(tmp.alloc(&co_id, NNZ));
-      SCAN_HIP_TRY(hipMemsetAsync(d_hist, 0, (size_t)hbase[G] * 4, cs));
-      SCAN_HIP_TRY(hipMemsetAsync(d_cursor, 0, (size_t)hbase[G] * 4, cs));
+      SCAN_HIP_TRY(hipMemsetAsync(d_hist, 0, (size_t)hbase[G] * 8, cs));
       if (!vt.empty())
         k_graph_hist<<<grid_for((int64_t)vt.size(), 1, 8192), 256, 0, cs>>>(d_vt, (int64_t)vt.size(), deg, d_hbase,
                                                                            d_dmax, d_hist);
@@ -875,7 +1007,7 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
         k_co_tiles<<<grid_for(nrt, 256), 256, 0, cs>>>(d_rt, nrt, d_sv, d_vbase, d_nz, d_tiles_of);
         SCAN_TRY(exclusive_scan(d_tiles_of, d_tile_first, nrt, scan_ws, cs));
       }
-      return sort_classify(d_seg, segbase[G], tmp, cs, co_cls);  // the core-order segments
+      return sort_classify(d_seg, segbase[G], NNZ, tmp, ctl_co, cs, co_cls);  // the core-order segments
     };
 
     // a2-a4: ownership plan, intersection and similarity over the union.

@@ -42,6 +42,26 @@ __device__ __forceinline__ bool key_less(uint64_t ka, int32_t ia, uint64_t kb, i
   return ka < kb || (ka == kb && ia < ib);
 }
 
+// Whether this workgroup is the last of its grid to get here (uniform across
+// it; `flag` is a shared int). What the workgroups leave for the last one must
+// be written with device-scope atomics and read back with load_agent: those
+// meet in memory, and every thread waits for its own before the workgroup
+// counts as finished. (A fence at device scope would do for plain stores too,
+// but it writes back the whole L2: k_plan 36 -> 106 us on R-MAT-20.)
+__device__ __forceinline__ bool last_workgroup(int32_t *done, int32_t *flag) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *flag = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int32_t)gridDim.x - 1;
+  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  return *flag != 0;
+}
+__device__ __forceinline__ int32_t load_agent(const int32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 constexpr uint64_t kPadKey = ~0ull;
 constexpr int32_t kPadId = 0x7fffffff;
 
@@ -130,6 +150,9 @@ class DevArena {
 // helper work reads. Null if a stream cannot be created.
 constexpr int kHelpers = 3;
 hipStream_t helper_stream(int k = 0);
+// The host waits for an event whose work is expected at once: polls it, which
+// returns some tens of microseconds sooner than hipEventSynchronize.
+hipError_t poll_event(hipEvent_t e);
 // `waiter` waits for everything enqueued on `signaller` so far.
 scan_status stream_wait(hipStream_t waiter, hipStream_t signaller);
 
@@ -175,18 +198,23 @@ void *pinned_get();
 void pinned_put(void *p);
 
 // A segmented sort in two steps. sort_classify enqueues, on stream s, the
-// classification of the segments [seg_off[i], seg_off[i+1]) by length (the
-// class lists live in `arena`, which must outlive sort_run) and a copy of the
-// class sizes to pinned host memory. sort_run then waits on the host for
-// those sizes (they size the grids; classified early, they are there before
-// they are needed) and enqueues on s the sort of every segment by key
-// descending, id ascending (ids distinct within a segment), reading
+// classification of the segments [seg_off[i], seg_off[i+1]) (total elements)
+// by length (the class lists live in `arena`, which must outlive sort_run; the
+// class sizes in `stats`, kSortStatsBytes of zeroed device memory), which
+// also writes the class sizes to pinned host memory. sort_run then waits on
+// the host for those sizes (they size the grids; classified early, they are
+// there before they are needed) and enqueues on s the sort of every segment
+// by key descending, id ascending (ids distinct within a segment), reading
 // key_in/id_in and writing key_out/id_out (no aliasing). s and the stream of
 // sort_classify may differ.
+constexpr size_t kSortStatsBytes = 64;
 struct SortClasses {
   int64_t nseg = 0;
   int32_t *lists = nullptr;
   int32_t *big_tiles_of = nullptr;
+  int64_t *tile_first = nullptr;  // first tile of each big segment
+  int32_t *tile_seg = nullptr;    // big segment of each tile
+  int64_t max_tiles = 0;          // what tile_seg holds
   void *stats = nullptr;       // device class sizes
   void *host = nullptr;        // pinned copy
   hipEvent_t ready = nullptr;  // recorded after the copy
@@ -196,8 +224,8 @@ struct SortClasses {
   SortClasses &operator=(const SortClasses &) = delete;
   ~SortClasses();
 };
-scan_status sort_classify(const int64_t *seg_off, int64_t nseg, DevArena &arena, hipStream_t s,
-                          SortClasses &c);
+scan_status sort_classify(const int64_t *seg_off, int64_t nseg, int64_t total, DevArena &arena, void *stats,
+                          hipStream_t s, SortClasses &c);
 scan_status sort_run(const SortClasses &c, const int64_t *seg_off, int64_t total, const double *key_in,
                      const int32_t *id_in, double *key_out, int32_t *id_out, hipStream_t s);
 // Both steps on s.

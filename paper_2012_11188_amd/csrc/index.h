@@ -34,16 +34,18 @@ struct IntersectStats {
   hipEvent_t ev_big_begin = nullptr, ev_big_end = nullptr;
 };
 
-// a2: the ownership plan, enqueued on s (the work lists live in `arena`,
-// which must outlive intersect_all), with a copy of its counts to pinned host
-// memory; intersect_all waits for them on the host. Launched early, the plan
-// is read back by a wait the caller makes anyway.
+// a2: the ownership plan, enqueued on s. The work lists live in `arena`, which
+// must outlive intersect_all; `counts` is kPlanCountBytes of zeroed device
+// memory, and what follows it belongs to the caller: the plan's last step
+// copies `words` int32 from `counts` to pinned `host` memory, and `ready` is
+// recorded then (before the window table). The caller waits for it before
+// intersect_all.
+constexpr size_t kPlanCountBytes = 32;
 struct IntersectPlan {
   int64_t n = 0, nnz = 0;
   int32_t *small_list = nullptr, *heavy_list = nullptr;
   void *big_list = nullptr, *counts = nullptr;  // device chunk list and counts
-  void *host = nullptr;                         // pinned copy of the counts
-  hipEvent_t ready = nullptr;
+  const void *host = nullptr;                   // the host's copy of the counts
   // helper streams already ordered after the plan (set by the caller), used
   // for the two small-owner kernels; null: intersect_all orders its own
   hipStream_t helper[2] = {nullptr, nullptr};
@@ -52,19 +54,18 @@ struct IntersectPlan {
   IntersectPlan() = default;
   IntersectPlan(const IntersectPlan &) = delete;
   IntersectPlan &operator=(const IntersectPlan &) = delete;
-  ~IntersectPlan();
 };
 scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, const int64_t *off,
                            const int32_t *deg, const int32_t *adj, int device, DevArena &arena, hipStream_t s,
-                           IntersectPlan &plan);
+                           void *counts, int32_t words, void *host, hipEvent_t ready, IntersectPlan &plan);
 
 // a2-a4: ownership plan, then intersection + similarity for every edge,
 // written into both CSR slots of sims (and counts if non-null).
 // after_launch (may be empty) runs on the host once every intersection
 // kernel is enqueued, so that the host enqueues other work (on streams it has
-// ordered itself) while the device intersects. plan (may be null: then it
-// plans on s itself) is one made by intersect_plan on s with the same cfg,
-// n, nnz and deg.
+// ordered itself) while the device intersects. plan is one made by
+// intersect_plan on s with the same cfg, n, nnz and deg, whose counts are on
+// the host.
 scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, const int64_t *off,
                           const int32_t *deg, const int32_t *adj, int kind, double *sims,
                           int32_t *counts, int device, hipStream_t s, IntersectStats *stats,

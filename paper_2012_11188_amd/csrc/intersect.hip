@@ -87,9 +87,10 @@ struct PlanCounts {
   int32_t big;
   int32_t counter;     // work counter of k_big_owner
   int32_t heavy;       // vertices of degree kLightDeg+1..small_max
-  int32_t heavy_next;  // work counter of the heavy small-vertex kernel
+  int32_t done;        // workgroups of k_plan that have finished
   int32_t pad[3];
 };
+static_assert(sizeof(PlanCounts) == kPlanCountBytes, "the maximum degrees follow the counts");
 
 constexpr int32_t kLightDeg = kWave;  // one wavefront per vertex up to this degree
 
@@ -124,7 +125,9 @@ constexpr int kPlanPer = 8;  // consecutive vertices per thread and tile
 // global atomic per list, and writes the entries in vertex order.
 __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, int64_t n, int small_max,
                                                        int spc, int32_t *small_list, int32_t *heavy_list,
-                                                       BigChunk *big_list, PlanCounts *pc) {
+                                                       BigChunk *big_list, PlanCounts *pc, int32_t words,
+                                                       int32_t *host) {
+  __shared__ int32_t last;
   __shared__ int32_t wsum[kPlanThreads / kWave];
   __shared__ int32_t tot_small, tot_heavy, tot_big, base_small, base_heavy, base_big;
   constexpr int64_t kTile = (int64_t)kPlanThreads * kPlanPer;
@@ -158,6 +161,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, int64
       for (int32_t j = 0; j < code[k]; ++j) big_list[pb++] = BigChunk{(int32_t)(v0 + k), j};
     }
   }
+  // The last block to finish hands the counts (and what follows them) to the
+  // host's pinned copy: a copy would be a launch more before the host goes on.
+  if (!last_workgroup(&pc->done, &last)) return;
+  for (int i = threadIdx.x; i < words; i += blockDim.x) host[i] = load_agent((const int32_t *)pc + i);
 }
 
 // ---------------------------------------------------------------------------
@@ -779,14 +786,6 @@ static size_t big_lds_bytes(int wbits, int spc) {
   return ((size_t)1 << wbits) / 8 + (size_t)spc * (8 + 4 * 8) + 4 + sizeof(BigShared);
 }
 
-IntersectPlan::~IntersectPlan() {
-  if (ready) {
-    (void)hipEventSynchronize(ready);  // the copy into `host` is done
-    (void)hipEventDestroy(ready);
-  }
-  pinned_put(host);
-}
-
 // The id window width of the large-owner kernel: cfg.wbits, no wider than
 // the id space and narrowed until its LDS fits.
 static int window_bits(const IntersectConfig &cfg, int64_t n, int lds_max) {
@@ -801,8 +800,7 @@ static int window_bits(const IntersectConfig &cfg, int64_t n, int lds_max) {
 
 scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, const int64_t *off,
                            const int32_t *deg, const int32_t *adj, int device, DevArena &arena, hipStream_t s,
-                           IntersectPlan &p) {
-  static_assert(sizeof(PlanCounts) <= kPinnedBlock, "plan counts fit a pinned block");
+                           void *counts, int32_t words, void *host, hipEvent_t ready, IntersectPlan &p) {
   p.n = n;
   p.nnz = nnz;
   if (nnz == 0) return SCAN_OK;
@@ -811,21 +809,16 @@ scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, c
   p.wbits = window_bits(cfg, n, lds_max);
   const int32_t nwin = (int32_t)((n + ((int64_t)1 << p.wbits) - 1) >> p.wbits);
   BigChunk *big_list;
-  PlanCounts *pc;
+  PlanCounts *pc = (PlanCounts *)counts;
   SCAN_TRY(arena.alloc(&p.small_list, n));
   SCAN_TRY(arena.alloc(&p.heavy_list, n));
   SCAN_TRY(arena.alloc(&big_list, nnz / cfg.spc + n + 1));
-  SCAN_TRY(arena.alloc(&pc, 1));
   p.big_list = big_list;
-  p.counts = pc;
-  p.host = pinned_get();
-  if (!p.host) return fail(SCAN_ENOMEM, "pinned host allocation failed");
-  SCAN_HIP_TRY(hipEventCreateWithFlags(&p.ready, hipEventDisableTiming));
-  SCAN_HIP_TRY(hipMemsetAsync(pc, 0, sizeof(PlanCounts), s));
-  k_plan<<<grid_for(n, kPlanThreads * kPlanPer, 2048), kPlanThreads, 0, s>>>(deg, n, cfg.small_max, cfg.spc,
-                                                                             p.small_list, p.heavy_list, big_list, pc);
-  SCAN_HIP_TRY(hipMemcpyAsync(p.host, pc, sizeof(PlanCounts), hipMemcpyDeviceToHost, s));
-  SCAN_HIP_TRY(hipEventRecord(p.ready, s));
+  p.counts = counts;
+  p.host = host;
+  k_plan<<<grid_for(n, kPlanThreads * kPlanPer, 2048), kPlanThreads, 0, s>>>(
+      deg, n, cfg.small_max, cfg.spc, p.small_list, p.heavy_list, big_list, pc, words, (int32_t *)host);
+  SCAN_HIP_TRY(hipEventRecord(ready, s));
   // Ids spanning several windows: the window table follows the plan (it
   // needs only the CSR, and nothing when there are no bitmap owners), so
   // that the large-owner kernel can start as soon as the host has read the
@@ -850,13 +843,7 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   const int wbits = window_bits(cfg, n, lds_max);
   if (big_lds_bytes(wbits, cfg.spc) > (size_t)lds_max) return fail(SCAN_EINVAL, "chunk size too large for LDS");
 
-  DevArena tmp(s);
-  IntersectPlan own;
-  if (!plan) {
-    SCAN_TRY(intersect_plan(cfg, n, nnz, off, deg, adj, device, tmp, s, own));
-    plan = &own;
-  }
-  if (plan->n != n || plan->nnz != nnz || !plan->ready || plan->wbits != wbits)
+  if (!plan || plan->n != n || plan->nnz != nnz || !plan->host || plan->wbits != wbits)
     return fail(SCAN_EINVAL, "plan made for another graph");
   const int32_t *small_list = plan->small_list, *heavy_list = plan->heavy_list;
   const BigChunk *big_list = (const BigChunk *)plan->big_list;
@@ -864,7 +851,6 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   // The host reads the work counts to size the grids: one block per vertex
   // lets the hardware balance the uneven rows, which persistent grids with a
   // static split do not.
-  SCAN_HIP_TRY(hipEventSynchronize(plan->ready));
   const PlanCounts h = *(const PlanCounts *)plan->host;
   if (stats) {
     stats->wbits = wbits;

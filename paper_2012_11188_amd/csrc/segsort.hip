@@ -9,6 +9,8 @@
 //   len >  4096   4096-element LDS tiles, then merge-path passes through HBM
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace scan {
@@ -88,8 +90,41 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_apply(const T *in, int64_t 
 
 int64_t scan_workspace_elems(int64_t n) { return (n + kScanTile - 1) / kScanTile + 2; }
 
+// Short inputs: one workgroup, one launch instead of three (4 against 25 us
+// with the gaps, up to a few thousand entries).
+constexpr int64_t kScanOne = 8192;
+template <class T>
+__global__ __launch_bounds__(kScanBlock) void k_scan_one(const T *in, int64_t n, int64_t *out) {
+  __shared__ int64_t sh[kScanBlock];
+  int64_t carry = 0;
+  for (int64_t base = 0; base < n; base += kScanTile) {
+    const int64_t b = base + (int64_t)threadIdx.x * kScanPer;
+    T v[kScanPer];
+    int64_t s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      v[k] = b + k < n ? in[b + k] : (T)0;
+      s += (int64_t)v[k];
+    }
+    int64_t total;
+    int64_t run = carry + block_exclusive_sum(s, sh, &total);
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      if (b + k < n) out[b + k] = run;
+      run += (int64_t)v[k];
+    }
+    carry += total;
+  }
+  if (threadIdx.x == 0) out[n] = carry;
+}
+
 template <class T>
 static scan_status scan_impl(const T *in, int64_t *out, int64_t n, int64_t *ws, hipStream_t s) {
+  if (n <= kScanOne) {
+    k_scan_one<T><<<1, kScanBlock, 0, s>>>(in, n, out);
+    SCAN_HIP_TRY(hipGetLastError());
+    return SCAN_OK;
+  }
   int64_t nb = (n + kScanTile - 1) / kScanTile;
   if (nb == 0) nb = 1;
   k_scan_reduce<T><<<(unsigned)nb, kScanBlock, 0, s>>>(in, n, ws);
@@ -133,7 +168,9 @@ struct SortStats {
   int32_t count[kNumCls];
   int32_t big_tiles;
   int32_t max_passes;
+  int32_t done;  // workgroups of k_classify that have finished
 };
+static_assert(sizeof(SortStats) <= kSortStatsBytes, "the callers' zeroed space holds the class sizes");
 
 __device__ __forceinline__ int passes_for(int64_t len) {
   int64_t tiles = (len + kBigTile - 1) / kBigTile;
@@ -145,7 +182,10 @@ __device__ __forceinline__ int passes_for(int64_t len) {
 // Segments are classified in tiles of kClassTile: a block counts its tile's
 // classes in LDS, reserves list space with one global atomic per class, then
 // places the segments (wave-aggregated LDS cursors). Few global atomics: a
-// per-wavefront reservation stalls on a handful of contended addresses.
+// per-wavefront reservation stalls on a handful of contended addresses. The
+// last block to finish numbers the tiles of the big segments (tile_first,
+// tile_seg) and writes the sizes to the host's pinned copy, so that neither
+// takes launches of its own.
 constexpr int kClassTile = 4096;
 
 __device__ __forceinline__ int seg_class(int64_t len) {
@@ -156,10 +196,33 @@ __device__ __forceinline__ int seg_class(int64_t len) {
   return c;
 }
 
+// tile_first[b] = first global tile of big segment b (tile_first[nbig]: their
+// number), tile_seg[t] = the big segment of tile t; one workgroup of
+// kScanBlock threads.
+__device__ __forceinline__ void plan_big_tiles(int32_t nbig, const int32_t *big_tiles_of, int64_t *tile_first,
+                                               int32_t *tile_seg, int64_t max_tiles, int64_t *sums) {
+  int64_t carry = 0;
+  for (int32_t b0 = 0; b0 < nbig; b0 += kScanBlock) {
+    const int32_t b = b0 + (int32_t)threadIdx.x;
+    const int32_t tiles = b < nbig ? load_agent(&big_tiles_of[b]) : 0;
+    int64_t total;
+    const int64_t first = carry + block_exclusive_sum(tiles, sums, &total);
+    if (b < nbig) {
+      tile_first[b] = first;
+      for (int32_t t = 0; t < tiles && first + t < max_tiles; ++t) tile_seg[first + t] = b;
+    }
+    carry += total;
+  }
+  if (threadIdx.x == 0) tile_first[nbig] = carry;
+}
+
 __global__ __launch_bounds__(256) void k_classify(const int64_t *seg_off, int64_t nseg,
                                                   int32_t *lists, int64_t cap, SortStats *st,
-                                                  int32_t *big_tiles_of) {
+                                                  int32_t *big_tiles_of, int64_t *tile_first, int32_t *tile_seg,
+                                                  int64_t max_tiles, SortStats *host) {
   __shared__ int32_t cnt[kNumCls], base[kNumCls], cur[kNumCls];
+  __shared__ int64_t sums[kScanBlock];
+  __shared__ int32_t last;
   __shared__ int32_t tiles_sum, passes_max;
   const int lane = threadIdx.x & (kWave - 1);
   const uint64_t below = (1ull << lane) - 1ull;
@@ -207,12 +270,18 @@ __global__ __launch_bounds__(256) void k_classify(const int64_t *seg_off, int64_
         if (pending && c == k) {
           const int32_t pos = base[k] + b + __popcll(m & below);
           lists[k * cap + pos] = (int32_t)i;
-          if (k == kClsBig) big_tiles_of[pos] = (int32_t)((len + kBigTile - 1) / kBigTile);
+          if (k == kClsBig)
+            __hip_atomic_store(&big_tiles_of[pos], (int32_t)((len + kBigTile - 1) / kBigTile), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);  // read by the last workgroup
           pending = false;
         }
       }
     }
   }
+  if (!last_workgroup(&st->done, &last)) return;
+  plan_big_tiles(load_agent(&st->count[kClsBig]), big_tiles_of, tile_first, tile_seg, max_tiles, sums);
+  static_assert(sizeof(SortStats) / 4 <= 256, "one thread per word");
+  if (threadIdx.x < sizeof(SortStats) / 4) ((int32_t *)host)[threadIdx.x] = load_agent((const int32_t *)st + threadIdx.x);
 }
 
 // Class kernels read their segment counts (written by k_classify) from
@@ -259,36 +328,41 @@ __device__ __forceinline__ void group_bitonic(uint64_t &k, int32_t &id, int pos)
 }
 
 // Segments of at most S elements; a wavefront sorts kWave / S of them, one
-// per group of S lanes.
+// per group of S lanes: set w of the list.
+template <int S>
+__device__ __forceinline__ void sort_group(int64_t w, int32_t count, const int64_t *seg_off, const int32_t *list,
+                                           const double *kin, const int32_t *iin, double *kout, int32_t *iout) {
+  constexpr int G = kWave / S;
+  const int lane = threadIdx.x & (kWave - 1), grp = lane / S, pos = lane % S;
+  const int64_t idx = w * G + grp;
+  int64_t o = 0;
+  int len = 0;
+  if (idx < count) {
+    const int32_t sg = list[idx];
+    o = seg_off[sg];
+    len = (int)(seg_off[sg + 1] - o);
+  }
+  uint64_t k = kPadKey;
+  int32_t id = kPadId;
+  if (pos < len) {
+    k = desc_key(kin[o + pos]);
+    id = iin[o + pos];
+  }
+  group_bitonic<S>(k, id, pos);
+  if (pos < len) {
+    kout[o + pos] = key_to_sim(k);
+    iout[o + pos] = id;
+  }
+}
+
 template <int S>
 __global__ __launch_bounds__(256) void k_sort_group(const int64_t *seg_off, const int32_t *list,
                                                     const int32_t *countp, const double *kin,
                                                     const int32_t *iin, double *kout, int32_t *iout) {
-  constexpr int G = kWave / S;
   const int32_t count = *countp;
-  const int lane = threadIdx.x & (kWave - 1), grp = lane / S, pos = lane % S;
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
-  for (int64_t w = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; w * G < count; w += nw) {
-    const int64_t idx = w * G + grp;
-    int64_t o = 0;
-    int len = 0;
-    if (idx < count) {
-      const int32_t sg = list[idx];
-      o = seg_off[sg];
-      len = (int)(seg_off[sg + 1] - o);
-    }
-    uint64_t k = kPadKey;
-    int32_t id = kPadId;
-    if (pos < len) {
-      k = desc_key(kin[o + pos]);
-      id = iin[o + pos];
-    }
-    group_bitonic<S>(k, id, pos);
-    if (pos < len) {
-      kout[o + pos] = key_to_sim(k);
-      iout[o + pos] = id;
-    }
-  }
+  for (int64_t w = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; w * (kWave / S) < count; w += nw)
+    sort_group<S>(w, count, seg_off, list, kin, iin, kout, iout);
 }
 
 // Block merge sort of up to THREADS * ITEMS (key, id) pairs, ascending by
@@ -300,6 +374,21 @@ __global__ __launch_bounds__(256) void k_sort_group(const int64_t *seg_off, cons
 // slot per 16 so that the blocked runs of consecutive threads start on
 // different banks.
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 4); }
+
+//
+// A sort of 64 threads is one wavefront's: it needs no workgroup barrier (LDS
+// operations of a wavefront complete in order), so several of them run side
+// by side in a larger workgroup.
+template <int THREADS>
+__device__ __forceinline__ void sort_sync() {
+  if constexpr (THREADS == kWave) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
 
 template <int THREADS, int ITEMS>
 struct BlockSort {
@@ -344,7 +433,7 @@ struct BlockSort {
         s.K[lds_pad(o + x)] = k[x];
         s.I[lds_pad(o + x)] = id[x];
       }
-      __syncthreads();
+      sort_sync<THREADS>();
       const int a0 = o & ~(2 * w - 1), b0 = a0 + w, diag = o - a0;
       int lo = diag > w ? diag - w : 0, hi = diag < w ? diag : w;
       while (lo < hi) {  // A elements among the first diag outputs
@@ -376,7 +465,7 @@ struct BlockSort {
           rb = take_b ? rn : rb;
         }
       }
-      __syncthreads();
+      sort_sync<THREADS>();
     }
   }
 
@@ -387,7 +476,7 @@ struct BlockSort {
     // The thread index passes through an empty asm statement, so the
     // per-element addresses derived from it are computed per call: hoisted
     // out of a caller's loop they occupy over a hundred registers.
-    int t = threadIdx.x;
+    int t = threadIdx.x % THREADS;
     asm volatile("" : "+v"(t));
 #pragma unroll
     for (int x = 0; x < ITEMS; ++x) {
@@ -398,7 +487,7 @@ struct BlockSort {
       s.K[lds_pad(i)] = key;
       s.I[lds_pad(i)] = idv;
     }
-    __syncthreads();
+    sort_sync<THREADS>();
     uint64_t k[ITEMS];
     int32_t id[ITEMS];
 #pragma unroll
@@ -406,7 +495,7 @@ struct BlockSort {
       k[x] = s.K[lds_pad(t * ITEMS + x)];
       id[x] = s.I[lds_pad(t * ITEMS + x)];
     }
-    __syncthreads();
+    sort_sync<THREADS>();
     thread_sort(k, id);
     merge_stages(s, k, id, t);
 #pragma unroll
@@ -414,15 +503,30 @@ struct BlockSort {
       s.K[lds_pad(t * ITEMS + x)] = k[x];
       s.I[lds_pad(t * ITEMS + x)] = id[x];
     }
-    __syncthreads();
+    sort_sync<THREADS>();
 #pragma unroll
     for (int x = 0; x < ITEMS; ++x) {
       const int i = x * THREADS + t;
       if (i < len) store(i, s.K[lds_pad(i)], s.I[lds_pad(i)]);
     }
-    __syncthreads();
+    sort_sync<THREADS>();
   }
 };
+
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ void sort_segment(typename BlockSort<THREADS, ITEMS>::Smem &sm, int64_t o, int len,
+                                             const double *kin, const int32_t *iin, double *kout, int32_t *iout) {
+  BlockSort<THREADS, ITEMS>::run(
+      sm, len,
+      [&](int i, uint64_t &k, int32_t &id) {
+        k = desc_key(kin[o + i]);
+        id = iin[o + i];
+      },
+      [&](int i, uint64_t k, int32_t id) {
+        kout[o + i] = key_to_sim(k);
+        iout[o + i] = id;
+      });
+}
 
 // One block per segment of the class (len <= THREADS * ITEMS).
 template <int THREADS, int ITEMS>
@@ -431,32 +535,36 @@ __global__ __launch_bounds__(THREADS) void k_sort_block(const int64_t *seg_off, 
                                                         const int32_t *iin, double *kout,
                                                         int32_t *iout) {
   const int32_t count = *countp;
-  using BS = BlockSort<THREADS, ITEMS>;
-  __shared__ typename BS::Smem sm;
+  __shared__ typename BlockSort<THREADS, ITEMS>::Smem sm;
   for (int64_t b = blockIdx.x; b < count; b += gridDim.x) {
     const int64_t o = seg_off[list[b]];
-    const int len = (int)(seg_off[list[b] + 1] - o);
-    BS::run(
-        sm, len,
-        [&](int i, uint64_t &k, int32_t &id) {
-          k = desc_key(kin[o + i]);
-          id = iin[o + i];
-        },
-        [&](int i, uint64_t k, int32_t id) {
-          kout[o + i] = key_to_sim(k);
-          iout[o + i] = id;
-        });
+    sort_segment<THREADS, ITEMS>(sm, o, (int)(seg_off[list[b] + 1] - o), kin, iin, kout, iout);
   }
 }
 
-// Big segments: tile_seg[t] = index into the big list; tile_first[b] = first
-// global tile of big segment b.
-__global__ void k_big_tiles(const int32_t *big_tiles_of, const int64_t *tile_first, const int32_t *nbigp,
-                            int32_t *tile_seg) {
-  const int32_t nbig = *nbigp;
-  for (int64_t b = blockIdx.x; b < nbig; b += gridDim.x)
-    for (int64_t t = threadIdx.x; t < big_tiles_of[b]; t += blockDim.x)
-      tile_seg[tile_first[b] + t] = (int32_t)b;
+using BigSort = BlockSort<kSortBlock, kBigTile / kSortBlock>;
+
+// Tile t of the big segments, sorted into KA / IA.
+__device__ __forceinline__ void sort_big_tile(BigSort::Smem &sm, int64_t t, const int64_t *seg_off,
+                                              const int32_t *big_list, const int32_t *tile_seg,
+                                              const int64_t *tile_first, const double *kin, const int32_t *iin,
+                                              uint64_t *KA, int32_t *IA) {
+  const int32_t b = tile_seg[t];
+  const int64_t seg = big_list[b];
+  const int64_t o = seg_off[seg];
+  const int64_t len = seg_off[seg + 1] - o;
+  const int64_t start = o + (t - tile_first[b]) * kBigTile;
+  const int cnt = (int)min((int64_t)kBigTile, len - (start - o));
+  BigSort::run(
+      sm, cnt,
+      [&](int i, uint64_t &k, int32_t &id) {
+        k = desc_key(kin[start + i]);
+        id = iin[start + i];
+      },
+      [&](int i, uint64_t k, int32_t id) {
+        KA[start + i] = k;
+        IA[start + i] = id;
+      });
 }
 
 __global__ __launch_bounds__(kSortBlock) void k_big_tile_sort(
@@ -464,25 +572,90 @@ __global__ __launch_bounds__(kSortBlock) void k_big_tile_sort(
     const int64_t *tile_first, const int32_t *ntilesp, const double *kin, const int32_t *iin,
     uint64_t *KA, int32_t *IA) {
   const int64_t ntiles = *ntilesp;
-  using BS = BlockSort<kSortBlock, kBigTile / kSortBlock>;
-  __shared__ typename BS::Smem sm;
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int32_t b = tile_seg[t];
-    const int64_t seg = big_list[b];
-    const int64_t o = seg_off[seg];
-    const int64_t len = seg_off[seg + 1] - o;
-    const int64_t start = o + (t - tile_first[b]) * kBigTile;
-    const int cnt = (int)min((int64_t)kBigTile, len - (start - o));
-    BS::run(
-        sm, cnt,
-        [&](int i, uint64_t &k, int32_t &id) {
-          k = desc_key(kin[start + i]);
-          id = iin[start + i];
-        },
-        [&](int i, uint64_t k, int32_t id) {
-          KA[start + i] = k;
-          IA[start + i] = id;
-        });
+  __shared__ BigSort::Smem sm;
+  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x)
+    sort_big_tile(sm, t, seg_off, big_list, tile_seg, tile_first, kin, iin, KA, IA);
+}
+
+// Every class in one launch, for sorts whose class kernels would each be a
+// few microseconds of work behind a launch (60k-vertex R-MAT graph, 1.8M
+// elements: 11 launches of the neighbour order 158 us, this one 44): workgroups of kSortBlock
+// threads, the longest classes first; a workgroup's class follows from its
+// number. Up to 512 elements a wavefront sorts a segment by itself.
+enum {
+  kRoleBig, kRole4096, kRole2048, kRole1024, kRole512, kRole256, kRole128, kRole64, kRole32, kRole16, kRole8,
+  kRoleCopy, kNumRoles
+};
+struct SortRoles {
+  int32_t end[kNumRoles];  // workgroups up to and including the role's
+};
+
+__global__ __launch_bounds__(kSortBlock) void k_sort_all(SortRoles roles, const int64_t *seg_off,
+                                                         const int32_t *lists, int64_t nseg, const SortStats *st,
+                                                         const int32_t *tile_seg, const int64_t *tile_first,
+                                                         const double *kin, const int32_t *iin, double *kout,
+                                                         int32_t *iout, uint64_t *KA, int32_t *IA) {
+  constexpr int kWaves = kSortBlock / kWave;
+  __shared__ union {
+    BigSort::Smem big;
+    BlockSort<kSortBlock, 8>::Smem b2048;
+    BlockSort<kSortBlock, 4>::Smem b1024;
+    BlockSort<kWave, 8>::Smem w512[kWaves];
+    BlockSort<kWave, 4>::Smem w256[kWaves];
+    BlockSort<kWave, 2>::Smem w128[kWaves];
+  } sm;
+  const int wave = threadIdx.x / kWave;
+  int role = 0;
+  while (role < kNumRoles - 1 && (int32_t)blockIdx.x >= roles.end[role]) ++role;
+  const int64_t b = (int32_t)blockIdx.x - (role ? roles.end[role - 1] : 0);
+  const int64_t w = b * kWaves + wave;
+  auto list = [&](int cls) { return lists + cls * nseg; };
+  auto segment = [&](int cls, int64_t i, int64_t &o) -> int {  // -1: past the list
+    if (i >= st->count[cls]) return -1;
+    const int32_t sg = list(cls)[i];
+    o = seg_off[sg];
+    return (int)(seg_off[sg + 1] - o);
+  };
+  int64_t o = 0;
+  int len;
+  switch (role) {
+    case kRoleBig: sort_big_tile(sm.big, b, seg_off, list(kClsBig), tile_seg, tile_first, kin, iin, KA, IA); break;
+    case kRole4096:
+      len = segment(kClsB4096, b, o);
+      if (len >= 0) sort_segment<kSortBlock, kBigTile / kSortBlock>(sm.big, o, len, kin, iin, kout, iout);
+      break;
+    case kRole2048:
+      len = segment(kClsB2048, b, o);
+      if (len >= 0) sort_segment<kSortBlock, 8>(sm.b2048, o, len, kin, iin, kout, iout);
+      break;
+    case kRole1024:
+      len = segment(kClsB1024, b, o);
+      if (len >= 0) sort_segment<kSortBlock, 4>(sm.b1024, o, len, kin, iin, kout, iout);
+      break;
+    case kRole512:
+      len = segment(kClsB512, w, o);
+      if (len >= 0) sort_segment<kWave, 8>(sm.w512[wave], o, len, kin, iin, kout, iout);
+      break;
+    case kRole256:
+      len = segment(kClsB256, w, o);
+      if (len >= 0) sort_segment<kWave, 4>(sm.w256[wave], o, len, kin, iin, kout, iout);
+      break;
+    case kRole128:
+      len = segment(kClsB128, w, o);
+      if (len >= 0) sort_segment<kWave, 2>(sm.w128[wave], o, len, kin, iin, kout, iout);
+      break;
+    case kRole64: sort_group<64>(w, st->count[kClsW64], seg_off, list(kClsW64), kin, iin, kout, iout); break;
+    case kRole32: sort_group<32>(w, st->count[kClsW32], seg_off, list(kClsW32), kin, iin, kout, iout); break;
+    case kRole16: sort_group<16>(w, st->count[kClsW16], seg_off, list(kClsW16), kin, iin, kout, iout); break;
+    case kRole8: sort_group<8>(w, st->count[kClsW8], seg_off, list(kClsW8), kin, iin, kout, iout); break;
+    default: {
+      const int64_t i = b * kSortBlock + threadIdx.x;
+      if (i < st->count[kClsCopy]) {
+        const int64_t at = seg_off[list(kClsCopy)[i]];
+        kout[at] = kin[at];
+        iout[at] = iin[at];
+      }
+    }
   }
 }
 
@@ -573,6 +746,11 @@ __global__ __launch_bounds__(256) void k_big_split(const int64_t *seg_off, const
 // max_passes; a segment needing P passes does its pass i = q - (max_passes -
 // P) when i >= 1, merging runs of width kBigTile << (i-1). Pass i reads A if
 // i is odd, else B; writes B / A, or the final output when i == P.
+// kOwnSplits: the workgroup finds the splits of its tile and of the next one
+// itself (two wavefronts, side by side) instead of reading k_big_split's: one
+// launch a pass, for passes of few tiles, where a launch costs more than the
+// search.
+template <bool kOwnSplits>
 __global__ __launch_bounds__(kSortBlock) void k_big_merge(
     const int64_t *seg_off, const int32_t *big_list, const int32_t *tile_seg,
     const int64_t *tile_first, const int32_t *ntilesp, int q, const int32_t *max_passesp,
@@ -583,6 +761,7 @@ __global__ __launch_bounds__(kSortBlock) void k_big_merge(
   const int64_t ntiles = *ntilesp;
   __shared__ uint64_t K[kBigTile + kBigTile / 16];  // padded indices (lds_pad)
   __shared__ int32_t I[kBigTile + kBigTile / 16];
+  __shared__ int64_t own[2];
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const MergePair m = merge_pair(seg_off, big_list, tile_seg, tile_first, t, q, max_passes);
     if (m.i < 1) continue;  // uniform across the block
@@ -601,8 +780,21 @@ __global__ __launch_bounds__(kSortBlock) void k_big_merge(
     const int32_t *BI = sI + o + m.b0;
     // The tile's outputs take A[i0, i1) and B[j0, j1); the next tile of the
     // pair starts where this one ends.
-    const int64_t i0 = split[t];
-    const int64_t i1 = m.ostart + cnt == m.la + m.lb ? m.la : split[t + 1];
+    int64_t i0, i1;
+    if constexpr (kOwnSplits) {
+      const int wave = tid / kWave;
+      if (wave < 2) {
+        const int64_t at = m.ostart + (wave ? cnt : 0);
+        const int64_t r = wave_co_rank(AK, AI, m.la, BK, BI, m.lb, at);
+        if (tid % kWave == 0) own[wave] = r;
+      }
+      __syncthreads();
+      i0 = own[0];
+      i1 = own[1];
+    } else {
+      i0 = split[t];
+      i1 = m.ostart + cnt == m.la + m.lb ? m.la : split[t + 1];
+    }
     const int64_t j0 = m.ostart - i0, j1 = m.ostart + cnt - i1;
     const int na = (int)(i1 - i0), nb = (int)(j1 - j0);
     __syncthreads();  // the previous tile's readers of K / I are done
@@ -696,6 +888,15 @@ __global__ __launch_bounds__(kSortBlock) void k_big_merge(
   }
 }
 
+// Sorts of up to kFusedTotal elements run every class in one launch; passes
+// of up to kOwnSplitTiles tiles find their own splits. Past these sizes every
+// class fills the chip by itself, with less LDS per wavefront, and the splits
+// of thousands of tiles are found faster by a wavefront each (R-MAT-20: the
+// 726 tiles of the neighbour order take 178 us of passes with own splits, 245
+// with split launches; the 7,032 tiles of the core order are the other case).
+constexpr int64_t kFusedTotal = 4 << 20;
+constexpr int64_t kOwnSplitTiles = 1024;
+
 SortClasses::~SortClasses() {
   if (ready) {
     (void)hipEventSynchronize(ready);  // the copy into `host` is done
@@ -704,25 +905,39 @@ SortClasses::~SortClasses() {
   pinned_put(host);
 }
 
-scan_status sort_classify(const int64_t *seg_off, int64_t nseg, DevArena &arena, hipStream_t s,
-                          SortClasses &c) {
+scan_status sort_plan(int64_t nseg, int64_t total, DevArena &arena, void *stats, SortClasses &c) {
   static_assert(sizeof(SortStats) <= kPinnedBlock, "class sizes fit a pinned block");
   c.nseg = nseg;
-  c.stream = s;
   if (nseg <= 0) return SCAN_OK;
-  SortStats *st;
+  // A big segment has more than kBigTile elements, so there are at most
+  // total / kBigTile of them and twice as many tiles.
+  c.max_tiles = total / kBigTile + std::min(nseg, total / kBigTile);
   SCAN_TRY(arena.alloc(&c.lists, kNumCls * nseg));
   SCAN_TRY(arena.alloc(&c.big_tiles_of, nseg));
-  SCAN_TRY(arena.alloc(&st, 1));
-  c.stats = st;
+  SCAN_TRY(arena.alloc(&c.tile_first, nseg + 1));
+  SCAN_TRY(arena.alloc(&c.tile_seg, c.max_tiles));
+  c.stats = stats;
   c.host = pinned_get();
   if (!c.host) return fail(SCAN_ENOMEM, "pinned host allocation failed");
+  return SCAN_OK;
+}
+
+scan_status sort_classified(SortClasses &c, hipStream_t s) {
+  c.stream = s;
+  if (c.nseg <= 0) return SCAN_OK;
   SCAN_HIP_TRY(hipEventCreateWithFlags(&c.ready, hipEventDisableTiming));
-  SCAN_HIP_TRY(hipMemsetAsync(st, 0, sizeof(SortStats), s));
-  k_classify<<<grid_for(nseg, kClassTile, 2048), 256, 0, s>>>(seg_off, nseg, c.lists, nseg, st, c.big_tiles_of);
-  SCAN_HIP_TRY(hipMemcpyAsync(c.host, st, sizeof(SortStats), hipMemcpyDeviceToHost, s));
   SCAN_HIP_TRY(hipEventRecord(c.ready, s));
   return SCAN_OK;
+}
+
+scan_status sort_classify(const int64_t *seg_off, int64_t nseg, int64_t total, DevArena &arena, void *stats,
+                          hipStream_t s, SortClasses &c) {
+  SCAN_TRY(sort_plan(nseg, total, arena, stats, c));
+  if (nseg > 0)
+    k_classify<<<grid_for(nseg, kClassTile, 2048), 256, 0, s>>>(seg_off, nseg, c.lists, nseg, (SortStats *)stats,
+                                                                c.big_tiles_of, c.tile_first, c.tile_seg, c.max_tiles,
+                                                                (SortStats *)c.host);
+  return sort_classified(c, s);
 }
 
 scan_status segmented_sort(const int64_t *seg_off, int64_t nseg, int64_t total,
@@ -731,7 +946,10 @@ scan_status segmented_sort(const int64_t *seg_off, int64_t nseg, int64_t total,
   if (nseg <= 0 || total <= 0) return SCAN_OK;
   DevArena arena(s);
   SortClasses c;
-  SCAN_TRY(sort_classify(seg_off, nseg, arena, s, c));
+  unsigned char *stats;
+  SCAN_TRY(arena.alloc(&stats, kSortStatsBytes));
+  SCAN_HIP_TRY(hipMemsetAsync(stats, 0, kSortStatsBytes, s));
+  SCAN_TRY(sort_classify(seg_off, nseg, total, arena, stats, s, c));
   return sort_run(c, seg_off, total, key_in, id_in, key_out, id_out, s);
 }
 
@@ -742,12 +960,65 @@ scan_status sort_run(const SortClasses &c, const int64_t *seg_off, int64_t total
   DevArena arena(s);
   // The host waits for the class sizes (they size each grid: one block or
   // wavefront per segment, which the hardware balances).
-  SCAN_HIP_TRY(hipEventSynchronize(c.ready));
+  SCAN_HIP_TRY(poll_event(c.ready));
   const SortStats h = *(const SortStats *)c.host;
+  if (h.big_tiles > c.max_tiles) return fail(SCAN_EGRAPH, "segments are longer than the elements they hold");
   if (c.stream != s) SCAN_HIP_TRY(hipStreamWaitEvent(s, c.ready, 0));  // the class lists
   SortStats *st = (SortStats *)c.stats;
-  const int32_t *lists = c.lists, *big_tiles_of = c.big_tiles_of;
+  const int32_t *lists = c.lists;
   const int32_t *cnt = st->count;  // device copies of the class sizes
+  const int64_t ntiles = h.big_tiles;
+  const int32_t *big_list = lists + kClsBig * nseg;
+  int64_t *split = nullptr;
+  int32_t *IA = nullptr, *IB = nullptr;
+  uint64_t *KA = nullptr, *KB = nullptr;
+  if (ntiles) {
+    SCAN_TRY(arena.alloc(&split, ntiles));
+    SCAN_TRY(arena.alloc(&KA, total));
+    SCAN_TRY(arena.alloc(&KB, total));
+    SCAN_TRY(arena.alloc(&IA, total));
+    SCAN_TRY(arena.alloc(&IB, total));
+  }
+  auto merge_passes = [&](hipStream_t bs) {
+    const bool own = ntiles <= kOwnSplitTiles;
+    for (int q = 1; q <= h.max_passes; ++q) {
+      if (!own)
+        k_big_split<<<grid_for(ntiles * kWave, 256), 256, 0, bs>>>(seg_off, big_list, c.tile_seg, c.tile_first,
+                                                                  &st->big_tiles, q, &st->max_passes, KA, IA, KB,
+                                                                  IB, split);
+      const auto merge = own ? k_big_merge<true> : k_big_merge<false>;
+      merge<<<grid_for(ntiles, 1), kSortBlock, 0, bs>>>(seg_off, big_list, c.tile_seg, c.tile_first,
+                                                       &st->big_tiles, q, &st->max_passes, split, KA, IA, KB, IB,
+                                                       key_out, id_out);
+    }
+  };
+  if (total <= kFusedTotal) {
+    SortRoles roles;
+    int64_t blocks = 0;
+    constexpr int kWaves = kSortBlock / kWave;
+    auto add = [&](int role, int64_t work, int64_t per_block) {
+      blocks += (work + per_block - 1) / per_block;
+      roles.end[role] = (int32_t)blocks;
+    };
+    add(kRoleBig, ntiles, 1);
+    add(kRole4096, h.count[kClsB4096], 1);
+    add(kRole2048, h.count[kClsB2048], 1);
+    add(kRole1024, h.count[kClsB1024], 1);
+    add(kRole512, h.count[kClsB512], kWaves);
+    add(kRole256, h.count[kClsB256], kWaves);
+    add(kRole128, h.count[kClsB128], kWaves);
+    add(kRole64, h.count[kClsW64], kWaves);
+    add(kRole32, h.count[kClsW32], 2 * kWaves);
+    add(kRole16, h.count[kClsW16], 4 * kWaves);
+    add(kRole8, h.count[kClsW8], 8 * kWaves);
+    add(kRoleCopy, h.count[kClsCopy], kSortBlock);
+    if (blocks)
+      k_sort_all<<<(unsigned)blocks, kSortBlock, 0, s>>>(roles, seg_off, lists, nseg, st, c.tile_seg, c.tile_first,
+                                                         key_in, id_in, key_out, id_out, KA, IA);
+    merge_passes(s);
+    SCAN_HIP_TRY(hipGetLastError());
+    return SCAN_OK;
+  }
   // The big segments' chain of launches (tile sorts, merge passes) and the
   // other classes' kernels run beside each other, the longer of the two on s
   // and the other on a helper stream (the join at the end then waits for the
@@ -786,33 +1057,10 @@ scan_status sort_run(const SortClasses &c, const int64_t *seg_off, int64_t total
   SCAN_BLOCK(256, 8, kClsB2048, gs)
   SCAN_BLOCK(kSortBlock, kBigTile / kSortBlock, kClsB4096, gs)
 #undef SCAN_BLOCK
-  if (h.count[kClsBig]) {
-    const int32_t nbig = h.count[kClsBig];
-    const int64_t ntiles = h.big_tiles;
-    int64_t *tile_first, *scan_ws, *split;
-    int32_t *tile_seg, *IA, *IB;
-    uint64_t *KA, *KB;
-    SCAN_TRY(arena.alloc(&tile_first, nbig + 1));
-    SCAN_TRY(arena.alloc(&scan_ws, scan_workspace_elems(nbig)));
-    SCAN_TRY(arena.alloc(&tile_seg, ntiles));
-    SCAN_TRY(arena.alloc(&split, ntiles));
-    SCAN_TRY(arena.alloc(&KA, total));
-    SCAN_TRY(arena.alloc(&KB, total));
-    SCAN_TRY(arena.alloc(&IA, total));
-    SCAN_TRY(arena.alloc(&IB, total));
-    SCAN_TRY(exclusive_scan(big_tiles_of, tile_first, nbig, scan_ws, bs));
-    const int32_t *big_list = lists + kClsBig * nseg;
-    k_big_tiles<<<grid_for(nbig, 1, 4096), 256, 0, bs>>>(big_tiles_of, tile_first, cnt + kClsBig, tile_seg);
-    k_big_tile_sort<<<grid_for(ntiles, 1), kSortBlock, 0, bs>>>(seg_off, big_list, tile_seg, tile_first,
+  if (ntiles) {
+    k_big_tile_sort<<<grid_for(ntiles, 1), kSortBlock, 0, bs>>>(seg_off, big_list, c.tile_seg, c.tile_first,
                                                                &st->big_tiles, key_in, id_in, KA, IA);
-    for (int q = 1; q <= h.max_passes; ++q) {
-      k_big_split<<<grid_for(ntiles * kWave, 256), 256, 0, bs>>>(seg_off, big_list, tile_seg, tile_first,
-                                                                &st->big_tiles, q, &st->max_passes, KA, IA, KB,
-                                                                IB, split);
-      k_big_merge<<<grid_for(ntiles, 1), kSortBlock, 0, bs>>>(seg_off, big_list, tile_seg, tile_first,
-                                                             &st->big_tiles, q, &st->max_passes, split, KA, IA,
-                                                             KB, IB, key_out, id_out);
-    }
+    merge_passes(bs);
   }
   SCAN_HIP_TRY(hipGetLastError());
   return SCAN_OK;

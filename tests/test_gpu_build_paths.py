@@ -1,0 +1,53 @@
+"""Builds and sorts at the edges of their dispatch: the one-launch sort and the
+per-class one, passes that find their own splits and passes that read them,
+and the one-workgroup core-order preparation, against numpy and the oracle."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import graphgen
+import oracle
+import paper_2012_11188_amd as scan
+from gpu_util import assert_index_equal, gpu_build
+
+pytestmark = pytest.mark.gpu
+
+
+# one launch for all classes up to 4 << 20 elements; own splits up to 1024 tiles of 4096
+@pytest.mark.parametrize("big", [[], [4097], [9000, 4096 * 40, 4096 * 33 + 1], [4096 * 900], [4096 * 1023 + 5],
+                                 [4096 * 1030, 8193, 50000]])
+@pytest.mark.parametrize("fill", [0, 1 << 20])
+def test_sort_paths(big, fill):
+    rng = np.random.default_rng(len(big) + fill + sum(big))
+    caps = [0, 1, 2, 8, 9, 16, 17, 32, 33, 64, 65, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096]
+    lens = caps * 3 + big
+    while fill > 0:
+        part = rng.integers(0, 5000, 50).tolist()
+        lens += part
+        fill -= sum(part)
+    lens = np.array(lens)[rng.permutation(len(lens))]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    keys = rng.integers(-50, 400, off[-1]) / 7.0  # many ties
+    keys[keys == 0] = 0.5
+    ids = np.concatenate([rng.permutation(n) for n in lens] or [np.zeros(0)]).astype(np.int32)
+    ko, io = scan.scan_segmented_sort(off, keys, ids)
+    seg = np.repeat(np.arange(len(lens)), lens)
+    order = np.lexsort((ids, -keys, seg))
+    assert np.array_equal(ko, keys[order]) and np.array_equal(io, ids[order])
+
+
+def hub_and_ring(n, degree):
+    """A ring of n vertices and one vertex joined to `degree` of them."""
+    ring = [(i, (i + 1) % n) for i in range(n)]
+    return graphgen.from_edges(n, ring + [(5, (7 + 2 * i) % n) for i in range(degree - 2)])
+
+
+# one workgroup prepares the core order up to 32768 vertices and degree 4096
+@pytest.mark.parametrize("n,degree", [(9001, 4095), (9001, 4096), (9001, 4097), (32767, 60), (32768, 4096),
+                                      (32769, 60), (63, 5), (64, 5), (65, 5)])
+def test_core_order_preparation(n, degree):
+    g = hub_and_ring(n, degree)
+    assert int(g.degrees().max()) == degree
+    assert_index_equal(gpu_build(g), oracle.build_index(g, oracle.COSINE, threads=8), g)
