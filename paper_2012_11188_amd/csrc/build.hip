@@ -809,8 +809,10 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
   // it, it ran into the placement of the intersection's persistent workgroups:
   // R-MAT-20 7.08 instead of 6.96 ms a build.)
   IntersectPlan plan;
-  if (NNZ > 0 && !weighted) {
-    SCAN_TRY(intersect_plan(cfg, N, NNZ, off_u, deg, adj_u, device, tmp, s, ctl_plan, (int32_t)(ctl_back / 4),
+  const bool planned = NNZ > 0 && (!weighted || weighted_planned(N, NNZ));
+  const IntersectConfig pcfg = weighted ? weighted_config(cfg) : cfg;
+  if (planned) {
+    SCAN_TRY(intersect_plan(pcfg, N, NNZ, off_u, deg, adj_u, device, tmp, s, ctl_plan, (int32_t)(ctl_back / 4),
                             back.block.p, back.ready, plan));
   } else {
     SCAN_HIP_TRY(hipMemcpyAsync(back.block.p, ctl_plan, ctl_back, hipMemcpyDeviceToHost, s));
@@ -819,7 +821,7 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
   // The small-owner kernels' helper streams wait for the plan now, off the
   // path between the read-back and the first intersection launch.
   JoinOnExit join_h0{s, nullptr}, join_h1{s, nullptr};
-  if (NNZ > 0 && !weighted) {
+  if (planned) {
     for (int k = 0; k < 2; ++k) {
       hipStream_t hs = helper_stream(k);
       if (hs && stream_wait(hs, s) == SCAN_OK) plan.helper[k] = hs;
@@ -1024,11 +1026,11 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     if (lsh)  // the edges between two high-degree vertices are left to the approximate pass
       icfg.skip_deg = kind == SCAN_SIM_JACCARD ? 3 * lsh->samples / 2 : lsh->samples;
     if (weighted) {
-      mark(2);  // no ownership plan
+      mark(2);
       if (cs != s) SCAN_TRY(stream_wait(cs, s));
       SCAN_TRY(co_prep());
       SCAN_TRY(weighted_similarity_all(N, NNZ, off_u, deg, adj_u, w_dev, sims, tmp, s, prof ? &ist : nullptr,
-                                       icfg.skip_deg));
+                                       planned ? &plan : nullptr, device, icfg.skip_deg));
     } else {
       SCAN_TRY(intersect_all(icfg, N, NNZ, off_u, deg, adj_u, kind, sims, counts, device, s, &ist, co_prep, &plan));
     }

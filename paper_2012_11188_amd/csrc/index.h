@@ -41,6 +41,20 @@ struct IntersectStats {
 // recorded then (before the window table). The caller waits for it before
 // intersect_all.
 constexpr size_t kPlanCountBytes = 32;
+constexpr int32_t kLightDeg = kWave;  // one wavefront per vertex up to this degree
+struct PlanCounts {
+  int32_t small;    // vertices of degree 1..kLightDeg
+  int32_t big;      // chunks of the vertices of degree above small_max
+  int32_t counter;  // work counter of the large-owner kernel
+  int32_t heavy;    // vertices of degree kLightDeg+1..small_max
+  int32_t done;     // workgroups of k_plan that have finished
+  int32_t pad[3];
+};
+static_assert(sizeof(PlanCounts) == kPlanCountBytes, "the maximum degrees follow the counts");
+struct BigChunk {
+  int32_t h;
+  int32_t k;  // slots [k*spc, (k+1)*spc) of row h
+};
 struct IntersectPlan {
   int64_t n = 0, nnz = 0;
   int32_t *small_list = nullptr, *heavy_list = nullptr;
@@ -84,9 +98,14 @@ struct LshSpec {
 // events (may be null) before the square sums, before the products, after.
 // The square sums are timed as the "small" part, the owner products as the
 // "big" part (stats may be null).
+// plan: the ownership plan (weighted_config's shapes) where weighted_planned
+// says so, else null.
+IntersectConfig weighted_config(const IntersectConfig &cfg);
+bool weighted_planned(int64_t n, int64_t nnz);
 scan_status weighted_similarity_all(int64_t n, int64_t nnz, const int64_t *off, const int32_t *deg,
                                     const int32_t *adj, const double *w, double *sims, DevArena &tmp,
-                                    hipStream_t s, const IntersectStats *stats, int32_t skip_deg = 0x7fffffff);
+                                    hipStream_t s, const IntersectStats *stats, const IntersectPlan *plan,
+                                    int device, int32_t skip_deg = 0x7fffffff);
 // Overwrites sims of the edges between two high-degree vertices with their
 // SimHash (cosine kinds) or k-partition MinHash (Jaccard) estimates; w may
 // be null (unweighted). spec's pointers are device pointers.

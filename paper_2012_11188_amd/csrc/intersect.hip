@@ -77,22 +77,6 @@ __device__ __forceinline__ int32_t wave_incl_sum(int32_t v) {
   return v;
 }
 
-struct BigChunk {
-  int32_t h;
-  int32_t k;  // slots [k*spc, (k+1)*spc) of row h
-};
-
-struct PlanCounts {
-  int32_t small;       // vertices of degree 1..kLightDeg
-  int32_t big;
-  int32_t counter;     // work counter of k_big_owner
-  int32_t heavy;       // vertices of degree kLightDeg+1..small_max
-  int32_t done;        // workgroups of k_plan that have finished
-  int32_t pad[3];
-};
-static_assert(sizeof(PlanCounts) == kPlanCountBytes, "the maximum degrees follow the counts");
-
-constexpr int32_t kLightDeg = kWave;  // one wavefront per vertex up to this degree
 
 // ---------------------------------------------------------------------------
 // a2: ownership plan.

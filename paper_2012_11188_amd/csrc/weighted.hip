@@ -10,22 +10,36 @@
 // division); with all weights 1 the sums are the integers c, a_u and a_v and
 // the result is the unweighted cosine bit for bit.
 //
-//   k_w_square_sums  one wavefront per vertex: the squares of its row, added
+// The sums are the cost: 1.27e9 products on R-MAT-20, each one dependent add.
+// A row of 16 lanes takes one edge; the lanes' products are broadcast within
+// the row one after the other (row_newbcast) and added by every lane, so one
+// add instruction serves four edges, and lanes without a common id add +0.0,
+// which changes nothing (a running sum is never -0).
+//
+//   k_w_square_sums  a row of lanes per vertex: the squares of its row, added
 //                    in order with the self term 1 at its place.
+// Up to 2^kWbMaxBits vertices, by the ownership plan of the unweighted path
+// (each edge by the endpoint larger in (degree, id), the owner h; every lower
+// neighbour l streams its row in ascending order):
+//   k_w_big          owners above kWbSmallMax: h's row is a bitmap in LDS with
+//                    counts per 128 bits, so that a common id gives its
+//                    position in h's row, and with it w(h, x).
+//   k_w_small        the others: h's row in an LDS hash table with its
+//                    positions and weights.
+// Above:
 //   k_w_unit_rows    the row holding the first slot of every kWUnit-slot unit
 //                    of the CSR.
-//   k_w_owner        one workgroup per unit. Each edge is handled once, by the
-//                    endpoint larger in (degree, id) (the owner h, as in the
-//                    unweighted path). The owner's ids and weights go into LDS
-//                    in tiles of kWTile; every lower neighbour l streams its
-//                    row through them in ascending order, a lane finds its id
-//                    by binary search in its bucket of the tile (kWBuckets
+//   k_w_owner        one workgroup per unit. The owner's ids and weights go
+//                    into LDS in tiles of kWTile; every lower neighbour l
+//                    streams its row through them, a lane finds its id by
+//                    binary search in its bucket of the tile (kWBuckets
 //                    buckets of equal id width, indexed per tile), and the
 //                    wavefront adds the products of the common ids in
-//                    ascending id, inserting the terms of x = h (1 * w(l, h))
-//                    and x = l (w(h, l) * 1).
+//                    ascending id.
+// All insert the terms of x = h (1 * w(l, h)) and x = l (w(h, l) * 1).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 
 #include "index.h"
@@ -59,47 +73,469 @@ __device__ __forceinline__ double lane_f64(double v, int k) {
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// Lanes past the end of a row re-read its last slot (clamped, so the id and
-// weight loads need no branch and are issued together) and contribute +0.0,
-// which leaves a non-negative running sum unchanged.
+// Lane N's value of each row of 16 lanes, in all of the row's lanes.
+template <int N>
+__device__ __forceinline__ double row_lane(double v) {
+  return __longlong_as_double(
+      __builtin_amdgcn_update_dpp((long long)0, __double_as_longlong(v), 0x150 + N, 0xf, 0xf, true));
+}
+// acc + p(lane 0) + p(lane 1) + ... of each row, added in that order. The add
+// is fma(p, 1, acc), the same value: of the FP64 operations only the fused
+// one reads a lane broadcast as an operand. (Two wait states between a
+// register's write and its read by a broadcast.)
+#define SCAN_ROW_ADD(n) "v_fmac_f64_dpp %0, %1, %2 row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
+__device__ __forceinline__ double row_sum(double acc, double p) {
+  asm("s_nop 1\n\t" SCAN_ROW_ADD(0) SCAN_ROW_ADD(1) SCAN_ROW_ADD(2) SCAN_ROW_ADD(3) SCAN_ROW_ADD(4) SCAN_ROW_ADD(5)
+          SCAN_ROW_ADD(6) SCAN_ROW_ADD(7) SCAN_ROW_ADD(8) SCAN_ROW_ADD(9) SCAN_ROW_ADD(10) SCAN_ROW_ADD(11)
+              SCAN_ROW_ADD(12) SCAN_ROW_ADD(13) SCAN_ROW_ADD(14) SCAN_ROW_ADD(15)
+      : "+&v"(acc)
+      : "v"(p), "v"(1.0));
+  return acc;
+}
+#undef SCAN_ROW_ADD
+// The same with x added before lane `at`'s value (at = 16: not at all).
+template <int N = 0>
+__device__ __forceinline__ double row_sum_with(double acc, double p, int at, double x) {
+  if constexpr (N == 16) return acc;
+  else return row_sum_with<N + 1>(acc + (at == N ? x : 0.0) + row_lane<N>(p), p, at, x);
+}
+// This row's 16 bits of a ballot.
+__device__ __forceinline__ uint32_t row_bits(uint64_t m) { return (uint32_t)(m >> (lane_id() & 48)) & 0xffffu; }
+
+// A row of lanes per vertex, four vertices per wavefront in step (a hub's sum
+// is its length in dependent adds; the others of its wavefront wait). The
+// loads of kSqAhead steps are in flight, none of them behind a branch.
+// R-MAT-20: 2.0 -> 0.64 ms.
+constexpr int kSqAhead = 8;
 __global__ __launch_bounds__(256) void k_w_square_sums(const int64_t *off, const int32_t *adj, const double *w,
                                                        int64_t n, double *S) {
-  const int lane = lane_id();
+  const int lane = lane_id(), row = lane / 16, gl = lane % 16;
   const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-  for (int64_t v = uniform64(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave); v < n; v += waves) {
-    const int64_t o = uniform64(off[v]), d = uniform64(off[v + 1]) - o;
+  for (int64_t v0 = uniform64(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave * 4); v0 < n; v0 += waves * 4) {
+    const int64_t v = v0 + row;
+    int64_t o = 0, d = 0;
+    if (v < n) {
+      o = off[v];
+      d = off[v + 1] - o;
+      if (d <= 0) o = 0;
+    }
+    const int64_t top = max(d - 1, (int64_t)0);  // the last position (an empty row reads slot 0: o is 0)
+    int64_t steps = (d + 15) / 16;
+    steps = max(max(steps, (int64_t)__shfl_xor((int)steps, 16, kWave)), (int64_t)__shfl_xor((int)steps, 32, kWave));
+    steps = uniform64(max(steps, (int64_t)__shfl_xor((int)steps, 48, kWave)));
     double acc = 0.0;
     bool self = false;
-    int32_t xr = 0;  // raw loads of the chunk in flight (masked where used)
-    double wr = 0.0;
-    auto fetch = [&](int64_t c) {
-      const int64_t p = c + lane;
-      const int64_t q = o + (p < d ? p : d - 1);
-      xr = adj[q];
-      wr = w[q];
+    int32_t x[kSqAhead];
+    double wx[kSqAhead];
+    auto fetch = [&](int64_t s, int32_t &xs, double &ws) {
+      const int64_t q = o + min(s * 16 + gl, top);
+      xs = adj[q];
+      ws = w[q];
     };
-    if (d > 0) fetch(0);
-    for (int64_t c = 0; c < d; c += kWave) {
-      const bool in = c + lane < d;
-      const double wx = in ? wr : 0.0;
-      const double sq = wx * wx;
-      const uint64_t above = __ballot(in && xr > v);
-      if (c + kWave < d) fetch(c + kWave);  // the next chunk's loads overlap this chunk's sum
-      if (!self && above) {                 // the self term 1 goes before the first id above v
-        const int fa = __ffsll((unsigned long long)above) - 1;
 #pragma unroll
-        for (int k = 0; k < kWave; ++k) {
-          if (k == fa) acc += 1.0;
-          acc += lane_f64(sq, k);
+    for (int k = 0; k < kSqAhead; ++k) fetch(k, x[k], wx[k]);
+    for (int64_t s0 = 0; s0 < steps; s0 += kSqAhead) {
+#pragma unroll
+      for (int k = 0; k < kSqAhead; ++k) {  // (steps past the end add +0.0)
+        const int64_t s = s0 + k;
+        const bool in = s * 16 + gl < d;
+        const double sq = in ? wx[k] * wx[k] : 0.0;
+        const uint32_t above = row_bits(__ballot(in && x[k] > v));
+        fetch(s + kSqAhead, x[k], wx[k]);
+        int at = 16;  // the self term 1 goes before the first id above v
+        if (!self && above) {
+          at = __ffs(above) - 1;
+          self = true;
         }
-        self = true;
-      } else {
-#pragma unroll
-        for (int k = 0; k < kWave; ++k) acc += lane_f64(sq, k);
+        acc = __any(at < 16) ? row_sum_with(acc, sq, at, 1.0) : row_sum(acc, sq);
       }
     }
     if (!self) acc += 1.0;
-    if (lane == 0) S[v] = acc;
+    if (gl == 0 && v < n) S[v] = acc;
+  }
+}
+
+// One edge's sum, the state of a row of lanes.
+struct WEdge {
+  int32_t l, du;   // the lower neighbour and its degree (du 0: no edge)
+  int64_t ou;      // its row
+  double whl, acc; // w(h, l), the running sum
+  bool ldone;      // the x = l term is in acc
+};
+// Adds a step's products (0.0 where there is none); at: the lane before which
+// the x = l term goes, 16 if not in this step.
+__device__ __forceinline__ void add_products(WEdge &e, double prod, int at) {
+  e.acc = __any(at < 16) ? row_sum_with(e.acc, prod, at, e.whl) : row_sum(e.acc, prod);
+}
+// Where the x = l term goes among a step's ids (marks it done).
+__device__ __forceinline__ int place_l(WEdge &e, bool valid, int32_t x) {
+  if (__all(e.ldone)) return 16;
+  const uint32_t above = row_bits(__ballot(valid && x > e.l));
+  if (e.ldone || !above) return 16;
+  e.ldone = true;
+  return __ffs(above) - 1;
+}
+__device__ __forceinline__ int32_t quad_max(int32_t v) {  // v is the same within a row of lanes
+  const int32_t a = max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16));
+  return max(a, max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// ---------------------------------------------------------------------------
+// Small owners. The next step's ids and weights are requested before a step is
+// summed; owners without lower neighbours end after the staging.
+
+constexpr int kWbSmallMax = 256;
+constexpr int kWSmallSpread = 4;  // table slots per row entry (at least)
+constexpr int32_t kWEmpty = -1;
+
+__host__ __device__ inline int smem_table(int cap) {  // table slots for rows of up to cap ids
+  int tb = 6;
+  while ((1 << tb) < kWSmallSpread * cap) ++tb;
+  return 1 << tb;
+}
+static inline size_t w_small_lds(int cap) {
+  return (size_t)cap * (8 + 8 + 4 * 3 + 2) + (size_t)6 * smem_table(cap);
+}
+
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void k_w_small(const int32_t *list, int cap, const int64_t *off,
+                                                           const int32_t *deg, const int32_t *adj, const double *w,
+                                                           const double *S, double *sims, int32_t skip) {
+  extern __shared__ unsigned char smem[];
+  double *tw = (double *)smem;              // [cap] the vertex's weights
+  int64_t *lou = (int64_t *)(tw + cap);     // [cap] row offset of the j-th lower neighbour
+  int32_t *ids = (int32_t *)(lou + cap);    // [cap] the vertex's row
+  int32_t *lid = ids + cap;                 // [cap] the j-th lower neighbour
+  int32_t *ldu = lid + cap;                 // [cap] its degree
+  int32_t *tab = ldu + cap;                 // [2^tbits] hash table of the row: ids
+  uint16_t *le = (uint16_t *)(tab + smem_table(cap));  // [cap] the lower neighbour's slot
+  uint16_t *tpos = le + cap;                // [2^tbits] their positions
+  __shared__ int32_t s_nlow;
+  const int lane = lane_id(), wave = threadIdx.x / kWave, row = lane / 16, gl = lane % 16;
+  const int32_t h = list[blockIdx.x];
+  const int32_t dh = deg[h];
+  const int64_t oh = off[h];
+  int tbits = 6;
+  while ((1 << tbits) < kWSmallSpread * dh) ++tbits;
+  const uint32_t tmask = (1u << tbits) - 1;
+  if (threadIdx.x == 0) s_nlow = 0;
+  __syncthreads();
+  for (int32_t i0 = 0; i0 < dh; i0 += blockDim.x) {
+    const int32_t i = i0 + (int32_t)threadIdx.x;
+    int32_t u = 0, d = 0;
+    if (i < dh) {
+      u = adj[oh + i];
+      d = deg[u];
+      ids[i] = u;
+      tw[i] = w[oh + i];
+    }
+    const bool low = i < dh && (d < dh || (d == dh && u < h)) && d <= skip;
+    const uint64_t m = __ballot(low);
+    int32_t base = 0;
+    if (m && lane == 0) base = atomicAdd(&s_nlow, __popcll(m));
+    base = uniform(base);
+    if (low) {
+      const int32_t j = base + __popcll(m & ((1ull << lane) - 1ull));
+      le[j] = (uint16_t)i;
+      lid[j] = u;
+      ldu[j] = d;
+      lou[j] = off[u];
+    }
+  }
+  __syncthreads();
+  const int32_t nlow = uniform(s_nlow);
+  if (nlow == 0) return;  // owns no edge (uniform across the block)
+  for (uint32_t i = threadIdx.x; i <= tmask; i += blockDim.x) tab[i] = kWEmpty;
+  __syncthreads();
+  for (int32_t i = threadIdx.x; i < dh; i += blockDim.x) {
+    const int32_t x = ids[i];
+    uint32_t sl = ((uint32_t)x * 2654435761u) >> (32 - tbits);
+    while (atomicCAS(&tab[sl], kWEmpty, x) != kWEmpty) sl = (sl + 1) & tmask;
+    tpos[sl] = (uint16_t)i;
+  }
+  __syncthreads();
+  const double sh = S[h];
+  for (int32_t j0 = wave * 4; j0 < nlow; j0 += WAVES * 4) {
+    const int32_t j = min(j0 + row, nlow - 1);
+    const bool has = j0 + row < nlow;
+    WEdge e{lid[j], has ? ldu[j] : 0, lou[j], tw[le[j]], 0.0, false};
+    const int32_t top = ldu[j] - 1, steps = (quad_max(e.du) + 15) / 16;
+    int64_t mpos = -1;
+    int32_t x;
+    double wl;
+    auto fetch = [&](int32_t s) {
+      const int64_t q = e.ou + min(s * 16 + gl, top);
+      x = adj[q];
+      wl = w[q];
+    };
+    fetch(0);
+    for (int32_t s = 0; s < steps; ++s) {
+      const bool valid = s * 16 + gl < e.du;
+      const int32_t xs = x;
+      const double ws = wl;
+      fetch(s + 1);
+      double wh = 0.0;
+      bool hit = false;
+      if (valid) {
+        uint32_t sl = ((uint32_t)xs * 2654435761u) >> (32 - tbits);
+        for (;;) {  // ends at xs or at an empty slot (the table is at most a quarter full)
+          const int32_t t = tab[sl];
+          if (t == xs) {
+            wh = tw[tpos[sl]];
+            hit = true;
+            break;
+          }
+          if (t == kWEmpty) break;
+          sl = (sl + 1) & tmask;
+        }
+      }
+      if (valid && xs == h) {
+        wh = 1.0;
+        hit = true;
+        mpos = e.ou + s * 16 + gl;
+      }
+      const int at = place_l(e, valid, xs);
+      add_products(e, hit ? wh * ws : 0.0, at);
+    }
+    if (!e.ldone) e.acc += e.whl;  // l is above every id of its row
+    // the lane that met h writes the mirror slot too
+    const double v = e.acc / sqrt(sh * S[e.l]);
+    if (has && gl == 0) sims[oh + le[j]] = v;
+    if (mpos >= 0) sims[mpos] = v;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Large owners: persistent workgroups claim chunks of kWbSpc slots of an
+// owner's row (in runs, so that an owner's bitmap serves several chunks). The
+// chunk's lower neighbours are ordered by length class, and every wavefront
+// takes four of them at a time, one per row of lanes, in step; their ids are
+// requested two steps ahead, the weights of a step's common ids one step
+// before they are summed (a common id takes two scattered reads of 8 bytes;
+// reading the weights of all ids takes 55 GB more on R-MAT-20). R-MAT-20, 1.0e8
+// steps: 20.6 ms with the small owners beside it, where k_w_owner took 45; its
+// vector instructions (87 a step, 16 of them the adds) are issued three
+// quarters of the time. Weights requested one step ahead: 21.2 ms, and 24.2
+// when the loop's exits made the compiler wait for every load.
+
+constexpr int kWbMaxBits = 20;
+constexpr int kWbThreads = 1024;
+constexpr int kWbSpc = 256;
+constexpr int32_t kWbRun = 4;
+constexpr int kWbClasses = 64;  // four per octave of the lower neighbour's degree
+
+struct WBigShared {
+  int32_t chunk, run_next, run_left, nlow, next;
+  int32_t cls[kWbClasses];
+  int32_t wsum[kWbThreads / kWave];
+};
+
+static size_t w_big_lds(int wbits) {
+  const size_t bits = (size_t)1 << wbits, blocks = bits / 128;
+  return bits / 8 + blocks * 2 + 32 * 4 + (size_t)kWbSpc * (8 + 8 + 4 * 3 + 2 * 2) + sizeof(WBigShared);
+}
+
+__device__ __forceinline__ double load_f64(__amdgpu_buffer_rsrc_t r, uint32_t byte) {
+  const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)byte, 0, 0);
+  return __longlong_as_double((long long)((uint64_t)v[1] << 32 | v[0]));
+}
+
+__device__ __forceinline__ int length_class(int32_t d) {  // 0: the longest
+  const int o = 31 - __clz(d);
+  const int c = 4 * o + (o >= 2 ? (d >> (o - 2)) & 3 : 0);
+  return kWbClasses - 1 - min(c, kWbClasses - 1);
+}
+
+__global__ __launch_bounds__(kWbThreads) void k_w_big(const BigChunk *chunks, PlanCounts *pc, int wbits,
+                                                      const int64_t *off, const int32_t *deg, const int32_t *adj,
+                                                      const double *w, int64_t nnz, const double *S, double *sims,
+                                                      int32_t skip) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int nwords = (1 << wbits) >> 5, nblk = nwords >> 2;  // blocks of 128 bits
+  uint32_t *bm = (uint32_t *)smem;
+  int64_t *le_ou = (int64_t *)(bm + nwords);
+  double *le_acc = (double *)(le_ou + kWbSpc);
+  int32_t *le_l = (int32_t *)(le_acc + kWbSpc);
+  int32_t *le_du = le_l + kWbSpc;
+  int32_t *le_mpos = le_du + kWbSpc;
+  int32_t *base = le_mpos + kWbSpc;         // [32] bits before every 32 * per blocks
+  uint16_t *pre = (uint16_t *)(base + 32);  // [nblk] bits before a block, from its base
+  uint16_t *le_e = pre + nblk;
+  uint16_t *order = le_e + kWbSpc;
+  WBigShared *sh = (WBigShared *)(order + kWbSpc);
+  const int tid = threadIdx.x, lane = lane_id(), row = lane / 16, gl = lane % 16, wave = tid / kWave;
+  const int per = max(1, nblk / kWbThreads);  // blocks per thread in the counts; a base per 32 threads
+  const int bshift = 31 - __clz(32 * per);
+  const int32_t nchunks = pc->big;
+  // resource word 3: DATA_FORMAT 32 (a valid format enables the buffer)
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc((void *)w, (short)0, (int)(uint32_t)(nnz * 8), 0x00020000);
+  for (int i = tid; i < nwords; i += kWbThreads) bm[i] = 0u;
+  if (tid == 0) sh->run_left = 0;
+  int32_t held = -1, held_dh = 0;  // the owner whose bits the bitmap holds
+  int64_t held_oh = 0;
+  for (;;) {
+    __syncthreads();
+    if (tid == 0) {
+      if (sh->run_left == 0) {
+        sh->run_next = atomicAdd(&pc->counter, kWbRun);
+        sh->run_left = kWbRun;
+      }
+      sh->chunk = sh->run_next++;
+      --sh->run_left;
+      sh->nlow = 0;
+      sh->next = 0;
+    }
+    if (tid < kWbClasses) sh->cls[tid] = 0;
+    __syncthreads();
+    const int32_t ci = uniform(sh->chunk);
+    if (ci >= nchunks) break;
+    const BigChunk ch = chunks[ci];
+    const int32_t h = ch.h;
+    const int32_t dh = deg[h];
+    const int64_t oh = off[h];
+    const int64_t s0 = oh + (int64_t)ch.k * kWbSpc;
+    const int m = (int)min((int64_t)kWbSpc, oh + dh - s0);
+    if (tid < kWbSpc) {  // the chunk's lower neighbours (whole wavefronts)
+      int32_t u = 0, du = 0;
+      if (tid < m) {
+        u = adj[s0 + tid];
+        du = deg[u];
+      }
+      const bool low = tid < m && (du < dh || (du == dh && u < h)) && du <= skip;
+      const uint64_t mk = __ballot(low);
+      int32_t b = 0;
+      if (mk && lane == 0) b = atomicAdd(&sh->nlow, __popcll(mk));
+      b = uniform(b);
+      if (low) {
+        const int k = b + __popcll(mk & ((1ull << lane) - 1ull));
+        le_e[k] = (uint16_t)tid;
+        le_l[k] = u;
+        le_du[k] = du;
+        le_ou[k] = off[u];
+        le_mpos[k] = -1;
+        atomicAdd(&sh->cls[length_class(du)], 1);
+      }
+    }
+    __syncthreads();
+    const int nlow = uniform(sh->nlow);
+    if (nlow == 0) continue;
+    if (h != held) {
+      if (held >= 0) {
+        for (int i = tid; i < held_dh; i += kWbThreads) bm[(uint32_t)adj[held_oh + i] >> 5] = 0u;
+        __syncthreads();  // the new owner's bits may share words with the old one's
+      }
+      for (int i = tid; i < dh; i += kWbThreads) {
+        const int32_t x = adj[oh + i];
+        atomicOr(&bm[x >> 5], 1u << (x & 31));
+      }
+      held = h;
+      held_oh = oh;
+      held_dh = dh;
+      __syncthreads();
+      // counts: this thread's blocks, then an exclusive sum over the workgroup
+      int32_t sum = 0;
+      for (int k = 0; k < per; ++k)
+        if (tid * per + k < nblk) {
+          const uint4 b = ((const uint4 *)bm)[tid * per + k];
+          sum += __popc(b.x) + __popc(b.y) + __popc(b.z) + __popc(b.w);
+        }
+      int32_t incl = sum;
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) {
+        const int32_t t = __shfl_up(incl, d, kWave);
+        if (lane >= d) incl += t;
+      }
+      if (lane == kWave - 1) sh->wsum[wave] = incl;
+      __syncthreads();
+      int32_t e = incl - sum;
+      for (int k = 0; k < wave; ++k) e += sh->wsum[k];
+      const int32_t b0 = __shfl(e, lane & 32, kWave);
+      if (tid % 32 == 0 && tid * per < nblk) base[tid / 32] = b0;
+      for (int k = 0; k < per; ++k)
+        if (tid * per + k < nblk) {
+          pre[tid * per + k] = (uint16_t)(e - b0);
+          const uint4 b = ((const uint4 *)bm)[tid * per + k];
+          e += __popc(b.x) + __popc(b.y) + __popc(b.z) + __popc(b.w);
+        }
+    }
+    if (wave == 0) {  // class starts
+      int32_t c = sh->cls[lane], incl = c;
+      static_assert(kWbClasses == kWave, "a lane per class");
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) {
+        const int32_t t = __shfl_up(incl, d, kWave);
+        if (lane >= d) incl += t;
+      }
+      sh->cls[lane] = incl - c;
+    }
+    __syncthreads();
+    if (tid < nlow) order[atomicAdd(&sh->cls[length_class(le_du[tid])], 1)] = (uint16_t)tid;
+    __syncthreads();
+    for (;;) {
+      int32_t q = 0;
+      if (lane == 0) q = atomicAdd(&sh->next, 1);
+      q = uniform(q) * 4;
+      if (q >= nlow) break;
+      const bool has = q + row < nlow;
+      const int k = order[min(q + row, nlow - 1)];
+      const int32_t ldu = le_du[k], top = ldu - 1;
+      WEdge e{le_l[k], has ? ldu : 0, le_ou[k], w[s0 + le_e[k]], 0.0, false};
+      const int32_t steps = (quad_max(e.du) + 15) / 16;
+      const uint32_t eo = (uint32_t)e.ou, ho = (uint32_t)oh;  // slots fit 32 bits, their weights' bytes too
+      auto fetch = [&](int32_t s) -> int32_t { return adj[e.ou + min(s * 16 + gl, top)]; };
+      // One step: probe its ids and request the weights of the common ones.
+      // Every load is issued by every lane, so that the compiler can wait for
+      // a step's loads by counting those issued after them (behind a branch it
+      // waits for all: 29.7 instead of 24.6 ms on R-MAT-20): buffer loads, whose
+      // offset is past the end where there is nothing to read, which gives 0
+      // and touches no memory.
+      auto probe = [&](int32_t x, int32_t s, double &wl, double &wh, bool &self, int &at) {
+        const int32_t p = s * 16 + gl;
+        const bool valid = p < e.du;
+        const uint4 b = ((const uint4 *)bm)[(uint32_t)x >> 7];
+        const uint64_t lo = (uint64_t)b.y << 32 | b.x, hi = (uint64_t)b.w << 32 | b.z;
+        const bool upper = (x & 64) != 0;
+        const uint64_t half = upper ? hi : lo;
+        const bool hit = valid && ((half >> (x & 63)) & 1);
+        self = valid && x == h;
+        // position of x in h's row, where x is in it
+        const uint32_t blk = (uint32_t)x >> 7;
+        const int32_t rank = base[blk >> bshift] + pre[blk] + (upper ? __popcll(lo) : 0) +
+                             __popcll(half & ~(~0ull << (x & 63)));
+        wl = load_f64(wr, hit || self ? (eo + (uint32_t)p) * 8u : ~7u);
+        wh = load_f64(wr, hit ? (ho + (uint32_t)rank) * 8u : ~7u);
+        if (self) le_mpos[k] = p;
+        at = place_l(e, valid, x);
+      };
+      int32_t x0 = fetch(0), x1 = fetch(1), x2 = fetch(2);
+      double wl0, wh0, wl1, wh1, wl2, wh2;
+      bool self0, self1, self2;  // x = h: w(h, h) = 1
+      int at0, at1, at2;
+      probe(x0, 0, wl0, wh0, self0, at0);
+      x0 = fetch(3);
+      probe(x1, 1, wl1, wh1, self1, at1);
+      x1 = fetch(4);
+      // The three register sets change roles without copies; steps past the
+      // rows' ends (no valid id) add nothing.
+      for (int32_t s = 2; s - 2 < steps; s += 3) {
+        probe(x2, s, wl2, wh2, self2, at2);
+        x2 = fetch(s + 3);
+        add_products(e, wl0 * (self0 ? 1.0 : wh0), at0);
+        probe(x0, s + 1, wl0, wh0, self0, at0);
+        x0 = fetch(s + 4);
+        add_products(e, wl1 * (self1 ? 1.0 : wh1), at1);
+        probe(x1, s + 2, wl1, wh1, self1, at1);
+        x1 = fetch(s + 5);
+        add_products(e, wl2 * (self2 ? 1.0 : wh2), at2);
+      }
+      if (has && gl == 0) le_acc[k] = e.ldone ? e.acc : e.acc + e.whl;  // (l above every id of its row)
+    }
+    __syncthreads();
+    if (tid < nlow) {
+      const double v = le_acc[tid] / sqrt(S[h] * S[le_l[tid]]);
+      sims[s0 + le_e[tid]] = v;
+      if (le_mpos[tid] >= 0) sims[le_ou[tid] + le_mpos[tid]] = v;
+    }
   }
 }
 
@@ -332,9 +768,59 @@ scan_status check_weights(const double *w, int64_t nnz, DevArena &tmp, hipStream
   return SCAN_OK;
 }
 
+// The bitmap path holds one id window and addresses the weights by 32-bit
+// byte offsets; larger graphs take k_w_owner.
+bool weighted_planned(int64_t n, int64_t nnz) {
+  return n <= ((int64_t)1 << kWbMaxBits) && nnz * 8 < (int64_t)0xfffffff8u;
+}
+IntersectConfig weighted_config(const IntersectConfig &cfg) {
+  IntersectConfig c = cfg;
+  c.small_max = kWbSmallMax;
+  c.spc = kWbSpc;
+  c.wbits = kWbMaxBits;
+  return c;
+}
+
+static scan_status weighted_by_plan(const IntersectPlan &plan, int64_t n, int64_t nnz, const int64_t *off, const int32_t *deg,
+                                    const int32_t *adj, const double *w, const double *S, double *sims, int device,
+                                    hipStream_t s, int32_t skip) {
+  const PlanCounts c = *(const PlanCounts *)plan.host;
+  int wbits = 10;
+  while (((int64_t)1 << wbits) < n) ++wbits;
+  const size_t lds = w_big_lds(wbits);
+  int lds_max = 65536, cus = 256;
+  (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
+  if (lds > (size_t)lds_max) return fail(SCAN_EDEVICE, "the weighted bitmap needs %zu bytes of LDS", lds);
+  // As in the unweighted path: the persistent large-owner kernel first, the
+  // small owners' on helper streams (ordered after the square sums).
+  auto fork = [&](int k) -> hipStream_t {
+    if (!c.big || !plan.helper[k] || stream_wait(plan.helper[k], s) != SCAN_OK) return s;
+    return plan.helper[k];
+  };
+  const hipStream_t sh = fork(0), sl = fork(1);
+  JoinOnExit join_sh{s, sh}, join_sl{s, sl};
+  if (c.big) {
+    SCAN_HIP_TRY(hipFuncSetAttribute((const void *)k_w_big, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const int per_cu = (int)std::min<size_t>(2, (size_t)lds_max / lds);
+    k_w_big<<<(unsigned)std::min<int64_t>((int64_t)cus * per_cu, c.big), kWbThreads, lds, s>>>(
+        (const BigChunk *)plan.big_list, (PlanCounts *)plan.counts, wbits, off, deg, adj, w, nnz, S, sims, skip);
+  }
+  constexpr int kHeavyWaves = 4;
+  if (c.heavy)
+    k_w_small<kHeavyWaves><<<c.heavy, kHeavyWaves * kWave, w_small_lds(kWbSmallMax), sh>>>(
+        plan.heavy_list, kWbSmallMax, off, deg, adj, w, S, sims, skip);
+  if (c.small)
+    k_w_small<1><<<c.small, kWave, w_small_lds(kLightDeg), sl>>>(plan.small_list, kLightDeg, off, deg, adj, w, S,
+                                                                 sims, skip);
+  SCAN_HIP_TRY(hipGetLastError());
+  return SCAN_OK;
+}
+
 scan_status weighted_similarity_all(int64_t n, int64_t nnz, const int64_t *off, const int32_t *deg,
                                     const int32_t *adj, const double *w, double *sims, DevArena &tmp,
-                                    hipStream_t s, const IntersectStats *stats, int32_t skip_deg) {
+                                    hipStream_t s, const IntersectStats *stats, const IntersectPlan *plan,
+                                    int device, int32_t skip_deg) {
   auto mark = [&](hipEvent_t e) -> scan_status {
     if (e) SCAN_HIP_TRY(hipEventRecord(e, s));
     return SCAN_OK;
@@ -346,13 +832,17 @@ scan_status weighted_similarity_all(int64_t n, int64_t nnz, const int64_t *off, 
     double *S;
     int32_t *row_of;
     SCAN_TRY(tmp.alloc(&S, n));
-    SCAN_TRY(tmp.alloc(&row_of, units));
-    k_w_square_sums<<<grid_for(n * kWave, 256), 256, 0, s>>>(off, adj, w, n, S);
-    k_w_unit_rows<<<grid_for(n, 256), 256, 0, s>>>(off, n, row_of);
+    k_w_square_sums<<<grid_for(n * 16, 256), 256, 0, s>>>(off, adj, w, n, S);
     SCAN_HIP_TRY(hipGetLastError());
     SCAN_TRY(mark(stats ? stats->ev_small_end : nullptr));
     SCAN_TRY(mark(stats ? stats->ev_big_begin : nullptr));
-    k_w_owner<<<(unsigned)units, kWThreads, 0, s>>>(off, deg, adj, w, S, row_of, n, nnz, sims, skip_deg);
+    if (plan) {
+      SCAN_TRY(weighted_by_plan(*plan, n, nnz, off, deg, adj, w, S, sims, device, s, skip_deg));
+    } else {
+      SCAN_TRY(tmp.alloc(&row_of, units));
+      k_w_unit_rows<<<grid_for(n, 256), 256, 0, s>>>(off, n, row_of);
+      k_w_owner<<<(unsigned)units, kWThreads, 0, s>>>(off, deg, adj, w, S, row_of, n, nnz, sims, skip_deg);
+    }
     SCAN_HIP_TRY(hipGetLastError());
   } else {
     SCAN_TRY(mark(stats ? stats->ev_small_end : nullptr));

@@ -211,3 +211,42 @@ def test_weighted_validated_build():
     w = graphgen.edge_weights(g, 41)
     say("weighted validated build")
     assert_weighted_equal(weighted_gpu(g, w, flags=FLAGS | scan.SCAN_VALIDATE), oracle.build_index_weighted(g, w))
+
+
+def spread(g, n):
+    """The same graph with its ids spread evenly over n."""
+    u = np.repeat(np.arange(g.n, dtype=np.int64), g.degrees())
+    step = n // g.n
+    return graphgen.from_edges(n, np.stack([u * step + step - 1, g.adj * step + step - 1], 1).astype(np.int32))
+
+
+def owners(degree, n):
+    """Hubs of the given degree (and one more and one less) over one set of
+    ring vertices, and a clique among them."""
+    ring = n - 3
+    e = [(i, (i + 1) % ring) for i in range(ring)]
+    for j, d in enumerate((degree - 1, degree, degree + 1)):
+        e += [(ring + j, (3 + j * 7 + i) % ring) for i in range(d - 2)]
+        e += [(ring + j, ring + k) for k in range(j)]
+    return graphgen.from_edges(n, e)
+
+
+# owner degrees around the kernels' limits (64, 256 and chunks of 256 slots), ids
+# around the widths of the bitmap (2^20 at most; above it the tiled kernel), a
+# hub past 65535 ids before the last one
+@pytest.mark.parametrize("degree,n", [(64, 700), (256, 1024), (256, 1025), (257, 2000), (512, 4000), (513, 1 << 16),
+                                      (70000, 80000), (1000, 1 << 20), (1000, (1 << 20) + 1), (300, 1 << 21)])
+def test_weighted_owner_classes(degree, n):
+    g = owners(degree, min(n, 80000))
+    g = spread(g, n) if n > g.n else g
+    rng = np.random.default_rng(degree)
+    w = graphgen.edge_weights(g, 5)
+    w[rng.integers(0, g.nnz, g.nnz // 20)] = 0.0
+    w[rng.integers(0, g.nnz, g.nnz // 20)] *= -1.0  # the two directions of an edge may differ
+    gix = weighted_gpu(g, w)
+    oix = oracle.build_index_weighted(g, w, threads=8)
+    for name, code, want in (("sim", scan.ARR_SIMS, oix.sim), ("no_sim", scan.ARR_NO_SIM, oix.no_sim),
+                             ("co_thr", scan.ARR_CO_THR, oix.co_thr)):
+        assert np.array_equal(bits(scan.scan_index_export(gix, code)), bits(want)), name
+    assert np.array_equal(scan.scan_index_export(gix, scan.ARR_NO_IDS), oix.no_ids)
+    assert np.array_equal(scan.scan_index_export(gix, scan.ARR_CO_IDS), oix.co_ids)
