@@ -273,6 +273,7 @@ static scan_status tune_to_config(const scan_tune *t, IntersectConfig *c) {
   if (!t) return SCAN_OK;
   if (t->flags & ~SCAN_TUNE_SEARCH_WINDOWS) return fail(SCAN_EINVAL, "unknown scan_tune.flags %d", t->flags);
   c->search_windows = (t->flags & SCAN_TUNE_SEARCH_WINDOWS) != 0;
+  c->auto_shapes = !t->small_max && !t->spc;
   if (t->small_max) c->small_max = t->small_max;
   if (t->spc) c->spc = t->spc;
   if (t->wbits) c->wbits = t->wbits;
@@ -363,6 +364,7 @@ scan_status scan_autotune(const scan_csr *gs, int32_t count, scan_sim_kind kind,
     return SCAN_OK;
   };
   IntersectConfig cur = default_config();
+  cur.auto_shapes = false;
   float cur_ms;
   SCAN_TRY(time_cfg(cur, &cur_ms));
   auto sweep = [&](int32_t IntersectConfig::*field, std::initializer_list<int32_t> values) -> scan_status {

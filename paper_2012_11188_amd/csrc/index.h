@@ -16,6 +16,9 @@ struct IntersectConfig {
   int32_t small_max = 256;  // owners of degree <= small_max: one wavefront each
   int32_t spc = 512;        // row slots per chunk of a larger owner
   int32_t wbits = 20;       // LDS bitmap window of 2^wbits ids (clamped to LDS)
+  // small_max and spc were left to the build, which then goes by the number of
+  // vertices (build.hip).
+  bool auto_shapes = true;
   bool search_windows = false;  // several windows: search row ranges instead of tabling them
   int32_t skip_deg = 0x7fffffff;  // edges whose endpoints both exceed this degree are left unwritten
                                   // (approximate builds overwrite them)
@@ -38,7 +41,7 @@ struct IntersectStats {
 // must outlive intersect_all; `counts` is kPlanCountBytes of zeroed device
 // memory, and what follows it belongs to the caller: the plan's last step
 // copies `words` int32 from `counts` to pinned `host` memory, and `ready` is
-// recorded then (before the window table). The caller waits for it before
+// recorded then. The caller waits for it before
 // intersect_all.
 constexpr size_t kPlanCountBytes = 32;
 constexpr int32_t kLightDeg = kWave;  // one wavefront per vertex up to this degree
@@ -48,7 +51,8 @@ struct PlanCounts {
   int32_t counter;  // work counter of the large-owner kernel
   int32_t heavy;    // vertices of degree kLightDeg+1..small_max
   int32_t done;     // workgroups of k_plan that have finished
-  int32_t pad[3];
+  int32_t rows;     // vertices with neighbours
+  int32_t pad[2];
 };
 static_assert(sizeof(PlanCounts) == kPlanCountBytes, "the maximum degrees follow the counts");
 struct BigChunk {
@@ -63,8 +67,6 @@ struct IntersectPlan {
   // helper streams already ordered after the plan (set by the caller), used
   // for the two small-owner kernels; null: intersect_all orders its own
   hipStream_t helper[2] = {nullptr, nullptr};
-  int32_t wbits = 0;       // the large-owner kernel's id window width
-  int32_t *wt = nullptr;   // window table (ids over several windows), or null
   IntersectPlan() = default;
   IntersectPlan(const IntersectPlan &) = delete;
   IntersectPlan &operator=(const IntersectPlan &) = delete;

@@ -113,21 +113,24 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, int64
                                                        int32_t *host) {
   __shared__ int32_t last;
   __shared__ int32_t wsum[kPlanThreads / kWave];
-  __shared__ int32_t tot_small, tot_heavy, tot_big, base_small, base_heavy, base_big;
+  __shared__ int32_t tot_small, tot_heavy, tot_big, base_small, base_heavy, base_big, rows;
   constexpr int64_t kTile = (int64_t)kPlanThreads * kPlanPer;
   for (int64_t t0 = (int64_t)blockIdx.x * kTile; t0 < n; t0 += (int64_t)gridDim.x * kTile) {
     const int64_t v0 = t0 + (int64_t)threadIdx.x * kPlanPer;
     int32_t code[kPlanPer];  // 0 nothing, -1 light, -2 heavy small, else number of chunks
-    int32_t ns = 0, nh = 0, nb = 0;
+    int32_t ns = 0, nh = 0, nb = 0, nr = 0;
+    if (threadIdx.x == 0) rows = 0;
 #pragma unroll
     for (int k = 0; k < kPlanPer; ++k) {
       const int32_t dh = v0 + k < n ? deg[v0 + k] : 0;
+      nr += __popcll(__ballot(dh != 0));
       code[k] = dh == 0 ? 0 : dh <= min(small_max, kLightDeg) ? -1 : dh <= small_max ? -2 : (dh + spc - 1) / spc;
       ns += code[k] == -1;
       nh += code[k] == -2;
       nb += code[k] > 0 ? code[k] : 0;
     }
     __syncthreads();  // wsum and the totals are reused across tiles
+    if (lane_id() == 0) atomicAdd(&rows, nr);
     const int32_t os = block_excl_scan(ns, wsum, &tot_small);
     const int32_t oh = block_excl_scan(nh, wsum, &tot_heavy);
     const int32_t ob = block_excl_scan(nb, wsum, &tot_big);
@@ -135,6 +138,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, int64
       base_small = tot_small ? atomicAdd(&pc->small, tot_small) : 0;
       base_heavy = tot_heavy ? atomicAdd(&pc->heavy, tot_heavy) : 0;
       base_big = tot_big ? atomicAdd(&pc->big, tot_big) : 0;
+      atomicAdd(&pc->rows, rows);
     }
     __syncthreads();
     int32_t ps = base_small + os, ph = base_heavy + oh, pb = base_big + ob;
@@ -378,12 +382,14 @@ __device__ __forceinline__ int64_t wave_lower_bound(const int32_t *row, int64_t 
 // segments of kSeg ids, and wavefronts claim segments from an LDS counter
 // (item j < nlow is the first segment of edge j; later items are the extra
 // segments of long rows), so one long row cannot hold the workgroup at the
-// barrier that ends the window. Partial counts meet in LDS.
+// barrier that ends the window. Partial counts meet in LDS. Rows are streamed
+// and set from radj: adj itself, or the same rows with ids numbered without
+// the isolated vertices (cid), in the same order.
 template <bool kOneWindow>
 __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     const BigChunk *chunks, PlanCounts *pc, int spc, int wbits, int64_t n,
-    const int64_t *off, const int32_t *deg, const int32_t *adj, const int32_t *wt, int32_t nwin, int kind,
-    double *sims, int32_t *counts, int32_t skip) {
+    const int64_t *off, const int32_t *deg, const int32_t *adj, const int32_t *radj, const int64_t *cid,
+    const int32_t *wt, int32_t nwin, int kind, double *sims, int32_t *counts, int32_t skip) {
   extern __shared__ unsigned char smem[];
   const int64_t W = (int64_t)1 << wbits;
   const int nwords = (int)(W >> 5);
@@ -435,6 +441,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     const int32_t h = ch.h;
     const int32_t dh = deg[h];
     const int64_t oh = off[h];
+    const int32_t hx = kOneWindow && cid ? (int32_t)cid[h] : h;  // h among the streamed ids
     const int64_t s0 = oh + (int64_t)ch.k * spc;
     const int m = (int)min((int64_t)spc, oh + dh - s0);
     // Stage the chunk's lower neighbours (wave-aggregated compaction).
@@ -472,11 +479,11 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     if (nlow == 0) continue;
     if (one_window && h != held) {
       if (held >= 0) {
-        for (int i = tid; i < held_dh; i += blockDim.x) bm[(uint32_t)adj[held_oh + i] >> 5] = 0u;
+        for (int i = tid; i < held_dh; i += blockDim.x) bm[(uint32_t)radj[held_oh + i] >> 5] = 0u;
         __syncthreads();  // the new owner's bits may share words with the old one's
       }
       for (int i = tid; i < dh; i += blockDim.x) {
-        const int32_t x = adj[oh + i];
+        const int32_t x = radj[oh + i];
         atomicOr(&bm[x >> 5], 1u << (x & 31));
       }
       held = h;
@@ -491,12 +498,12 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     int32_t pf0 = 0, pf1 = 0;
     int64_t pf_w = -1;
     while (p < dh) {
-      const int64_t w0 = one_window ? 0 : ((int64_t)adj[oh + p] >> wbits) << wbits;
+      const int64_t w0 = one_window ? 0 : ((int64_t)radj[oh + p] >> wbits) << wbits;
       const int64_t pe = one_window ? dh
                          : wt ? (int64_t)wt[(int64_t)h * (nwin + 1) + (w0 >> wbits) + 1]
-                              : wave_lower_bound(adj + oh, p, dh, (int32_t)min(w0 + W, (int64_t)INT32_MAX));
+                              : wave_lower_bound(radj + oh, p, dh, (int32_t)min(w0 + W, (int64_t)INT32_MAX));
       for (int64_t i = p + tid; !one_window && i < pe; i += blockDim.x) {
-        const int32_t x = (int32_t)(adj[oh + i] - w0);
+        const int32_t x = (int32_t)(radj[oh + i] - w0);
         atomicOr(&bm[x >> 5], 1u << (x & 31));
       }
       if (!one_window && wt) {
@@ -523,7 +530,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
           const int32_t i = __builtin_amdgcn_readlane(old, 0);
           if (i >= nlow) break;
           const int32_t du = uniform(le_du[i]);
-          const int32_t *row = adj + uniform64(le_ou[i]);
+          const int32_t *row = radj + uniform64(le_ou[i]);
           const int64_t b0 = wave_lower_bound(row, uniform(le_b1[i]), du, (int32_t)w0);
           const int64_t b1 = wave_lower_bound(row, b0, du, (int32_t)min(w0 + W, (int64_t)INT32_MAX));
           le_b0[i] = (int32_t)b0;
@@ -543,7 +550,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
       __syncthreads();
       const int32_t nitems = nlow + uniform(sh->nextra);
       if (!one_window && wt && pe < dh && tid < nlow) {  // the next window's ranges, read during the items
-        const int64_t kwn = (int64_t)adj[oh + pe] >> wbits;
+        const int64_t kwn = (int64_t)radj[oh + pe] >> wbits;
         const int32_t *t = wt + (int64_t)le_u[tid] * (nwin + 1) + kwn;
         pf0 = t[0];
         pf1 = t[1];
@@ -598,7 +605,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
 #pragma unroll
           for (int k = 0; k < kUnroll; ++k) {
             const uint32_t y = kOneWindow ? (uint32_t)x[k] : (uint32_t)(x[k] - (int32_t)w0);
-            acc += __builtin_amdgcn_ubfe(bitmap_word(y), y, 1) + (x[k] < h ? 0x10000u : 0u);  // bit y & 31
+            acc += __builtin_amdgcn_ubfe(bitmap_word(y), y, 1) + (x[k] < hx ? 0x10000u : 0u);  // bit y & 31
           }
         } else {
 #pragma unroll
@@ -608,7 +615,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
             const uint32_t vm = 0u - (uint32_t)valid;
             // inside the item every id lies in the current window
             const uint32_t y = kOneWindow ? (uint32_t)x[k] : (uint32_t)(x[k] - (int32_t)w0);
-            acc += (__builtin_amdgcn_ubfe(bitmap_word(y & vm), y, 1) + (x[k] < h ? 0x10000u : 0u)) & vm;
+            acc += (__builtin_amdgcn_ubfe(bitmap_word(y & vm), y, 1) + (x[k] < hx ? 0x10000u : 0u)) & vm;
           }
         }
       };
@@ -625,7 +632,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
       auto fetch_item = [&](int32_t x[kItemLoads], int64_t ou, int32_t lo, int32_t len) {
         // resource word 3: DATA_FORMAT 32 (a valid format enables the buffer)
         const __amdgpu_buffer_rsrc_t r =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(adj + ou + lo), (short)0, len * 4, 0x00020000);
+            __builtin_amdgcn_make_buffer_rsrc((void *)(radj + ou + lo), (short)0, len * 4, 0x00020000);
 #pragma unroll
         for (int j = 0; j < kItemLoads; ++j) x[j] = __builtin_amdgcn_raw_buffer_load_b32(r, lane * 4 + j * kWave * 4, 0, 0);
       };
@@ -664,7 +671,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
       }
       __syncthreads();
       for (int64_t i = p + tid; !one_window && i < pe; i += blockDim.x) {
-        const int32_t x = (int32_t)(adj[oh + i] - w0);
+        const int32_t x = (int32_t)(radj[oh + i] - w0);
         bm[x >> 5] = 0u;
       }
       p = pe;
@@ -707,8 +714,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
 constexpr int32_t kTableScan = 2048;
 
 __global__ __launch_bounds__(256) void k_window_table(const int64_t *off, const int32_t *adj, int64_t n,
-                                                      int wbits, int32_t nwin, const PlanCounts *pc, int32_t *wt) {
-  if (pc->big == 0) return;  // no bitmap owners: the table is not read
+                                                      int wbits, int32_t nwin, int32_t *wt) {
   const int lane = lane_id();
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
   int64_t u = uniform64((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave);
@@ -761,6 +767,25 @@ __global__ __launch_bounds__(256) void k_window_table(const int64_t *off, const 
   }
 }
 
+// Ids without the isolated vertices, in the same order.
+__global__ void k_id_flags(const int32_t *deg, int64_t n, int32_t *flags) {
+  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
+    flags[v] = deg[v] > 0;
+}
+__global__ __launch_bounds__(256) void k_rename(const int32_t *adj, int64_t nnz, const int64_t *cid, int32_t *out) {
+  constexpr int kPer = 4;  // ids per thread in flight
+  for (int64_t s0 = blockIdx.x * (int64_t)(kPer * 256) + threadIdx.x; s0 < nnz; s0 += (int64_t)gridDim.x * kPer * 256) {
+    int32_t x[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) x[k] = s0 + k * 256 < nnz ? adj[s0 + k * 256] : 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) x[k] = (int32_t)cid[x[k]];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+      if (s0 + k * 256 < nnz) out[s0 + k * 256] = x[k];
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Host side.
 
@@ -788,10 +813,6 @@ scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, c
   p.n = n;
   p.nnz = nnz;
   if (nnz == 0) return SCAN_OK;
-  int lds_max = 65536;
-  (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
-  p.wbits = window_bits(cfg, n, lds_max);
-  const int32_t nwin = (int32_t)((n + ((int64_t)1 << p.wbits) - 1) >> p.wbits);
   BigChunk *big_list;
   PlanCounts *pc = (PlanCounts *)counts;
   SCAN_TRY(arena.alloc(&p.small_list, n));
@@ -803,14 +824,6 @@ scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, c
   k_plan<<<grid_for(n, kPlanThreads * kPlanPer, 2048), kPlanThreads, 0, s>>>(
       deg, n, cfg.small_max, cfg.spc, p.small_list, p.heavy_list, big_list, pc, words, (int32_t *)host);
   SCAN_HIP_TRY(hipEventRecord(ready, s));
-  // Ids spanning several windows: the window table follows the plan (it
-  // needs only the CSR, and nothing when there are no bitmap owners), so
-  // that the large-owner kernel can start as soon as the host has read the
-  // plan's counts.
-  if (nwin > 1 && !cfg.search_windows && (size_t)(nwin + 1) * (size_t)n * 4 <= kMaxWindowTable) {
-    SCAN_TRY(arena.alloc(&p.wt, (int64_t)(nwin + 1) * n));
-    k_window_table<<<grid_for(n * kWave, 256), 256, 0, s>>>(off, adj, n, p.wbits, nwin, pc, p.wt);
-  }
   return SCAN_OK;
 }
 
@@ -824,10 +837,7 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   int lds_max = 65536, cus = 256;
   (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
-  const int wbits = window_bits(cfg, n, lds_max);
-  if (big_lds_bytes(wbits, cfg.spc) > (size_t)lds_max) return fail(SCAN_EINVAL, "chunk size too large for LDS");
-
-  if (!plan || plan->n != n || plan->nnz != nnz || !plan->host || plan->wbits != wbits)
+  if (!plan || plan->n != n || plan->nnz != nnz || !plan->host)
     return fail(SCAN_EINVAL, "plan made for another graph");
   const int32_t *small_list = plan->small_list, *heavy_list = plan->heavy_list;
   const BigChunk *big_list = (const BigChunk *)plan->big_list;
@@ -836,6 +846,41 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   // lets the hardware balance the uneven rows, which persistent grids with a
   // static split do not.
   const PlanCounts h = *(const PlanCounts *)plan->host;
+  DevArena tmp(s);
+  int wbits = window_bits(cfg, n, lds_max);
+  auto windows = [](int64_t ids, int bits) { return (int32_t)((ids + ((int64_t)1 << bits) - 1) >> bits); };
+  int32_t nwin = windows(n, wbits);
+  int32_t *wt = nullptr, *renamed = nullptr;
+  int64_t *cid = nullptr;
+  if (h.big && nwin > 1) {
+    // Ids spanning several windows. A chunk's cost is mostly its work items,
+    // and each lower neighbour makes at least one per window, so ids are
+    // numbered without the isolated vertices where that saves a window (half
+    // of an R-MAT graph's: R-MAT-23 has 8 windows with them and 5 without, and
+    // its large owners take 448 ms with them, 400 without; renaming takes 5).
+    // Where there is no memory for the second adjacency, they stay.
+    const int rbits = window_bits(cfg, h.rows, lds_max);
+    int32_t *flags;
+    int64_t *ws;
+    if (windows(h.rows, rbits) < nwin && tmp.alloc(&renamed, nnz) == SCAN_OK && tmp.alloc(&flags, n) == SCAN_OK &&
+        tmp.alloc(&cid, n + 1) == SCAN_OK && tmp.alloc(&ws, scan_workspace_elems(n)) == SCAN_OK) {
+      k_id_flags<<<grid_for(n, 256), 256, 0, s>>>(deg, n, flags);
+      SCAN_TRY(exclusive_scan(flags, cid, n, ws, s));
+      k_rename<<<grid_for(nnz, 1024), 256, 0, s>>>(adj, nnz, cid, renamed);
+      wbits = rbits;
+      nwin = windows(h.rows, rbits);
+    } else {
+      renamed = nullptr;
+      cid = nullptr;
+    }
+    // The window table, unless it would exceed kMaxWindowTable bytes or the
+    // searched ranges are asked for; then chunks search them per window.
+    if (nwin > 1 && !cfg.search_windows && (size_t)(nwin + 1) * (size_t)n * 4 <= kMaxWindowTable) {
+      SCAN_TRY(tmp.alloc(&wt, (int64_t)(nwin + 1) * n));
+      k_window_table<<<grid_for(n * kWave, 256), 256, 0, s>>>(off, renamed ? renamed : adj, n, wbits, nwin, wt);
+    }
+  }
+  if (big_lds_bytes(wbits, cfg.spc) > (size_t)lds_max) return fail(SCAN_EINVAL, "chunk size too large for LDS");
   if (stats) {
     stats->wbits = wbits;
     stats->launches = (h.small > 0) + (h.heavy > 0) + (h.big > 0);
@@ -868,12 +913,8 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   JoinOnExit join_sh{s, sh}, join_sl{s, sl};  // before the plan lists are released
   if (h.big) {
     size_t lds = big_lds_bytes(wbits, cfg.spc);
-    const bool one = n <= ((int64_t)1 << wbits);
-    // Several windows: each row's window starts come from the plan's table
-    // unless it would exceed kMaxWindowTable bytes or the searched ranges are
-    // asked for; then chunks search them per window.
-    int32_t *wt = plan->wt;
-    const int32_t nwin = (int32_t)((n + ((int64_t)1 << wbits) - 1) >> wbits);
+    const bool one = nwin == 1;
+    const int32_t *radj = renamed ? renamed : adj;
     const void *fn = one ? (const void *)k_big_owner<true> : (const void *)k_big_owner<false>;
     hipFuncAttributes fa;
     SCAN_HIP_TRY(hipFuncGetAttributes(&fa, fn));
@@ -885,10 +926,10 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
     const int grid = (int)std::min<int64_t>((int64_t)cus * per_cu, h.big);
     SCAN_TRY(mark(stats ? stats->ev_big_begin : nullptr, s));
     if (one)
-      k_big_owner<true><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, off, deg, adj, nullptr,
+      k_big_owner<true><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, off, deg, adj, radj, cid, nullptr,
                                                        nwin, kind, sims, counts, cfg.skip_deg);
     else
-      k_big_owner<false><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, off, deg, adj, wt,
+      k_big_owner<false><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, off, deg, adj, radj, cid, wt,
                                                         nwin, kind, sims, counts, cfg.skip_deg);
     SCAN_HIP_TRY(hipGetLastError());
     SCAN_TRY(mark(stats ? stats->ev_big_end : nullptr, s));

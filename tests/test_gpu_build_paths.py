@@ -51,3 +51,21 @@ def test_core_order_preparation(n, degree):
     g = hub_and_ring(n, degree)
     assert int(g.degrees().max()) == degree
     assert_index_equal(gpu_build(g), oracle.build_index(g, oracle.COSINE, threads=8), g)
+
+
+# ids numbered without isolated vertices: several windows left, one left, and
+# one or no id between used ones
+@pytest.mark.parametrize("tune", [{"wbits": 10, "small_max": 8, "spc": 64}, {"wbits": 11, "small_max": 4},
+                                  {"wbits": 10, "small_max": 8, "flags": scan.SCAN_TUNE_SEARCH_WINDOWS}])
+@pytest.mark.parametrize("used,n", [(700, 5000), (1024, 2049), (1025, 4000), (3000, 3001), (3000, 9000)])
+def test_isolated_vertices_left_out(used, n, tune):
+    from gpu_util import device_csr
+
+    base = graphgen.sbm(used, 5, 0.06, 0.02, 31)
+    rng = np.random.default_rng(used + n)
+    place = np.sort(rng.permutation(n)[:used])
+    u = np.repeat(np.arange(used), base.degrees())
+    g = graphgen.from_edges(n, np.stack([place[u], place[base.adj]], 1).astype(np.int32))
+    for kind in (scan.COSINE, scan.JACCARD):
+        ix = scan.scan_build_index(*device_csr(g), kind, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
+        assert_index_equal(ix, oracle.build_index(g, kind, threads=8), g)
