@@ -70,12 +70,13 @@ enum {
 
 /* Per-phase device times of a build made with SCAN_PROFILE, in milliseconds,
  * from hipEvents recorded on the build stream between phases:
- *   prepare     degrees, offsets, max degree (and validation if asked),
- *               the per-row window table (when ids span several bitmap
- *               windows), the edge-ownership plan (chunk lists per table
- *               class) and the read-back of the max degree and plan counts
- *   plan        from that read-back to the first intersection launch (the
- *               device is idle here)
+ *   prepare     degrees, offsets, max degree (and validation if asked), the
+ *               edge-ownership plan (chunk lists per table class) and the
+ *               read-back of the max degree and plan counts
+ *   plan        from that read-back to the first intersection launch: with
+ *               ids over several bitmap windows their renumbering and the
+ *               per-row window table, and the product over hub rows where
+ *               one is formed (the device is idle here without them)
  *   intersect   all intersection + similarity launches, split into
  *               intersect_small (owners of degree <= small_max, one
  *               wavefront each) and intersect_big (bitmap-window owners)
@@ -268,8 +269,8 @@ scan_status scan_build_index_ex(const scan_csr *gs, int32_t count, scan_sim_kind
                                 scan_index **outs);
 
 /* Autotuner: times the phases of builds of gs (count graphs, merged as in
- * scan_build_index_batch) up to the end of the intersection (prepare, which
- * holds the ownership plan and any window table, plan and intersect) over a
+ * scan_build_index_batch) up to the end of the intersection (prepare, plan
+ * and intersect: the ownership plan, any window table, the kernels) over a
  * coordinate sweep of scan_tune (small_max, then spc, then wbits; each
  * candidate run `reps` times, the minimum kept) and writes the fastest
  * setting to *best and that time to *best_ms (may be NULL). Synchronous;

@@ -821,6 +821,7 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
   // it, it ran into the placement of the intersection's persistent workgroups:
   // R-MAT-20 7.08 instead of 6.96 ms a build.)
   IntersectPlan plan;
+  plan.one_graph = G == 1;
   const bool planned = NNZ > 0 && (!weighted || weighted_planned(N, NNZ));
   const IntersectConfig pcfg = weighted ? weighted_config(cfg) : cfg;
   if (planned) {

@@ -1,6 +1,7 @@
 // Index object and internal entry points shared by the library's host code.
 #pragma once
 
+#include <cmath>
 #include <functional>
 #include <memory>
 #include <mutex>
@@ -43,7 +44,17 @@ struct IntersectStats {
 // copies `words` int32 from `counts` to pinned `host` memory, and `ready` is
 // recorded then. The caller waits for it before
 // intersect_all.
-constexpr size_t kPlanCountBytes = 32;
+constexpr int32_t kDegBins = 192;  // eight per octave from degree 128 up
+constexpr size_t kPlanCountBytes = 32 + 4 * (size_t)kDegBins;
+// Least degree of bin b (b = kDegBins: past every degree).
+__host__ __device__ inline int32_t deg_bin_low(int b) {
+  const int64_t lo = (int64_t)(128 + 16 * (b & 7)) << (b >> 3);
+  return lo > 0x7fffffff ? 0x7fffffff : (int32_t)lo;
+}
+__device__ __forceinline__ int deg_bin(int32_t d) {  // d >= 128
+  const int o = 24 - __clz(d);
+  return 8 * o + (int)(((uint32_t)d >> (o + 4)) & 7u);
+}
 constexpr int32_t kLightDeg = kWave;  // one wavefront per vertex up to this degree
 struct PlanCounts {
   int32_t small;    // vertices of degree 1..kLightDeg
@@ -53,6 +64,7 @@ struct PlanCounts {
   int32_t done;     // workgroups of k_plan that have finished
   int32_t rows;     // vertices with neighbours
   int32_t pad[2];
+  int32_t bins[kDegBins];  // vertices by degree, from 128 up
 };
 static_assert(sizeof(PlanCounts) == kPlanCountBytes, "the maximum degrees follow the counts");
 struct BigChunk {
@@ -61,6 +73,7 @@ struct BigChunk {
 };
 struct IntersectPlan {
   int64_t n = 0, nnz = 0;
+  bool one_graph = false;  // set by the caller
   int32_t *small_list = nullptr, *heavy_list = nullptr;
   void *big_list = nullptr, *counts = nullptr;  // device chunk list and counts
   const void *host = nullptr;                   // the host's copy of the counts
@@ -74,6 +87,39 @@ struct IntersectPlan {
 scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, const int64_t *off,
                            const int32_t *deg, const int32_t *adj, int device, DevArena &arena, hipStream_t s,
                            void *counts, int32_t words, void *host, hipEvent_t ready, IntersectPlan &plan);
+
+// Common neighbours among hubs by matrix product (hubs.hip).
+constexpr int32_t kHubMaxRows = 32768, kHubMaxCols = 65536;  // counts of common columns fit 16 bits
+constexpr int32_t kHubMaxWindows = 63;
+struct HubShape {
+  int32_t rows = 0, cols = 0;        // their numbers (0: no product)
+  int32_t row_deg = 0, col_deg = 0;  // least degrees
+  int64_t slots = 0;                 // at least the rows' ids
+};
+struct HubRow {
+  int64_t off;  // its ids outside the columns: rest[off, off + len)
+  int32_t len;
+  int32_t pad;
+};
+struct HubView {
+  int32_t rows = 0, cols = 0;          // cols padded to a multiple of 256
+  int32_t stride = 0;                  // rows padded to a multiple of 256
+  const int32_t *row = nullptr;        // per vertex: its row, or -1
+  const int32_t *col = nullptr;        // per vertex: its column, or -1
+  const HubRow *row_of = nullptr;
+  const int32_t *rest = nullptr;
+  const uint4 *bits = nullptr;         // 128 columns of a row per entry (piece)
+  const uint16_t *pre = nullptr;       // [row * cols / 128 + q]: bits before block q
+  const uint16_t *D = nullptr;         // [i * stride + j], i >= j: common columns of rows i and j
+  __host__ __device__ int64_t piece(int32_t r, int32_t q) const {
+    return ((int64_t)(r >> 5) * (cols / 128) + q) * 32 + (r & 31);
+  }
+};
+HubShape choose_hubs(const PlanCounts &pc, int64_t nnz, bool one_window);
+// win (several id windows): window starts of the rows' rests, rows x (nwin + 1).
+scan_status prepare_hubs(const HubShape &shape, int64_t n, const int64_t *off, const int32_t *deg,
+                         const int32_t *adj, const int32_t *radj, int32_t wbits, int32_t nwin, int32_t *win,
+                         DevArena &arena, hipStream_t s, HubView *out);
 
 // a2-a4: ownership plan, then intersection + similarity for every edge,
 // written into both CSR slots of sims (and counts if non-null).

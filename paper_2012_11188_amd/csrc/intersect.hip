@@ -22,6 +22,11 @@
 //   k_window_table  (ids spanning several windows) the first position of
 //                   every window in every row, so that chunks read each lower
 //                   neighbour's range in a window instead of searching it.
+//   k_id_flags, k_rename  (several windows) ids numbered without the isolated
+//                   vertices, so that they span fewer windows.
+//
+// Where it pays, the common neighbours of two high-degree vertices come from a
+// matrix product (hubs.hip) and k_big_owner streams what is left of their rows.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -114,6 +119,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, int64
   __shared__ int32_t last;
   __shared__ int32_t wsum[kPlanThreads / kWave];
   __shared__ int32_t tot_small, tot_heavy, tot_big, base_small, base_heavy, base_big, rows;
+  __shared__ int32_t bins[kDegBins];
+  static_assert(kDegBins <= kPlanThreads, "a thread per degree bin");
+  if (threadIdx.x < kDegBins) bins[threadIdx.x] = 0;
+  __syncthreads();
   constexpr int64_t kTile = (int64_t)kPlanThreads * kPlanPer;
   for (int64_t t0 = (int64_t)blockIdx.x * kTile; t0 < n; t0 += (int64_t)gridDim.x * kTile) {
     const int64_t v0 = t0 + (int64_t)threadIdx.x * kPlanPer;
@@ -124,6 +133,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, int64
     for (int k = 0; k < kPlanPer; ++k) {
       const int32_t dh = v0 + k < n ? deg[v0 + k] : 0;
       nr += __popcll(__ballot(dh != 0));
+      if (dh >= 128) atomicAdd(&bins[deg_bin(dh)], 1);
       code[k] = dh == 0 ? 0 : dh <= min(small_max, kLightDeg) ? -1 : dh <= small_max ? -2 : (dh + spc - 1) / spc;
       ns += code[k] == -1;
       nh += code[k] == -2;
@@ -149,6 +159,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, int64
       for (int32_t j = 0; j < code[k]; ++j) big_list[pb++] = BigChunk{(int32_t)(v0 + k), j};
     }
   }
+  __syncthreads();
+  if (threadIdx.x < kDegBins && bins[threadIdx.x]) atomicAdd(&pc->bins[threadIdx.x], bins[threadIdx.x]);
   // The last block to finish hands the counts (and what follows them) to the
   // host's pinned copy: a copy would be a launch more before the host goes on.
   if (!last_workgroup(&pc->done, &last)) return;
@@ -389,20 +401,21 @@ template <bool kOneWindow>
 __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     const BigChunk *chunks, PlanCounts *pc, int spc, int wbits, int64_t n,
     const int64_t *off, const int32_t *deg, const int32_t *adj, const int32_t *radj, const int64_t *cid,
-    const int32_t *wt, int32_t nwin, int kind, double *sims, int32_t *counts, int32_t skip) {
+    const int32_t *wt, int32_t nwin, HubView hub, int kind, double *sims, int32_t *counts, int32_t skip) {
   extern __shared__ unsigned char smem[];
   const int64_t W = (int64_t)1 << wbits;
   const int nwords = (int)(W >> 5);
   uint32_t *bm = (uint32_t *)smem;
-  int64_t *le_ou = (int64_t *)(bm + nwords);
-  int32_t *le_lt = (int32_t *)(le_ou + spc);  // ids below h in the row (one window)
+  int64_t *le_ids = (int64_t *)(bm + nwords);  // address of the ids streamed
+  int32_t *le_lt = (int32_t *)(le_ids + spc);  // ids below h in the row; with several windows, the lower neighbour
   int32_t *le_e = le_lt + spc;
   int32_t *le_du = le_e + spc;
   int32_t *le_cnt = le_du + spc;
-  int32_t *le_b0 = le_cnt + spc;
-  int32_t *le_b1 = le_b0 + spc;  // end of the range in the current window (cursor)
-  int32_t *le_u = le_b1 + spc;    // the lower neighbour
-  int32_t *le_xp = le_u + spc;    // [spc + 1] exclusive prefix of extra segments
+  int32_t *le_b1 = le_cnt + spc;  // end of the range in the current window (cursor)
+  int32_t *le_b0 = le_b1 + spc;   // its start (several windows)
+  int32_t *le_wrow = le_b0 + spc;  // the neighbour's row of the window table (several windows)
+  int32_t *le_full = le_b0;        // [2 * spc] with one window: the neighbour's row offset
+  int32_t *le_xp = le_wrow + spc;  // [spc + 1] exclusive prefix of extra segments
   BigShared *sh = (BigShared *)(le_xp + spc + 1);
   const int tid = threadIdx.x, lane = lane_id();
   constexpr bool one_window = kOneWindow;  // the whole id space fits one window
@@ -444,6 +457,11 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     const int32_t hx = kOneWindow && cid ? (int32_t)cid[h] : h;  // h among the streamed ids
     const int64_t s0 = oh + (int64_t)ch.k * spc;
     const int m = (int)min((int64_t)spc, oh + dh - s0);
+    // An owner that is a hub streams only the ids outside the product's
+    // columns of lower neighbours that are hubs too; the count of the others
+    // is in D, and of those below h in the bits before its column.
+    const int32_t hr = hub.rows ? hub.row[h] : -1;
+    const int32_t hc = hr >= 0 ? hub.col[h] : 0;
     // Stage the chunk's lower neighbours (wave-aggregated compaction).
     for (int e0 = 0; e0 < m; e0 += blockDim.x) {
       const int e = e0 + tid;
@@ -464,14 +482,39 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
       }
       if (low) {
         const int k = base + __popcll(mk & lanes_below());
+        const int64_t ou = off[u];
+        const int32_t *ids = radj + ou;  // what is streamed, and how much of it
+        int32_t len = du, cnt = 0, lt = 0, wrow = u;
+        const int32_t r = hr >= 0 ? hub.row[u] : -1;
+        if (r >= 0) {
+          const HubRow q = hub.row_of[r];
+          ids = hub.rest + q.off;
+          len = q.len;
+          cnt = hub.D[(int64_t)max(r, hr) * hub.stride + min(r, hr)];
+          wrow = (int32_t)n + r;
+          if (one_window) {
+            const uint4 b = hub.bits[hub.piece(r, hc >> 7)];
+            const uint64_t lo = (uint64_t)b.y << 32 | b.x, hi = (uint64_t)b.w << 32 | b.z;
+            const uint64_t below = (1ull << (hc & 63)) - 1;
+            lt = hub.pre[(int64_t)r * (hub.cols / 128) + (hc >> 7)] +
+                 ((hc & 64) ? __popcll(lo) + __popcll(hi & below) : __popcll(lo & below));
+          }
+        }
         le_e[k] = e;
-        le_u[k] = u;
         le_du[k] = du;
-        le_ou[k] = off[u];
-        le_cnt[k] = 0;
-        le_lt[k] = 0;
-        le_b0[k] = 0;
-        le_b1[k] = one_window ? du : 0;
+        le_ids[k] = (int64_t)(uintptr_t)ids;
+        le_cnt[k] = cnt;
+        if (one_window) {
+          le_full[2 * k] = (int32_t)(uint32_t)ou;  // the row's offset, for the mirror slot
+          le_full[2 * k + 1] = (int32_t)(ou >> 32);
+          le_lt[k] = lt;
+          le_b1[k] = len;
+        } else {
+          le_lt[k] = u;
+          le_wrow[k] = wrow;
+          le_b0[k] = 0;
+          le_b1[k] = 0;
+        }
       }
     }
     __syncthreads();
@@ -513,7 +556,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
         const int64_t kw = w0 >> wbits;
         if (tid < nlow) {
           if (pf_w != kw) {
-            const int32_t *t = wt + (int64_t)le_u[tid] * (nwin + 1) + kw;
+            const int32_t *t = wt + (int64_t)le_wrow[tid] * (nwin + 1) + kw;
             pf0 = t[0];
             pf1 = t[1];
           }
@@ -530,7 +573,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
           const int32_t i = __builtin_amdgcn_readlane(old, 0);
           if (i >= nlow) break;
           const int32_t du = uniform(le_du[i]);
-          const int32_t *row = radj + uniform64(le_ou[i]);
+          const int32_t *row = (const int32_t *)(uintptr_t)uniform64(le_ids[i]);  // (no hubs here)
           const int64_t b0 = wave_lower_bound(row, uniform(le_b1[i]), du, (int32_t)w0);
           const int64_t b1 = wave_lower_bound(row, b0, du, (int32_t)min(w0 + W, (int64_t)INT32_MAX));
           le_b0[i] = (int32_t)b0;
@@ -541,7 +584,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
       // Extra segments of long ranges, as an exclusive prefix over the edges.
       int32_t ex = 0;
       if (tid < nlow) {
-        const int32_t len = le_b1[tid] - le_b0[tid];
+        const int32_t len = le_b1[tid] - (one_window ? 0 : le_b0[tid]);
         ex = len > kItem ? (len - 1) / kItem : 0;
       }
       const int32_t xp = block_excl_scan(ex, sh->wsum, &sh->nextra);
@@ -551,7 +594,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
       const int32_t nitems = nlow + uniform(sh->nextra);
       if (!one_window && wt && pe < dh && tid < nlow) {  // the next window's ranges, read during the items
         const int64_t kwn = (int64_t)radj[oh + pe] >> wbits;
-        const int32_t *t = wt + (int64_t)le_u[tid] * (nwin + 1) + kwn;
+        const int32_t *t = wt + (int64_t)le_wrow[tid] * (nwin + 1) + kwn;
         pf0 = t[0];
         pf1 = t[1];
         pf_w = kwn;
@@ -565,12 +608,12 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
         if (lane == 0) old = atomicAdd(&sh->next, 1);
         return old;
       };
-      auto resolve = [&](int32_t tok, int32_t &e, int32_t &lo, int32_t &hi, int64_t &ou) {
+      auto resolve = [&](int32_t tok, int32_t &e, int32_t &lo, int32_t &hi, const int32_t *&ids) {
         const int32_t j = __builtin_amdgcn_readlane(tok, 0);
         if (j >= nitems) {
           e = -1;
           lo = hi = 0;
-          ou = 0;
+          ids = radj;
           return;
         }
         int32_t ee = j, sg = 0;
@@ -591,8 +634,8 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
           sg = 1 + jj - uniform(le_xp[a0]);
         }
         e = ee;
-        ou = uniform64(le_ou[ee]);
-        lo = uniform(le_b0[ee]) + sg * kItem;
+        ids = (const int32_t *)(uintptr_t)uniform64(le_ids[ee]);
+        lo = (one_window ? 0 : uniform(le_b0[ee])) + sg * kItem;
         hi = min(uniform(le_b1[ee]), lo + kItem);
       };
       // Probes the group of kWave * kUnroll ids that starts at position g0
@@ -629,10 +672,10 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
       // fetched for them, and no bound check or mask is needed; the probe
       // masks those lanes). Addressing is scalar base + lane offset +
       // immediate: no vector instruction per load.
-      auto fetch_item = [&](int32_t x[kItemLoads], int64_t ou, int32_t lo, int32_t len) {
+      auto fetch_item = [&](int32_t x[kItemLoads], const int32_t *ids, int32_t lo, int32_t len) {
         // resource word 3: DATA_FORMAT 32 (a valid format enables the buffer)
         const __amdgpu_buffer_rsrc_t r =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(radj + ou + lo), (short)0, len * 4, 0x00020000);
+            __builtin_amdgcn_make_buffer_rsrc((void *)(ids + lo), (short)0, len * 4, 0x00020000);
 #pragma unroll
         for (int j = 0; j < kItemLoads; ++j) x[j] = __builtin_amdgcn_raw_buffer_load_b32(r, lane * 4 + j * kWave * 4, 0, 0);
       };
@@ -653,21 +696,21 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
       // out before a probe and is resolved after it, when the probe has
       // freed its registers, so no claim waits on loads in flight.
       int32_t ea, loa, hia, eb, lob, hib;
-      int64_t oua, oub;
+      const int32_t *ida, *idb;
       int32_t xa[kItemLoads], xb[kItemLoads];
-      resolve(take(), ea, loa, hia, oua);
-      fetch_item(xa, oua, loa, hia - loa);
-      resolve(take(), eb, lob, hib, oub);
+      resolve(take(), ea, loa, hia, ida);
+      fetch_item(xa, ida, loa, hia - loa);
+      resolve(take(), eb, lob, hib, idb);
       while (ea >= 0) {
-        fetch_item(xb, oub, lob, hib - lob);
+        fetch_item(xb, idb, lob, hib - lob);
         const int32_t ta = take();
         probe_item(xa, ea, hia - loa);
-        resolve(ta, ea, loa, hia, oua);
+        resolve(ta, ea, loa, hia, ida);
         if (eb < 0) break;
-        fetch_item(xa, oua, loa, hia - loa);
+        fetch_item(xa, ida, loa, hia - loa);
         const int32_t tb = take();
         probe_item(xb, eb, hib - lob);
-        resolve(tb, eb, lob, hib, oub);
+        resolve(tb, eb, lob, hib, idb);
       }
       __syncthreads();
       for (int64_t i = p + tid; !one_window && i < pe; i += blockDim.x) {
@@ -684,10 +727,11 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
       if (one_window) {
         // h sits after the ids below it (absent only from an asymmetric row)
         const int32_t lt = le_lt[i];
-        if (lt < le_du[i] && adj[le_ou[i] + lt] == h) mir = le_ou[i] + lt;
+        const int64_t ou = (int64_t)(uint32_t)le_full[2 * i] | (int64_t)le_full[2 * i + 1] << 32;
+        if (lt < le_du[i] && adj[ou + lt] == h) mir = ou + lt;
       } else {
         // h may lie in a window that holds no id of N(h): locate it directly
-        const int64_t ou = le_ou[i];
+        const int64_t ou = off[le_lt[i]];
         int64_t lo = 0, hi = le_du[i];
         while (lo < hi) {
           const int64_t mid = (lo + hi) >> 1;
@@ -873,13 +917,27 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
       renamed = nullptr;
       cid = nullptr;
     }
+  }
+  // Common neighbours among hubs by matrix product, where that saves enough.
+  // (Not in approximate builds, which leave the hubs' edges out.)
+  const bool table = nwin > 1 && !cfg.search_windows;
+  HubShape shape;
+  if (h.big && plan->one_graph && cfg.skip_deg == 0x7fffffff && (nwin == 1 || (table && nwin <= kHubMaxWindows)))
+    shape = choose_hubs(h, nnz, nwin == 1);
+  if (h.big && nwin > 1) {
     // The window table, unless it would exceed kMaxWindowTable bytes or the
     // searched ranges are asked for; then chunks search them per window.
-    if (nwin > 1 && !cfg.search_windows && (size_t)(nwin + 1) * (size_t)n * 4 <= kMaxWindowTable) {
-      SCAN_TRY(tmp.alloc(&wt, (int64_t)(nwin + 1) * n));
+    // The rows of the hubs' rests follow those of the vertices.
+    if (table && (size_t)(nwin + 1) * (size_t)n * 4 <= kMaxWindowTable) {
+      SCAN_TRY(tmp.alloc(&wt, (int64_t)(nwin + 1) * (n + shape.rows)));
       k_window_table<<<grid_for(n * kWave, 256), 256, 0, s>>>(off, renamed ? renamed : adj, n, wbits, nwin, wt);
     }
   }
+  HubView hub;
+  if (shape.rows && (nwin == 1 || wt) &&
+      prepare_hubs(shape, n, off, deg, adj, renamed ? renamed : adj, wbits, nwin,
+                   wt ? wt + (int64_t)(nwin + 1) * n : nullptr, tmp, s, &hub) != SCAN_OK)
+    hub = HubView{};  // no memory for it: every row is streamed whole
   if (big_lds_bytes(wbits, cfg.spc) > (size_t)lds_max) return fail(SCAN_EINVAL, "chunk size too large for LDS");
   if (stats) {
     stats->wbits = wbits;
@@ -904,7 +962,10 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   // neither waits for the other.
   auto fork = [&](int k, bool used) -> hipStream_t {
     if (!used || !h.big) return s;
-    if (plan->helper[k]) return plan->helper[k];  // ordered after the plan by the caller
+    // Ordered after the plan by the caller; after the hub product they run
+    // beside the large-owner kernel, which leaves room for them, and not
+    // beside the product, which does not.
+    if (plan->helper[k] && (!hub.rows || stream_wait(plan->helper[k], s) == SCAN_OK)) return plan->helper[k];
     hipStream_t hs = helper_stream(k);
     if (!hs || stream_wait(hs, s) != SCAN_OK) return s;
     return hs;
@@ -927,10 +988,10 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
     SCAN_TRY(mark(stats ? stats->ev_big_begin : nullptr, s));
     if (one)
       k_big_owner<true><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, off, deg, adj, radj, cid, nullptr,
-                                                       nwin, kind, sims, counts, cfg.skip_deg);
+                                                       nwin, hub, kind, sims, counts, cfg.skip_deg);
     else
       k_big_owner<false><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, off, deg, adj, radj, cid, wt,
-                                                        nwin, kind, sims, counts, cfg.skip_deg);
+                                                        nwin, hub, kind, sims, counts, cfg.skip_deg);
     SCAN_HIP_TRY(hipGetLastError());
     SCAN_TRY(mark(stats ? stats->ev_big_end : nullptr, s));
   } else {

@@ -69,3 +69,28 @@ def test_isolated_vertices_left_out(used, n, tune):
     for kind in (scan.COSINE, scan.JACCARD):
         ix = scan.scan_build_index(*device_csr(g), kind, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
         assert_index_equal(ix, oracle.build_index(g, kind, threads=8), g)
+
+
+# a dense core (rows and columns of the hub product: tiles of 256, column
+# blocks of 256) with a sparse rim whose ids lie between the core's; one id
+# window, several, and ranges searched instead of tabled (no product)
+@pytest.mark.parametrize("core,rim,tune", [(1535, 0, None), (1536, 100, None), (1537, 6000, None), (1700, 9000, None),
+                                           (1537, 6000, {"wbits": 11}), (1700, 9000, {"wbits": 12, "spc": 96}),
+                                           (1700, 3000, {"wbits": 10, "small_max": 900}),
+                                           (1537, 6000, {"wbits": 11, "flags": scan.SCAN_TUNE_SEARCH_WINDOWS})])
+def test_hub_product(core, rim, tune):
+    from gpu_util import device_csr
+
+    rng = np.random.default_rng(core + rim)
+    n = core + rim
+    place = rng.permutation(n)
+    p = np.where(np.arange(core) < core // 3, 0.97, 0.6)  # two levels of degree
+    u, v = np.nonzero(np.triu(rng.random((core, core)) < np.sqrt(p[:, None] * p[None, :]), 1))
+    edges = [np.stack([place[u], place[v]], 1)]
+    if rim:
+        k = 6 * rim
+        edges.append(np.stack([place[core + rng.integers(0, rim, k)], place[rng.integers(0, n, k)]], 1))
+    g = graphgen.from_edges(n, np.concatenate(edges).astype(np.int32))
+    for kind in (scan.COSINE, scan.JACCARD):
+        ix = scan.scan_build_index(*device_csr(g), kind, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
+        assert_index_equal(ix, oracle.build_index(g, kind, threads=8), g)
