@@ -562,11 +562,11 @@ void index_release(scan_index *ix) {
 namespace {
 
 // Intersection shapes of builds over several id windows, where the caller
-// leaves them open: every chunk sweeps the windows, so larger chunks and fewer
-// of them pay (768 slots is what the LDS holds beside the bitmap; R-MAT-23:
-// 445 ms a build with 256 and 512, 417 with these; 3.5M vertices: 62 and 58).
+// leaves them open: every chunk sweeps the windows, so the largest chunks pay
+// (a thread per slot; R-MAT-23 with 512, 768 and 1024: 338, 327 and 316 ms a
+// build; owners of up to 256 and 1024 among the small ones: 327 and 390).
 constexpr int64_t kWideN = (int64_t)1 << 21;
-constexpr int32_t kWideSmallMax = 512, kWideSpc = 768;
+constexpr int32_t kWideSmallMax = 512, kWideSpc = 1024;
 
 // A pinned block and the event after its last use by the device; waits for
 // that use before the block goes back to the pool.

@@ -69,7 +69,10 @@ struct PlanCounts {
 static_assert(sizeof(PlanCounts) == kPlanCountBytes, "the maximum degrees follow the counts");
 struct BigChunk {
   int32_t h;
-  int32_t k;  // slots [k*spc, (k+1)*spc) of row h
+  int32_t k;    // slots [k*spc, (k+1)*spc) of row h
+  int32_t dh;   // degree of h
+  int32_t pad;
+  int64_t oh;   // first slot of row h
 };
 struct IntersectPlan {
   int64_t n = 0, nnz = 0;

@@ -112,7 +112,7 @@ constexpr int kPlanPer = 8;  // consecutive vertices per thread and tile
 // read the neighbour degrees anyway; a vertex that owns nothing costs one
 // staging pass). The block scans its counts, reserves list space with one
 // global atomic per list, and writes the entries in vertex order.
-__global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, int64_t n, int small_max,
+__global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, const int64_t *off, int64_t n, int small_max,
                                                        int spc, int32_t *small_list, int32_t *heavy_list,
                                                        BigChunk *big_list, PlanCounts *pc, int32_t words,
                                                        int32_t *host) {
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, int64
     for (int k = 0; k < kPlanPer; ++k) {
       if (code[k] == -1) small_list[ps++] = (int32_t)(v0 + k);
       if (code[k] == -2) heavy_list[ph++] = (int32_t)(v0 + k);
-      for (int32_t j = 0; j < code[k]; ++j) big_list[pb++] = BigChunk{(int32_t)(v0 + k), j};
+      for (int32_t j = 0; j < code[k]; ++j) big_list[pb++] = BigChunk{(int32_t)(v0 + k), j, deg[v0 + k], 0, off[v0 + k]};
     }
   }
   __syncthreads();
@@ -342,26 +342,30 @@ __global__ __launch_bounds__(WAVES * kWave) void k_small_owner(
 // Big owners: persistent workgroups with an LDS bitmap window.
 
 constexpr int kBigThreads = 1024;
-#ifndef SCAN_BIG_RUN
-#define SCAN_BIG_RUN 4
-#endif
-constexpr int kUnroll = 4;   // ids per lane per probe group
-constexpr int kSeg = 1024;   // most ids per work item (rows longer than this are split)
+constexpr int kBigRun = 4;   // chunks per claim (one window)
+constexpr int kUnroll = 4;   // LDS reads in flight per wavefront
+constexpr int kDeep = 2;     // items of a wavefront, one probed and one in flight (3 and 4 measured the same)
+// Short ranges are taken four per wavefront, by rows of lanes: a whole
+// wavefront on one has most of its loads past the end (R-MAT-23, up to 64,
+// 128 and 192 ids: 294, 284 and 304 ms; none: 330).
+constexpr int kRow = 16;      // lanes per short range
+constexpr int kShort = 128;   // its most ids
 
-// Word of the owner bitmap holding bit y. The bitmap starts the kernel's
-// dynamic LDS, which starts at LDS address 0 because the kernel has no
-// static LDS (the host checks), so the byte address is (y / 32) * 4: two
-// instructions, where a pointer to the bitmap costs a third (adding a base
-// the compiler cannot fold).
-__device__ __forceinline__ uint32_t bitmap_word(uint32_t y) {
-  return *(const __attribute__((address_space(3))) uint32_t *)(size_t)((y >> 3) & ~3u);
+// Word of the owner bitmap holding id x's bit (x & 31), with the words' byte
+// addresses under mask: ids of other windows are not asked for, and an id's
+// place in its own window are its low bits. The bitmap starts the kernel's
+// dynamic LDS, which starts at LDS address 0 because the kernel has no static
+// LDS (the host checks), so the byte address takes two instructions, where a
+// pointer to the bitmap costs a third (adding a base the compiler cannot fold).
+__device__ __forceinline__ uint32_t bitmap_word(uint32_t x, uint32_t mask) {
+  return *(const __attribute__((address_space(3))) uint32_t *)(size_t)((x >> 3) & mask);
 }
 
 struct BigShared {
-  int32_t chunk;
-  int32_t run_next, run_left;  // the rest of the workgroup's current run of chunks
-  int32_t nlow;
-  int32_t next;
+  int32_t claim[2];  // chunk claimed for later, by iteration parity
+  int32_t some[2];   // the last iteration whose chunk has lower neighbours, by parity
+  int32_t nlong, nshort;
+  int32_t next, snext;
   int32_t nextra;
   int32_t wsum[kBigThreads / kWave];
 };
@@ -390,13 +394,24 @@ __device__ __forceinline__ int64_t wave_lower_bound(const int32_t *row, int64_t 
 
 // One workgroup per chunk (owner h, up to spc row slots), persistent over a
 // global chunk counter. Per id window: the owner's ids in the window are set
-// in the LDS bitmap; each lower neighbour's ids in the window are cut into
-// segments of kSeg ids, and wavefronts claim segments from an LDS counter
-// (item j < nlow is the first segment of edge j; later items are the extra
-// segments of long rows), so one long row cannot hold the workgroup at the
-// barrier that ends the window. Partial counts meet in LDS. Rows are streamed
-// and set from radj: adj itself, or the same rows with ids numbered without
-// the isolated vertices (cid), in the same order.
+// in the LDS bitmap; each lower neighbour's ids in the window (its range) are
+// looked up there, the short ranges four per wavefront, the long ones in items
+// of kItem ids, which wavefronts claim from an LDS counter (item j < nlong is
+// the first of long range j; later ones are the further items of ranges longer
+// than that), so that one long row cannot hold the workgroup at the barrier
+// that ends the window. Partial counts meet in LDS. Rows are streamed and set
+// from radj: adj itself, or the same rows with ids numbered without the
+// isolated vertices (cid), in the same order.
+//
+// No unit is saturated: on R-MAT-20, alone, 3.1 ms with the vector units and
+// the LDS each at 48 %, 11 GB read from the Infinity Cache at 3.6 of 7.6 TB/s
+// (random kilobytes, measured), a quarter of the wavefronts' time waiting for
+// their turn to issue. What helped was fewer instructions and fewer waits per
+// id and per range (before, with the hub product: R-MAT-20 4.13 ms, R-MAT-23
+// 330; now 3.70 and 268): LDS reads in groups, short ranges together, ranges
+// past the end read as id 0 and taken out of the sums, claims not waited for,
+// the next chunk's data read ahead. Two workgroups of half the size where the
+// bitmap leaves room (2^19 vertices) were slower, 3.29 against 3.12 ms a build.
 template <bool kOneWindow>
 __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     const BigChunk *chunks, PlanCounts *pc, int spc, int wbits, int64_t n,
@@ -405,209 +420,258 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
   extern __shared__ unsigned char smem[];
   const int64_t W = (int64_t)1 << wbits;
   const int nwords = (int)(W >> 5);
+  const uint32_t wmask = (uint32_t)(nwords - 1) * 4;
   uint32_t *bm = (uint32_t *)smem;
-  int64_t *le_ids = (int64_t *)(bm + nwords);  // address of the ids streamed
-  int32_t *le_lt = (int32_t *)(le_ids + spc);  // ids below h in the row; with several windows, the lower neighbour
-  int32_t *le_e = le_lt + spc;
-  int32_t *le_du = le_e + spc;
-  int32_t *le_cnt = le_du + spc;
-  int32_t *le_b1 = le_cnt + spc;  // end of the range in the current window (cursor)
-  int32_t *le_b0 = le_b1 + spc;   // its start (several windows)
-  int32_t *le_wrow = le_b0 + spc;  // the neighbour's row of the window table (several windows)
-  int32_t *le_full = le_b0;        // [2 * spc] with one window: the neighbour's row offset
-  int32_t *le_xp = le_wrow + spc;  // [spc + 1] exclusive prefix of extra segments
-  BigShared *sh = (BigShared *)(le_xp + spc + 1);
+  // Per slot of the chunk, where it is a lower neighbour:
+  struct Range {
+    const int32_t *ids;  // what is streamed of the row
+    int32_t b0, b1;      // positions in the current window
+  };
+  static_assert(sizeof(Range) == 16, "one LDS read");
+  Range *le = (Range *)(bm + nwords);
+  int32_t *le_cnt = (int32_t *)(le + spc);  // common neighbours found
+  int32_t *le_lt = le_cnt + spc;  // ids below h in the row (searched windows: the row's length)
+  int32_t *le_xp = le_lt + spc;   // exclusive prefix of the long ranges' extra segments
+  BigShared *sh = (BigShared *)(le_xp + spc);
+  uint16_t *le_ord = (uint16_t *)(sh + 1);  // slots with long ranges from the front, with short ones from the back
   const int tid = threadIdx.x, lane = lane_id();
   constexpr bool one_window = kOneWindow;  // the whole id space fits one window
-  // Ids per work item: with several windows the per-window ranges are short
-  // and half-size items measure faster (R-MAT-23: 0.57 against 0.62 s),
-  // with one window full-size ones (R-MAT-20: 5.6 against 5.8 ms).
-  constexpr int kItem = kOneWindow ? kSeg : kSeg / 2;
+  // Ids per work item: with several windows the ranges are shorter
+  // (R-MAT-23, 512 and 1024: 284.0 and 284.2 ms; R-MAT-20: 3.76 and 3.74).
+  constexpr int kItem = kOneWindow ? 1024 : 512;
   constexpr int kItemLoads = kItem / kWave;
   constexpr int kGroups = kItem / (kWave * kUnroll);
 
   const int32_t nchunks = pc->big;  // written by k_plan: no host round trip
-  for (int i = tid; i < nwords; i += blockDim.x) bm[i] = 0u;
-  if (tid == 0) sh->run_left = 0;
+  if (nchunks <= 0) return;
   // With one window, chunks are claimed in runs of kRun consecutive ones:
   // a high-degree owner's chunks are consecutive, so a run often keeps one
   // owner, and the owner's bits stay in the bitmap from chunk to chunk
-  // (they are cleared only when the next chunk has another owner).
-  constexpr int32_t kRun = kOneWindow ? SCAN_BIG_RUN : 1;
-  int32_t held = -1, held_dh = 0;  // the owner whose bits the bitmap holds
-  int64_t held_oh = 0;
-  for (;;) {
-    __syncthreads();
-    if (tid == 0) {
-      if (sh->run_left == 0) {
-        sh->run_next = atomicAdd(&pc->counter, kRun);
-        sh->run_left = kRun;
+  // (they are cleared only when the next chunk has another owner). The last
+  // chunks are claimed one by one.
+  constexpr int32_t kRun = kOneWindow ? kBigRun : 1;
+  int32_t run_base = 0, run_pos = 0, run_len = 0;  // (of thread 0)
+  // The bitmap is cleared as a whole: 128 KB are written in half a
+  // microsecond, less than it takes to read back the ids that were set.
+  auto wipe = [&]() {
+    for (int i = tid; i < nwords / 4; i += kBigThreads) ((uint4 *)bm)[i] = uint4{0, 0, 0, 0};
+  };
+  struct Owner {
+    int32_t ci, h, dh, m;  // chunk, vertex, degree, slots in the chunk
+    int64_t oh, s0;        // first slot of the row, of the chunk
+  };
+  // (words: a chunk's descriptor spread over the lanes)
+  auto owner_of = [&](int32_t ci, int32_t words) {
+    Owner o;
+    const bool ok = ci >= 0 && ci < nchunks;
+    o.ci = ci;
+    auto word = [&](size_t at) { return __builtin_amdgcn_readlane(words, (int)(at / 4)); };
+    o.h = word(offsetof(BigChunk, h));
+    o.dh = ok ? word(offsetof(BigChunk, dh)) : 0;
+    o.oh = (int64_t)(uint32_t)word(offsetof(BigChunk, oh)) | (int64_t)word(offsetof(BigChunk, oh) + 4) << 32;
+    o.s0 = o.oh + (int64_t)word(offsetof(BigChunk, k)) * spc;
+    o.m = ok ? (int32_t)min((int64_t)spc, o.oh + o.dh - o.s0) : 0;
+    return o;
+  };
+  const bool own_tab = !one_window && wt && nwin < kWave;
+  constexpr int kOwn = 4;  // owner ids per thread in flight
+
+  // A chunk's data come through a chain of dependent reads: claim,
+  // descriptor, ids, their degrees and offsets, the hubs' counts. They are
+  // made up to three chunks ahead, one step of the chain per chunk, so that
+  // each is in flight while a whole chunk is handled (waiting for them in
+  // turn took 10 of the 46 thousand cycles of a chunk of R-MAT-20). Thread t carries slot t
+  // in registers. Iterations whose chunk is not there yet have no slots.
+  Owner cur{-1, 0, 0, 0, 0, 0}, nxt = cur;  // this chunk and the next
+  int32_t c2 = -1;                           // the chunk after
+  int32_t d2 = 0;
+  bool low = false;                          // this chunk's slot is a lower neighbour, and then:
+  int32_t u = 0, du = 0, wrow = 0;           // it, its degree, its row of the window table
+  int64_t ou = 0;                            // and its first slot
+  int32_t un = 0, du_n = 0, r_n = -1;        // the next chunk's slot: vertex, degree, hub row
+  int64_t ou_n = 0;
+  int32_t of_n = 0;                          // the next owner's hub row and column, and its id among the streamed ones
+  int32_t hc = 0, hx = 0;                    // this one's
+  bool hubs = false;                         // this chunk's slot is an edge between hubs, and then:
+  HubRow hq{0, 0, 0};
+  int32_t hcnt = 0, hpre = 0;
+  uint4 hbits{0, 0, 0, 0};
+  int32_t ox[kOwn];              // the owner's ids at positions p + tid + j * kBigThreads
+  int32_t own = 0, own_n = 0;    // the owner's row of the window table, spread over the lanes
+  int32_t kw = 0, pe = 0;        // window, and end of its ids in the owner's row
+  int32_t pf0 = 0, pf1 = 0;      // the slot's range in it
+  int32_t held = -1;             // the owner whose bits the bitmap holds (one window)
+#pragma unroll
+  for (int j = 0; j < kOwn; ++j) ox[j] = 0;
+  auto load_own = [&](const Owner &o, int32_t p, int32_t pe) {
+#pragma unroll
+    for (int j = 0; j < kOwn; ++j) ox[j] = radj[o.oh + p + min(tid + j * kBigThreads, pe - p - 1)];
+  };
+  auto set_own = [&](const Owner &o, int32_t p, int32_t pe, int32_t w0) {
+    for (;;) {
+#pragma unroll
+      for (int j = 0; j < kOwn; ++j) {
+        const int32_t x = ox[j] - w0;
+        if (tid + j * kBigThreads < pe - p) atomicOr(&bm[x >> 5], 1u << (x & 31));
       }
-      sh->chunk = sh->run_next++;
-      --sh->run_left;
-      sh->nlow = 0;
+      if (pe - p <= kOwn * kBigThreads) break;
+      p += kOwn * kBigThreads;
+      load_own(o, p, pe);
     }
-    __syncthreads();
-    const int32_t ci = uniform(sh->chunk);
-    if (ci >= nchunks) break;
-    const BigChunk ch = chunks[ci];
-    const int32_t h = ch.h;
-    const int32_t dh = deg[h];
-    const int64_t oh = off[h];
-    const int32_t hx = kOneWindow && cid ? (int32_t)cid[h] : h;  // h among the streamed ids
-    const int64_t s0 = oh + (int64_t)ch.k * spc;
-    const int m = (int)min((int64_t)spc, oh + dh - s0);
-    // An owner that is a hub streams only the ids outside the product's
-    // columns of lower neighbours that are hubs too; the count of the others
-    // is in D, and of those below h in the bits before its column.
-    const int32_t hr = hub.rows ? hub.row[h] : -1;
-    const int32_t hc = hr >= 0 ? hub.col[h] : 0;
-    // Stage the chunk's lower neighbours (wave-aggregated compaction).
-    for (int e0 = 0; e0 < m; e0 += blockDim.x) {
-      const int e = e0 + tid;
-      int32_t u = 0, du = 0;
-      bool low = false;
-      if (e < m) {
-        u = adj[s0 + e];
-        du = deg[u];
-        low = is_lower(u, du, h, dh) && du <= skip;
-      }
-      const uint64_t mk = __ballot(low);
-      int32_t base = 0;
-      if (mk) {
-        const int leader = __ffsll((unsigned long long)mk) - 1;
-        int32_t old = 0;
-        if (lane == leader) old = atomicAdd(&sh->nlow, __popcll(mk));
-        base = __builtin_amdgcn_readlane(old, leader);
-      }
-      if (low) {
-        const int k = base + __popcll(mk & lanes_below());
-        const int64_t ou = off[u];
-        const int32_t *ids = radj + ou;  // what is streamed, and how much of it
-        int32_t len = du, cnt = 0, lt = 0, wrow = u;
-        const int32_t r = hr >= 0 ? hub.row[u] : -1;
-        if (r >= 0) {
-          const HubRow q = hub.row_of[r];
-          ids = hub.rest + q.off;
-          len = q.len;
-          cnt = hub.D[(int64_t)max(r, hr) * hub.stride + min(r, hr)];
-          wrow = (int32_t)n + r;
-          if (one_window) {
-            const uint4 b = hub.bits[hub.piece(r, hc >> 7)];
-            const uint64_t lo = (uint64_t)b.y << 32 | b.x, hi = (uint64_t)b.w << 32 | b.z;
-            const uint64_t below = (1ull << (hc & 63)) - 1;
-            lt = hub.pre[(int64_t)r * (hub.cols / 128) + (hc >> 7)] +
-                 ((hc & 64) ? __popcll(lo) + __popcll(hi & below) : __popcll(lo & below));
-          }
-        }
-        le_e[k] = e;
-        le_du[k] = du;
-        le_ids[k] = (int64_t)(uintptr_t)ids;
-        le_cnt[k] = cnt;
-        if (one_window) {
-          le_full[2 * k] = (int32_t)(uint32_t)ou;  // the row's offset, for the mirror slot
-          le_full[2 * k + 1] = (int32_t)(ou >> 32);
-          le_lt[k] = lt;
-          le_b1[k] = len;
-        } else {
-          le_lt[k] = u;
-          le_wrow[k] = wrow;
-          le_b0[k] = 0;
-          le_b1[k] = 0;
-        }
-      }
+  };
+  // The window of position p of the owner's row, and where its ids end there.
+  auto window_at = [&](const Owner &o, int32_t row, int32_t p, int32_t &k, int32_t &end) {
+    if (own_tab) {
+      k = __popcll(__ballot(row <= p)) - 1;
+      end = __builtin_amdgcn_readlane(row, k + 1);
+      return;
     }
+    k = uniform(radj[o.oh + p] >> wbits);
+    const int64_t w1 = (int64_t)(k + 1) << wbits;
+    end = wt ? uniform(wt[(int64_t)o.h * (nwin + 1) + k + 1])
+             : (int32_t)wave_lower_bound(radj + o.oh, p, o.dh, (int32_t)min(w1, (int64_t)INT32_MAX));
+  };
+  auto load_ranges = [&](bool is_low, int32_t row) {
+    if (wt && is_low) {
+      const int32_t *t = wt + (int64_t)row * (nwin + 1) + kw;
+      pf0 = t[0];
+      pf1 = t[1];
+    }
+  };
+
+  wipe();
+  if (tid == 0) {
+    sh->claim[0] = -1;
+    sh->some[0] = sh->some[1] = -1;
+    sh->nlong = sh->nshort = sh->nextra = 0;
+    sh->next = sh->snext = 0;
+  }
+  for (int32_t it = 0;; ++it) {
     __syncthreads();
-    const int nlow = uniform(sh->nlow);
-    if (nlow == 0) continue;
-    if (one_window && h != held) {
-      if (held >= 0) {
-        for (int i = tid; i < held_dh; i += blockDim.x) bm[(uint32_t)radj[held_oh + i] >> 5] = 0u;
-        __syncthreads();  // the new owner's bits may share words with the old one's
+    if (cur.ci >= nchunks) break;
+    const int32_t c3 = uniform(sh->claim[it & 1]);
+    const Owner own_c = cur;
+    const int32_t h = own_c.h, dh = own_c.dh;
+    if (tid < own_c.m) {
+      // An edge between two hubs streams only the ids outside the product's
+      // columns; the count of the others is in D, and of those below h in the
+      // bits before its column.
+      int32_t lt = !one_window && !wt && low ? du : 0;
+      if (one_window && hubs) {
+        const uint64_t lo = (uint64_t)hbits.y << 32 | hbits.x, hi = (uint64_t)hbits.w << 32 | hbits.z;
+        const uint64_t below = (1ull << (hc & 63)) - 1;
+        lt = hpre + ((hc & 64) ? __popcll(lo) + __popcll(hi & below) : __popcll(lo & below));
       }
-      for (int i = tid; i < dh; i += blockDim.x) {
-        const int32_t x = radj[oh + i];
-        atomicOr(&bm[x >> 5], 1u << (x & 31));
+      le_cnt[tid] = hubs ? hcnt : 0;
+      le_lt[tid] = lt;
+      le[tid] = Range{hubs ? hub.rest + hq.off : radj + ou, 0, !one_window || !low ? 0 : hubs ? hq.len : du};
+    }
+    // The next chunk's slots, and what follows of the chain.
+    auto advance = [&]() {
+      du_n = deg[un];
+      ou_n = off[un];
+      if (hub.rows) r_n = hub.row[un];
+      if (own_tab) own_n = lane <= nwin ? wt[(int64_t)nxt.h * (nwin + 1) + lane] : INT32_MAX;
+      c2 = c3;
+      d2 = ((const int32_t *)(chunks + max(0, min(c3, nchunks - 1))))[min(lane, (int)(sizeof(BigChunk) / 4) - 1)];
+      if (tid == 0 && run_pos == run_len) {
+        run_len = run_base + 16 * (int32_t)gridDim.x < nchunks ? kRun : 1;
+        run_base = atomicAdd(&pc->counter, run_len);
+        run_pos = 0;
       }
+    };
+    if (one_window && own_c.m && h != held) {
+      set_own(own_c, 0, dh, 0);
       held = h;
-      held_oh = oh;
-      held_dh = dh;
     }
-    // Windows of ids [w0, w0 + W) that hold ids of N(h), in increasing order.
-    // With the window table, thread i < nlow reads edge i's range in the
-    // next window while the current window's items run (pf_w: the window
-    // its prefetched pair belongs to).
-    int64_t p = 0;
-    int32_t pf0 = 0, pf1 = 0;
-    int64_t pf_w = -1;
+    if (!one_window) advance();
+    // Windows of ids [w0, w0 + W) that hold ids of N(h), in increasing order:
+    // window kw holds positions [p, pe) of the owner's row. The owner's ids in
+    // the next window and, with the table, the slot's range in it are read
+    // while the current window's items run.
+    int32_t p = 0;
+    if (one_window) pe = dh;
+    if (!one_window && uniform(sh->some[it & 1]) != it) p = dh;  // no lower neighbours
+    if (one_window && dh == 0) advance();
     while (p < dh) {
-      const int64_t w0 = one_window ? 0 : ((int64_t)radj[oh + p] >> wbits) << wbits;
-      const int64_t pe = one_window ? dh
-                         : wt ? (int64_t)wt[(int64_t)h * (nwin + 1) + (w0 >> wbits) + 1]
-                              : wave_lower_bound(radj + oh, p, dh, (int32_t)min(w0 + W, (int64_t)INT32_MAX));
-      for (int64_t i = p + tid; !one_window && i < pe; i += blockDim.x) {
-        const int32_t x = (int32_t)(radj[oh + i] - w0);
-        atomicOr(&bm[x >> 5], 1u << (x & 31));
-      }
+      const int32_t w0 = one_window ? 0 : (int32_t)((int64_t)kw << wbits);
+      if (!one_window) set_own(own_c, p, pe, w0);
       if (!one_window && wt) {
-        // each lower neighbour's ids inside this window, from the table;
-        // thread i reads back only its own edge's range before the scan's
-        // barriers, so no barrier is needed here (nlow <= spc <= blockDim)
-        const int64_t kw = w0 >> wbits;
-        if (tid < nlow) {
-          if (pf_w != kw) {
-            const int32_t *t = wt + (int64_t)le_wrow[tid] * (nwin + 1) + kw;
-            pf0 = t[0];
-            pf1 = t[1];
-          }
-          le_b0[tid] = pf0;
-          le_b1[tid] = pf1;
+        // thread t alone writes and reads slot t's range before the barrier
+        if (tid < own_c.m) {
+          le[tid].b0 = low ? pf0 : 0;
+          le[tid].b1 = low ? pf1 : 0;
         }
       } else if (!one_window) {
         // each lower neighbour's ids inside this window, after the last one
-        if (tid == 0) sh->next = 0;
         __syncthreads();
         for (;;) {
           int32_t old = 0;
-          if (lane == 0) old = atomicAdd(&sh->next, 1);
+          if (lane == 0) old = atomicAdd(&sh->snext, 1);
           const int32_t i = __builtin_amdgcn_readlane(old, 0);
-          if (i >= nlow) break;
-          const int32_t du = uniform(le_du[i]);
-          const int32_t *row = (const int32_t *)(uintptr_t)uniform64(le_ids[i]);  // (no hubs here)
-          const int64_t b0 = wave_lower_bound(row, uniform(le_b1[i]), du, (int32_t)w0);
-          const int64_t b1 = wave_lower_bound(row, b0, du, (int32_t)min(w0 + W, (int64_t)INT32_MAX));
-          le_b0[i] = (int32_t)b0;
-          le_b1[i] = (int32_t)b1;
+          if (i >= own_c.m) break;
+          const int32_t len = uniform(le_lt[i]);
+          const int32_t *row = (const int32_t *)(uintptr_t)uniform64((int64_t)(uintptr_t)le[i].ids);  // (no hubs here)
+          const int64_t w1 = (int64_t)w0 + W;
+          const int64_t b0 = wave_lower_bound(row, uniform(le[i].b1), len, w0);
+          const int64_t b1 = wave_lower_bound(row, b0, len, (int32_t)min(w1, (int64_t)INT32_MAX));
+          le[i].b0 = (int32_t)b0;
+          le[i].b1 = (int32_t)b1;
         }
         __syncthreads();
+        if (tid == 0) sh->snext = 0;
       }
-      // Extra segments of long ranges, as an exclusive prefix over the edges.
-      int32_t ex = 0;
-      if (tid < nlow) {
-        const int32_t len = le_b1[tid] - (one_window ? 0 : le_b0[tid]);
-        ex = len > kItem ? (len - 1) / kItem : 0;
+      // Long and short ranges; empty ones need nothing.
+      const int32_t range = tid < own_c.m ? le[tid].b1 - le[tid].b0 : 0;
+      {
+        const uint64_t ml = __ballot(range > kShort), ms = __ballot(range > 0 && range <= kShort);
+        int32_t bl = 0, bs = 0;
+        if (lane == 0) {
+          if (ml) bl = atomicAdd(&sh->nlong, __popcll(ml));
+          if (ms) bs = atomicAdd(&sh->nshort, __popcll(ms));
+        }
+        bl = uniform(bl) + __popcll(ml & lanes_below());
+        bs = uniform(bs) + __popcll(ms & lanes_below());
+        if (range > kShort) le_ord[bl] = (uint16_t)tid;
+        else if (range > 0) le_ord[spc - 1 - bs] = (uint16_t)tid;
+        if (range > kItem) sh->nextra = 1;
       }
-      const int32_t xp = block_excl_scan(ex, sh->wsum, &sh->nextra);
-      if (tid < nlow) le_xp[tid] = xp;
-      if (tid == 0) sh->next = 0;
       __syncthreads();
-      const int32_t nitems = nlow + uniform(sh->nextra);
-      if (!one_window && wt && pe < dh && tid < nlow) {  // the next window's ranges, read during the items
-        const int64_t kwn = (int64_t)radj[oh + pe] >> wbits;
-        const int32_t *t = wt + (int64_t)le_wrow[tid] * (nwin + 1) + kwn;
-        pf0 = t[0];
-        pf1 = t[1];
-        pf_w = kwn;
+      if (one_window) advance();
+      const int nlong = uniform(sh->nlong), nshort = uniform(sh->nshort);
+      const bool bit0 = uniform((int32_t)bm[0]) & 1;
+      int32_t nitems = nlong;
+      if (uniform(sh->nextra)) {
+        // Extra segments of the long ranges, as an exclusive prefix over them.
+        int32_t ex = 0;
+        if (tid < nlong) {
+          const int32_t e = le_ord[tid];
+          ex = (le[e].b1 - le[e].b0 - 1) / kItem;
+        }
+        const int32_t xp = block_excl_scan(ex, sh->wsum, &sh->nextra);
+        if (tid < nlong) le_xp[tid] = xp;
+        __syncthreads();
+        nitems += uniform(sh->nextra);
+      }
+      const int32_t pn = pe;  // the next window's start
+      if (!one_window && pn < dh) {
+        window_at(own_c, own, pn, kw, pe);
+        load_own(own_c, pn, pe);
+        load_ranges(low, wrow);
       }
       // Work items are claimed from the LDS counter, one lane adding 1.
       // A claim is split in two: take() issues the LDS atomic, resolve()
       // turns its result into an item. Between the two the wavefront probes
       // its current item, so the atomic's round trip is not on its path.
-      auto take = [&]() -> int32_t {
-        int32_t old = 0;
-        if (lane == 0) old = atomicAdd(&sh->next, 1);
+      // (the address is made to look divergent, or the compiler would combine
+      // the lanes' adds first and wait for the result at once)
+      auto take_of = [&](int32_t *counter, int32_t count) -> int32_t {
+        int32_t zero = 0, old = 0;
+        asm("" : "+v"(zero));
+        if (lane == 0) old = atomicAdd(counter + zero, count);
         return old;
       };
+      auto take = [&]() { return take_of(&sh->next, 1); };
       auto resolve = [&](int32_t tok, int32_t &e, int32_t &lo, int32_t &hi, const int32_t *&ids) {
         const int32_t j = __builtin_amdgcn_readlane(tok, 0);
         if (j >= nitems) {
@@ -617,11 +681,11 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
           return;
         }
         int32_t ee = j, sg = 0;
-        if (j >= nlow) {
-          // the last edge with le_xp[e] <= jj (le_xp is non-decreasing and
+        if (j >= nlong) {
+          // the last long range e with le_xp[e] <= jj (le_xp is non-decreasing and
           // le_xp[0] = 0): a 64-way search, every lane sampling one edge
-          const int32_t jj = j - nlow;
-          int32_t a0 = 0, na = nlow;
+          const int32_t jj = j - nlong;
+          int32_t a0 = 0, na = nlong;
           while (na > 1) {
             const int32_t step = (na + kWave - 1) / kWave;
             const int32_t q = a0 + lane * step;
@@ -633,115 +697,259 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
           ee = a0;
           sg = 1 + jj - uniform(le_xp[a0]);
         }
+        ee = uniform((int32_t)le_ord[ee]);
         e = ee;
-        ids = (const int32_t *)(uintptr_t)uniform64(le_ids[ee]);
-        lo = (one_window ? 0 : uniform(le_b0[ee])) + sg * kItem;
-        hi = min(uniform(le_b1[ee]), lo + kItem);
-      };
-      // Probes the group of kWave * kUnroll ids that starts at position g0
-      // of an item of len ids. Per lane, acc counts the hits (low half) and
-      // the ids below h (high half): rows are sorted, so with one window the
-      // position of h in the lower neighbour's row is the sum of the latter
-      // over the row's items. Both halves stay below 2^16 (<= kItem per item).
-      auto probe_group = [&](const int32_t x[kUnroll], int32_t g0, int32_t len, uint32_t &acc) {
-        if (g0 + kWave * kUnroll <= len) {
-#pragma unroll
-          for (int k = 0; k < kUnroll; ++k) {
-            const uint32_t y = kOneWindow ? (uint32_t)x[k] : (uint32_t)(x[k] - (int32_t)w0);
-            acc += __builtin_amdgcn_ubfe(bitmap_word(y), y, 1) + (x[k] < hx ? 0x10000u : 0u);  // bit y & 31
-          }
-        } else {
-#pragma unroll
-          for (int k = 0; k < kUnroll; ++k) {
-            if (g0 + k * kWave >= len) break;  // uniform
-            const bool valid = g0 + k * kWave + lane < len;
-            const uint32_t vm = 0u - (uint32_t)valid;
-            // inside the item every id lies in the current window
-            const uint32_t y = kOneWindow ? (uint32_t)x[k] : (uint32_t)(x[k] - (int32_t)w0);
-            acc += (__builtin_amdgcn_ubfe(bitmap_word(y & vm), y, 1) + (x[k] < hx ? 0x10000u : 0u)) & vm;
-          }
-        }
+        const Range q = le[ee];
+        ids = (const int32_t *)(uintptr_t)uniform64((int64_t)(uintptr_t)q.ids);
+        lo = (one_window ? 0 : uniform(q.b0)) + sg * kItem;
+        hi = min(uniform(q.b1), lo + kItem);
       };
       // Whole items are requested one item ahead, and the loop body is
-      // unrolled twice so the two register sets swap roles without register
+      // unrolled so that the register sets swap roles without register
       // copies (a copy waits for its load). Every load of an item is
       // issued: a fixed count keeps the waits exact (the compiler waits for
       // an item's loads by counting the loads issued after them). The loads
       // are raw buffer loads over a resource of exactly the item's bytes, so
       // lanes past its end read 0 without touching memory (no line is
-      // fetched for them, and no bound check or mask is needed; the probe
-      // masks those lanes). Addressing is scalar base + lane offset +
-      // immediate: no vector instruction per load.
+      // fetched for them, and no bound check or mask is needed). Addressing
+      // is scalar base + lane offset + immediate: no vector instruction per
+      // load.
       auto fetch_item = [&](int32_t x[kItemLoads], const int32_t *ids, int32_t lo, int32_t len) {
         // resource word 3: DATA_FORMAT 32 (a valid format enables the buffer)
         const __amdgpu_buffer_rsrc_t r =
             __builtin_amdgcn_make_buffer_rsrc((void *)(ids + lo), (short)0, len * 4, 0x00020000);
+        // (opaque here, so that the lane offset and the immediates are not added
+        // up ahead of the loop, in a register each)
+        int32_t at = lane * 4;
+        asm("" : "+v"(at));
 #pragma unroll
-        for (int j = 0; j < kItemLoads; ++j) x[j] = __builtin_amdgcn_raw_buffer_load_b32(r, lane * 4 + j * kWave * 4, 0, 0);
+        for (int j = 0; j < kItemLoads; ++j) x[j] = __builtin_amdgcn_raw_buffer_load_b32(r, at + j * kWave * 4, 0, 0);
       };
+      // Hits of an item's len ids and, with one window, how many are below h:
+      // rows are sorted, so the position of h in the lower neighbour's row is
+      // the sum of the latter over the row's items. kUnroll LDS reads are in
+      // flight (left to itself the compiler waits for each in turn). Lanes
+      // past the end hold id 0 and are taken out of the sums afterwards.
       auto probe_item = [&](const int32_t x[kItemLoads], int32_t e, int32_t len) {
         uint32_t acc = 0;
+        int32_t below = 0, lanes = 0;
 #pragma unroll
         for (int c = 0; c < kGroups; ++c)
-          if (c == 0 || len > c * kWave * kUnroll) probe_group(x + c * kUnroll, c * kWave * kUnroll, len, acc);
-        const uint32_t t = (uint32_t)dpp_wave_sum((int32_t)acc);
+          if (c == 0 || len > c * kWave * kUnroll) {
+            uint32_t w[kUnroll];
+#pragma unroll
+            for (int k = 0; k < kUnroll; ++k) w[k] = bitmap_word((uint32_t)x[c * kUnroll + k], wmask);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < kUnroll; ++k) {
+              acc += __builtin_amdgcn_ubfe(w[k], (uint32_t)x[c * kUnroll + k], 1);
+              if (kOneWindow) below += __popcll(__ballot(x[c * kUnroll + k] < hx));
+            }
+            lanes += kWave * kUnroll;
+          }
+        const int32_t past = lanes - len;
+        const int32_t t = dpp_wave_sum((int32_t)acc) - (bit0 ? past : 0);
         // t is wave-uniform: lane 0 records it (no return value is used, so
         // no lane waits on another)
         if (lane == 0) {
-          atomicAdd(&le_cnt[e], (int32_t)(t & 0xffffu));
-          if (kOneWindow) atomicAdd(&le_lt[e], (int32_t)(t >> 16));
+          atomicAdd(&le_cnt[e], t);
+          if (kOneWindow) atomicAdd(&le_lt[e], below - (hx > 0 ? past : 0));
         }
       };
       // Items are claimed one step further ahead: the claim's atomic goes
       // out before a probe and is resolved after it, when the probe has
       // freed its registers, so no claim waits on loads in flight.
-      int32_t ea, loa, hia, eb, lob, hib;
-      const int32_t *ida, *idb;
-      int32_t xa[kItemLoads], xb[kItemLoads];
-      resolve(take(), ea, loa, hia, ida);
-      fetch_item(xa, ida, loa, hia - loa);
-      resolve(take(), eb, lob, hib, idb);
-      while (ea >= 0) {
-        fetch_item(xb, idb, lob, hib - lob);
-        const int32_t ta = take();
-        probe_item(xa, ea, hia - loa);
-        resolve(ta, ea, loa, hia, ida);
-        if (eb < 0) break;
-        fetch_item(xa, ida, loa, hia - loa);
-        const int32_t tb = take();
-        probe_item(xb, eb, hib - lob);
-        resolve(tb, eb, lob, hib, idb);
+      if (nitems) {
+        int32_t e[kDeep], lo[kDeep], hi[kDeep];
+        const int32_t *ids[kDeep];
+        int32_t x[kDeep][kItemLoads];
+#pragma unroll
+        for (int d = 0; d < kDeep; ++d) {
+          resolve(take(), e[d], lo[d], hi[d], ids[d]);
+          if (d + 1 < kDeep) fetch_item(x[d], ids[d], lo[d], hi[d] - lo[d]);
+        }
+        for (bool more = true; more;) {
+#pragma unroll
+          for (int d = 0; d < kDeep; ++d) {
+            const int f = (d + kDeep - 1) % kDeep;
+            if (e[d] < 0) {
+              more = false;
+              break;
+            }
+            fetch_item(x[f], ids[f], lo[f], hi[f] - lo[f]);
+            const int32_t t = take();
+            probe_item(x[d], e[d], hi[d] - lo[d]);
+            resolve(t, e[d], lo[d], hi[d], ids[d]);
+          }
+        }
+      }
+      // Short ranges: four per wavefront, one in each row of kRow lanes.
+      constexpr int kShortLoads = kShort / kRow;
+      const int rlane = lane & (kRow - 1), rowi = lane / kRow;
+      auto stake = [&]() -> int32_t {
+        return take_of(&sh->snext, kWave / kRow);
+      };
+      auto sresolve = [&](int32_t tok, int32_t &q, int32_t &e, int32_t &len, const int32_t *&ids) {
+        q = __builtin_amdgcn_readlane(tok, 0);
+        const bool ok = q + rowi < nshort;
+        e = le_ord[ok ? spc - 1 - q - rowi : spc - 1];
+        const Range r = le[e];
+        len = ok ? r.b1 - r.b0 : 0;
+        ids = r.ids + r.b0;
+      };
+      // (past its end a lane reads the range's last id again)
+      auto sfetch = [&](int32_t x[kShortLoads], const int32_t *ids, int32_t len) {
+#pragma unroll
+        for (int j = 0; j < kShortLoads; ++j) x[j] = ids[max(min(rlane + j * kRow, len - 1), 0)];
+      };
+      auto sprobe = [&](const int32_t x[kShortLoads], int32_t e, int32_t len) {
+        uint32_t acc = 0, w[kShortLoads];
+#pragma unroll
+        for (int j = 0; j < kShortLoads; ++j) w[j] = bitmap_word((uint32_t)x[j], wmask);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < kShortLoads; ++j) {
+          const uint32_t hit = __builtin_amdgcn_ubfe(w[j], (uint32_t)x[j], 1) + (kOneWindow && x[j] < hx ? 0x10000u : 0u);
+          acc += rlane + j * kRow < len ? hit : 0u;
+        }
+        int32_t v = (int32_t)acc;
+        v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+        if (rlane == kRow - 1 && len > 0) {
+          atomicAdd(&le_cnt[e], v & 0xffff);
+          if (kOneWindow) atomicAdd(&le_lt[e], (int32_t)((uint32_t)v >> 16));
+        }
+      };
+      if (nshort) {
+        int32_t q[kDeep], e[kDeep], len[kDeep];
+        const int32_t *ids[kDeep];
+        int32_t x[kDeep][kShortLoads];
+#pragma unroll
+        for (int d = 0; d < kDeep; ++d) {
+          sresolve(stake(), q[d], e[d], len[d], ids[d]);
+          if (d + 1 < kDeep) sfetch(x[d], ids[d], len[d]);
+        }
+        for (bool more = true; more;) {
+#pragma unroll
+          for (int d = 0; d < kDeep; ++d) {
+            const int f = (d + kDeep - 1) % kDeep;
+            if (q[d] >= nshort) {
+              more = false;
+              break;
+            }
+            sfetch(x[f], ids[f], len[f]);
+            const int32_t t = stake();
+            sprobe(x[d], e[d], len[d]);
+            sresolve(t, q[d], e[d], len[d], ids[d]);
+          }
+        }
       }
       __syncthreads();
-      for (int64_t i = p + tid; !one_window && i < pe; i += blockDim.x) {
-        const int32_t x = (int32_t)(radj[oh + i] - w0);
-        bm[x >> 5] = 0u;
+      if (tid == 0) {
+        sh->nlong = sh->nshort = sh->nextra = 0;
+        sh->next = sh->snext = 0;
       }
-      p = pe;
-      // the next window's bits may share words with the ones just cleared
-      if (!one_window) __syncthreads();
+      if (!one_window) {
+        wipe();
+        __syncthreads();
+      }
+      p = pn;
     }
-    __syncthreads();
-    for (int i = tid; i < nlow; i += blockDim.x) {
+    // Ahead: the next chunk's hub data, first window and owner ids, the ids
+    // of the chunk after.
+    const int32_t lt = le_lt[min(tid, spc - 1)], cnt = le_cnt[min(tid, spc - 1)];
+    const bool low_c = low;
+    const int32_t du_c = du;
+    const int64_t ou_c = ou;
+    const bool low_n = tid < nxt.m && is_lower(un, du_n, nxt.h, nxt.dh) && du_n <= skip;
+    const int32_t hr = hub.rows ? uniform(of_n) : -1;
+    hc = __builtin_amdgcn_readlane(of_n, 1);
+    const int32_t hx_c = hx;
+    hx = cid ? __builtin_amdgcn_readlane(of_n, 2) : nxt.h;
+    hubs = low_n && hr >= 0 && r_n >= 0;
+    wrow = un;
+    if (hubs) {
+      hq = hub.row_of[r_n];
+      hcnt = hub.D[(int64_t)max(r_n, hr) * hub.stride + min(r_n, hr)];
+      wrow = (int32_t)n + r_n;
+      if (one_window) {
+        hbits = hub.bits[hub.piece(r_n, hc >> 7)];
+        hpre = hub.pre[(int64_t)r_n * (hub.cols / 128) + (hc >> 7)];
+      }
+    }
+    if (!one_window && __ballot(low_n) && lane == 0) sh->some[(it + 1) & 1] = it + 1;
+    const int32_t u_c = u;
+    u = un;
+    own = own_n;
+    low = low_n;
+    du = du_n;
+    ou = ou_n;
+    if (one_window) {
+      if (nxt.m && nxt.h != held) {
+        load_own(nxt, 0, nxt.dh);
+        wipe();
+      }
+    } else if (nxt.m) {
+      window_at(nxt, own, 0, kw, pe);
+      load_own(nxt, 0, pe);
+      load_ranges(low, wrow);
+    }
+    const Owner two = owner_of(c2, d2);
+    if (two.m) {
+      un = adj[two.s0 + min(tid, two.m - 1)];
+      const int32_t *at = lane == 0 ? hub.row + two.h : lane == 1 ? hub.col + two.h : (const int32_t *)(cid + two.h);
+      if (lane < 2 ? hub.rows > 0 : lane == 2 && cid) of_n = *at;
+    }
+    // This chunk's edges.
+    if (low_c) {
       int64_t mir = -1;
       if (one_window) {
         // h sits after the ids below it (absent only from an asymmetric row)
-        const int32_t lt = le_lt[i];
-        const int64_t ou = (int64_t)(uint32_t)le_full[2 * i] | (int64_t)le_full[2 * i + 1] << 32;
-        if (lt < le_du[i] && adj[ou + lt] == h) mir = ou + lt;
+        if (lt < du_c && adj[ou_c + lt] == h) mir = ou_c + lt;
       } else {
-        // h may lie in a window that holds no id of N(h): locate it directly
-        const int64_t ou = off[le_lt[i]];
-        int64_t lo = 0, hi = le_du[i];
-        while (lo < hi) {
-          const int64_t mid = (lo + hi) >> 1;
-          if (adj[ou + mid] < h) lo = mid + 1;
-          else hi = mid;
+        // h may lie in a window that holds no id of N(h): locate it directly,
+        // with the table among the ids of its window and by interpolation in
+        // every other step (rows are long and ids spread: four dependent
+        // reads instead of eleven; 37 of the 345 thousand cycles of a chunk
+        // of R-MAT-23 were spent here)
+        int64_t a = 0, b = du_c, va = 0, vb = 0;
+        if (wt) {
+          const int32_t *t = wt + (int64_t)u_c * (nwin + 1) + (hx_c >> wbits);
+          a = t[0];
+          b = t[1];
+          va = (int64_t)(hx_c >> wbits) << wbits;
+          vb = va + W;
         }
-        mir = (lo < le_du[i] && adj[ou + lo] == h) ? ou + lo : -1;
+        for (bool guess = wt != nullptr; a < b; guess = !guess && wt) {
+          int64_t mid = (a + b) >> 1;
+          if (guess) mid = min(b - 1, a + (int64_t)((float)(hx_c - va) * (float)(b - a) / (float)(vb - va)));
+          const int32_t v = radj[ou_c + mid];
+          if (v == hx_c) {
+            mir = ou_c + mid;
+            break;
+          }
+          if (v < hx_c) {
+            a = mid + 1;
+            va = v;
+          } else {
+            b = mid;
+            vb = v;
+          }
+        }
       }
-      write_edge(kind, s0 + le_e[i], mir, le_cnt[i], le_du[i], dh, sims, counts);
+      // (nothing read for the chunks to come is waited for behind the stores)
+      asm volatile("" ::"v"(un), "v"(of_n), "v"(hcnt), "v"(hq.off), "v"(hq.len));
+      if (one_window) asm volatile("" ::"v"(hpre), "v"(hbits.x), "v"(hbits.y), "v"(hbits.z), "v"(hbits.w));
+      else asm volatile("" ::"v"(pf0), "v"(pf1));
+#pragma unroll
+      for (int j = 0; j < kOwn; ++j) asm volatile("" ::"v"(ox[j]));
+      write_edge(kind, own_c.s0 + tid, mir, cnt, du_c, dh, sims, counts);
     }
+    if (tid == 0) sh->claim[(it + 1) & 1] = run_base + run_pos++;
+    cur = nxt;
+    nxt = two;
   }
 }
 
@@ -836,7 +1044,7 @@ __global__ __launch_bounds__(256) void k_rename(const int32_t *adj, int64_t nnz,
 constexpr size_t kMaxWindowTable = (size_t)4 << 30;
 
 static size_t big_lds_bytes(int wbits, int spc) {
-  return ((size_t)1 << wbits) / 8 + (size_t)spc * (8 + 4 * 8) + 4 + sizeof(BigShared);
+  return ((size_t)1 << wbits) / 8 + (size_t)spc * (16 + 4 * 3 + 2) + sizeof(BigShared);
 }
 
 // The id window width of the large-owner kernel: cfg.wbits, no wider than
@@ -861,12 +1069,12 @@ scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, c
   PlanCounts *pc = (PlanCounts *)counts;
   SCAN_TRY(arena.alloc(&p.small_list, n));
   SCAN_TRY(arena.alloc(&p.heavy_list, n));
-  SCAN_TRY(arena.alloc(&big_list, nnz / cfg.spc + n + 1));
+  SCAN_TRY(arena.alloc(&big_list, nnz / cfg.spc + std::min(n, nnz / cfg.small_max) + 1));
   p.big_list = big_list;
   p.counts = counts;
   p.host = host;
   k_plan<<<grid_for(n, kPlanThreads * kPlanPer, 2048), kPlanThreads, 0, s>>>(
-      deg, n, cfg.small_max, cfg.spc, p.small_list, p.heavy_list, big_list, pc, words, (int32_t *)host);
+      deg, off, n, cfg.small_max, cfg.spc, p.small_list, p.heavy_list, big_list, pc, words, (int32_t *)host);
   SCAN_HIP_TRY(hipEventRecord(ready, s));
   return SCAN_OK;
 }

@@ -94,3 +94,37 @@ def test_hub_product(core, rim, tune):
     for kind in (scan.COSINE, scan.JACCARD):
         ix = scan.scan_build_index(*device_csr(g), kind, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
         assert_index_equal(ix, oracle.build_index(g, kind, threads=8), g)
+
+
+# lengths around a short range (128 ids), an item (512 with several windows,
+# 1024 with one) and two of them, among large owners' lower neighbours; one
+# window, a few, and more than a wavefront's lanes; a slot per chunk, few, a
+# thread per slot
+@pytest.mark.parametrize("tune", [{"small_max": 2100, "spc": 1024}, {"small_max": 2100, "spc": 1},
+                                  {"small_max": 2100, "spc": 7, "wbits": 16}, {"small_max": 2100, "wbits": 10},
+                                  {"small_max": 2100, "wbits": 12, "spc": 1024},
+                                  {"small_max": 2100, "wbits": 13, "flags": scan.SCAN_TUNE_SEARCH_WINDOWS}])
+@pytest.mark.parametrize("first", [True, False])
+def test_range_lengths(tune, first):
+    from gpu_util import device_csr
+
+    n, owners = 70000, 3
+    rng = np.random.default_rng(5)
+    place = rng.permutation(n)
+    if first:  # the owners have the ids 0 and n - 1 and one between as neighbours and ids
+        place[[np.flatnonzero(place == 0)[0], 0]] = place[[0, np.flatnonzero(place == 0)[0]]]
+        place[[np.flatnonzero(place == n - 1)[0], 1]] = place[[1, np.flatnonzero(place == n - 1)[0]]]
+    edges = [np.stack([np.full(6000, o), rng.choice(np.arange(100, n), 6000, replace=False)], 1) for o in range(owners)]
+    edges.append(np.array([(0, 1), (0, 2), (1, 2)]))
+    pool = np.concatenate([e[:, 1] for e in edges[:owners]])
+    at = owners
+    for length in (2, 3, 15, 16, 17, 63, 64, 65, 127, 128, 129, 130, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2049):
+        for seen in range(2):
+            mates = rng.choice(pool if seen else np.arange(100, n), 4 * length + 40)
+            mates = np.unique(mates[mates != at])[: length - owners] if length > owners else mates[:0]
+            edges.append(np.stack([np.full(len(mates), at), mates], 1))
+            edges.append(np.stack([np.full(owners, at), np.arange(owners)], 1)[:length])
+            at += 1
+    g = graphgen.from_edges(n, place[np.concatenate(edges)].astype(np.int32))
+    ix = scan.scan_build_index(*device_csr(g), scan.COSINE, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
+    assert_index_equal(ix, oracle.build_index(g, scan.COSINE, threads=8), g)
