@@ -67,6 +67,10 @@ struct PlanCounts {
   int32_t bins[kDegBins];  // vertices by degree, from 128 up
 };
 static_assert(sizeof(PlanCounts) == kPlanCountBytes, "the maximum degrees follow the counts");
+struct SmallOwner {
+  int32_t h, dh;  // vertex, degree
+  int64_t oh;     // first slot of its row
+};
 struct BigChunk {
   int32_t h;
   int32_t k;    // slots [k*spc, (k+1)*spc) of row h
@@ -77,7 +81,7 @@ struct BigChunk {
 struct IntersectPlan {
   int64_t n = 0, nnz = 0;
   bool one_graph = false;  // set by the caller
-  int32_t *small_list = nullptr, *heavy_list = nullptr;
+  SmallOwner *small_list = nullptr, *heavy_list = nullptr;
   void *big_list = nullptr, *counts = nullptr;  // device chunk list and counts
   const void *host = nullptr;                   // the host's copy of the counts
   // helper streams already ordered after the plan (set by the caller), used

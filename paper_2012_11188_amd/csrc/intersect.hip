@@ -113,7 +113,7 @@ constexpr int kPlanPer = 8;  // consecutive vertices per thread and tile
 // staging pass). The block scans its counts, reserves list space with one
 // global atomic per list, and writes the entries in vertex order.
 __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, const int64_t *off, int64_t n, int small_max,
-                                                       int spc, int32_t *small_list, int32_t *heavy_list,
+                                                       int spc, SmallOwner *small_list, SmallOwner *heavy_list,
                                                        BigChunk *big_list, PlanCounts *pc, int32_t words,
                                                        int32_t *host) {
   __shared__ int32_t last;
@@ -154,8 +154,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, const
     int32_t ps = base_small + os, ph = base_heavy + oh, pb = base_big + ob;
 #pragma unroll
     for (int k = 0; k < kPlanPer; ++k) {
-      if (code[k] == -1) small_list[ps++] = (int32_t)(v0 + k);
-      if (code[k] == -2) heavy_list[ph++] = (int32_t)(v0 + k);
+      if (code[k] == -1) small_list[ps++] = SmallOwner{(int32_t)(v0 + k), deg[v0 + k], off[v0 + k]};
+      if (code[k] == -2) heavy_list[ph++] = SmallOwner{(int32_t)(v0 + k), deg[v0 + k], off[v0 + k]};
       for (int32_t j = 0; j < code[k]; ++j) big_list[pb++] = BigChunk{(int32_t)(v0 + k), j, deg[v0 + k], 0, off[v0 + k]};
     }
   }
@@ -186,155 +186,186 @@ __device__ __forceinline__ void write_edge(int kind, int64_t s, int64_t mirror, 
 // ---------------------------------------------------------------------------
 // Small owners (degree <= small_max): one workgroup per vertex, of one
 // wavefront up to degree kLightDeg and of kSmallWaves wavefronts above. The
-// vertex's lower neighbours are compacted into LDS; if there are any, its row
-// goes into an LDS hash table (open addressing, load <= 1/2) and the lower
-// neighbours' rows are streamed through it: with one wavefront, each group of
-// kLightGroup lanes takes one lower neighbour (several rows per step, since
-// these rows are short); with several, the wavefronts take them in turn, 64
-// ids at a time.
+// vertex's row goes into an LDS hash table of buckets of four ids, its lower
+// neighbours into an LDS list, and the lower neighbours' rows are streamed
+// through the table: groups of lanes take one lower neighbour each (several
+// rows per step, since these rows are short), kSmallLoads ids per lane and
+// step, with the next step's ids in flight. Bound by latency: a vertex is a
+// chain of four dependent reads (list entry, ids, their offsets, rows) and a
+// lookup should be one LDS read, so a bucket is read whole and all of a lane's
+// lookups are issued before the first is waited for. (One slot per read, a
+// step's lookups one after the other, six dependent reads a vertex: builds of
+// 12 SBM graphs 6.74 ms, now 6.07; R-MAT of 60,000 vertices 546 and 507 us;
+// R-MAT-20, beside the large owners, 6.60 and 6.41 ms. Two loads of 32 lanes
+// instead of four of 16 for the light rows: 6.49 ms for the SBM graphs.)
 
 constexpr int kSmallWaves = 4;
-#ifndef SCAN_LIGHT_GROUP
-#define SCAN_LIGHT_GROUP 16
-#endif
-constexpr int kLightGroup = SCAN_LIGHT_GROUP;  // lanes per lower neighbour in the one-wavefront kernel
-#ifndef SCAN_HEAVY_GROUP
-#define SCAN_HEAVY_GROUP 32
-#endif
-constexpr int kHeavyGroup = SCAN_HEAVY_GROUP;  // and in the kSmallWaves kernel
+constexpr int kLightGroup = 16;  // lanes per lower neighbour in the one-wavefront kernel
+constexpr int kHeavyGroup = 32;  // and in the kSmallWaves kernel
+constexpr int kSmallLoads = 4;
 constexpr int32_t kEmpty = -1;
 
-__device__ __forceinline__ uint32_t hash_slot(int32_t x, int tbits) {
-  return ((uint32_t)x * 2654435761u) >> (32 - tbits);  // Fibonacci hashing
+__device__ __forceinline__ uint32_t hash_bucket(int32_t x, int bbits) {
+  return ((uint32_t)x * 2654435761u) >> (32 - bbits);  // Fibonacci hashing
 }
 
-// Hash table slots per row entry (at least), the kernels' `spread`: the load
-// factor is at most 1 / spread. A wavefront's probe loop runs as long as its
-// longest chain, so sparse tables pay, up to the LDS they take from other
-// workgroups. Builds of the 256-graph SBM batch (light owners, no bitmap
-// kernel beside them) took 59.8, 53.0 and 50.8 ms with spreads of 2, 4 and 8;
-// R-MAT-23 (heavy owners) 455.4, 452.6 and 454.9 ms. R-MAT-20, whose light
-// owners run beside the bitmap kernel, took 7.06 ms per step with a light
-// spread of 4 and 7.11 ms with 8. So the heavy kernel takes 4 (which also
-// keeps small_max = 4096 within the LDS) and the light one 4 beside the
-// bitmap kernel, else 8.
-constexpr int kSpreadHeavy = 4, kSpreadLight = 4, kSpreadLightAlone = 8;
+// Hash table slots per row entry (at least), the kernels' `spread`: a full
+// bucket sends a lookup on to the next one (with a quarter of the slots taken
+// one bucket in fifty is full, with an eighth one in five hundred), so sparse
+// tables pay as long as the LDS holds several workgroups (builds with 4 and 8:
+// R-MAT of 60,000 vertices 518 and 507 us, R-MAT-20 6.41 and 6.41 ms, 12 SBM
+// graphs 6.10 and 6.08 ms); small_max = 4096 fits with 4.
+constexpr int kSpread = 8, kSpreadLarge = 4;
+constexpr size_t kSmallLdsMax = 32768;
+
+struct LowRow {
+  int64_t ou;     // row offset of a lower neighbour
+  int32_t du, e;  // its degree, its slot in the vertex's row
+};
 
 // LDS bytes of k_small_owner for a given small_max and spread.
 static inline size_t small_lds_bytes(int small_max, int spread) {
   int tb = 6;
   while ((1 << tb) < spread * small_max) ++tb;
-  return (size_t)small_max * 20 + ((size_t)4 << tb);
+  return (size_t)small_max * sizeof(LowRow) + ((size_t)4 << tb) + 16;
 }
 
-// One block per list entry, or (claim != nullptr) persistent blocks that
-// claim entries from a counter. The count is read from device memory.
+// One block per list entry.
 template <int WAVES>
-__global__ __launch_bounds__(WAVES * kWave) void k_small_owner(
-    const int32_t *list, const int32_t *countp, int32_t *claim, int small_max, int spread, const int64_t *off,
-    const int32_t *deg, const int32_t *adj, int kind, double *sims, int32_t *counts, int32_t skip) {
-  const int32_t count = *countp;
-  __shared__ int32_t s_idx;
+__global__ __launch_bounds__(WAVES * kWave) void k_small_owner(const SmallOwner *list, int small_max, int spread,
+                                                               const int64_t *off, const int32_t *adj, int kind,
+                                                               double *sims, int32_t *counts, int32_t skip) {
   extern __shared__ unsigned char smem[];
-  int64_t *lou = (int64_t *)smem;               // [small_max] row offset of the j-th lower neighbour
-  int32_t *row = (int32_t *)(lou + small_max);  // [small_max] the vertex's row
-  int32_t *ldu = row + small_max;               // [small_max] degree of the j-th lower neighbour
-  int32_t *le = ldu + small_max;                // [small_max] its slot in the vertex's row
-  int32_t *tab = le + small_max;                // [2^tbits] hash table of the row
-  __shared__ int32_t s_nlow;
+  int32_t &s_nlow = *(int32_t *)smem;
+  LowRow *lows = (LowRow *)(smem + 16);        // [small_max] the lower neighbours
+  int4 *buckets = (int4 *)(lows + small_max);  // hash table of the row
+  int32_t *tab = (int32_t *)buckets;
   const int lane = lane_id(), wave = threadIdx.x / kWave;
-  for (int64_t idx0 = blockIdx.x;; idx0 += gridDim.x) {
-    int64_t idx = idx0;
-    if (WAVES > 1 && claim) {
-      __syncthreads();
-      if (threadIdx.x == 0) s_idx = atomicAdd(claim, 1);
-      __syncthreads();
-      idx = uniform(s_idx);
+  const SmallOwner o = list[blockIdx.x];
+  const int32_t h = o.h, dh = o.dh;
+  const int64_t oh = o.oh;
+  int tbits = 6;
+  while ((1 << tbits) < spread * dh) ++tbits;
+  const int bbits = tbits - 2;
+  const uint32_t bmask = (1u << bbits) - 1;
+  for (int32_t i = threadIdx.x; i < 1 << bbits; i += WAVES * kWave) buckets[i] = int4{kEmpty, kEmpty, kEmpty, kEmpty};
+  if (threadIdx.x == 0) s_nlow = 0;
+  __syncthreads();
+  for (int32_t i0 = 0; i0 < dh; i0 += WAVES * kWave) {
+    const int32_t i = i0 + (int32_t)threadIdx.x;
+    const int32_t u = adj[oh + min(i, dh - 1)];
+    const int64_t ou = off[u];
+    const int32_t d = (int32_t)(off[u + 1] - ou);
+    if (i < dh) {
+      // (a bucket fills from its first slot: one with an empty last slot ends a lookup)
+      uint32_t sl = hash_bucket(u, bbits) * 4;
+      while (atomicCAS(&tab[sl], kEmpty, u) != kEmpty) sl = (sl + 1) & (bmask * 4 + 3);
     }
-    if (idx >= count) break;  // uniform across the block
-    const int32_t h = list[idx];
-    const int32_t dh = deg[h];
-    const int64_t oh = off[h];
-    int tbits = 6;
-    while ((1 << tbits) < spread * dh) ++tbits;
-    const int32_t tsize = 1 << tbits;
-    __syncthreads();
-    if (threadIdx.x == 0) s_nlow = 0;
-    __syncthreads();
-    for (int32_t i0 = 0; i0 < dh; i0 += blockDim.x) {
-      const int32_t i = i0 + (int32_t)threadIdx.x;
-      int32_t u = 0, d = 0;
-      if (i < dh) {
-        u = adj[oh + i];
-        d = deg[u];
-        row[i] = u;
-      }
-      const bool low = i < dh && is_lower(u, d, h, dh) && d <= skip;
-      const uint64_t m = __ballot(low);
-      int32_t base = 0;
-      if (m) {
-        const int leader = __ffsll((unsigned long long)m) - 1;
-        int32_t old = 0;
-        if (lane == leader) old = atomicAdd(&s_nlow, __popcll(m));
-        base = __builtin_amdgcn_readlane(old, leader);
-      }
-      if (low) {
-        const int32_t j = base + __popcll(m & lanes_below());
-        le[j] = i;
-        ldu[j] = d;
-        lou[j] = off[u];
-      }
+    const bool low = i < dh && is_lower(u, d, h, dh) && d <= skip;
+    const uint64_t m = __ballot(low);
+    int32_t base = 0;
+    if (m) {
+      const int leader = __ffsll((unsigned long long)m) - 1;
+      int32_t old = 0;
+      if (lane == leader) old = atomicAdd(&s_nlow, __popcll(m));
+      base = __builtin_amdgcn_readlane(old, leader);
     }
-    __syncthreads();
-    const int32_t nlow = uniform(s_nlow);
-    if (nlow == 0) continue;  // owns no edge (uniform across the block)
-    for (int32_t i = threadIdx.x; i < tsize; i += blockDim.x) tab[i] = kEmpty;
-    __syncthreads();
-    for (int32_t i = threadIdx.x; i < dh; i += blockDim.x) {
-      const int32_t x = row[i];
-      uint32_t sl = hash_slot(x, tbits);
-      while (atomicCAS(&tab[sl], kEmpty, x) != kEmpty) sl = (sl + 1) & (uint32_t)(tsize - 1);
-    }
-    __syncthreads();
-    // Each group of G lanes takes one lower neighbour (NG per wavefront, the
-    // wavefronts take successive sets) and streams its row G ids per step; a
-    // missing row has length 0. Loads are clamped into the row.
-    constexpr int G = WAVES == 1 ? kLightGroup : kHeavyGroup, NG = kWave / G;
-    constexpr uint64_t gmask = G == 64 ? ~0ull : (1ull << G) - 1;
-    const int grp = lane / G, gl = lane % G;
-    for (int32_t j0 = wave * NG; j0 < nlow; j0 += WAVES * NG) {
-      const int32_t j = j0 + grp;
-      const bool has = j < nlow;
-      const int32_t du = has ? ldu[j] : 0;
-      const int64_t ou = has ? lou[j] : 0;
-      int32_t dmaxg = 0;  // the longest of the NG rows
+    if (low) lows[base + __popcll(m & lanes_below())] = LowRow{ou, d, i};
+  }
+  __syncthreads();
+  const int32_t nlow = uniform(s_nlow);
+  // Each group of G lanes takes one lower neighbour (NG per wavefront, the
+  // wavefronts take successive sets); a missing row has length 0. Reads past a
+  // row's end read its last id again.
+  constexpr int G = WAVES == 1 ? kLightGroup : kHeavyGroup, NG = kWave / G, L = kSmallLoads;
+  const int grp = lane / G, gl = lane % G;
+  struct Rows {  // a step: the rows from j, ids from k
+    int32_t j, k, longest;
+    LowRow q;
+  };
+  auto rows_at = [&](int32_t j) {
+    Rows r{j, 0, 0, lows[min(j + grp, nlow - 1)]};
+    if (j + grp >= nlow) r.q.du = 0;
 #pragma unroll
-      for (int g = 0; g < NG; ++g)
-        if (j0 + g < nlow) dmaxg = max(dmaxg, uniform(ldu[j0 + g]));
-      int32_t t = 0;
-      int64_t mpos = -1;
-      for (int32_t k0 = 0; k0 < dmaxg; k0 += G) {
-        const int32_t i = k0 + gl;
-        const bool valid = i < du;
-        const int32_t x = adj[ou + (valid ? i : (du > 0 ? du - 1 : 0))];
-        uint32_t sl = hash_slot(x, tbits);
-        bool hit = false;
-        for (int32_t probe = 0; probe < tsize; ++probe) {  // ends at x or at an empty slot
-          const int32_t v = tab[sl];
-          if (v == x) {
-            hit = true;
-            break;
-          }
-          if (v == kEmpty) break;
-          sl = (sl + 1) & (uint32_t)(tsize - 1);
-        }
-        const uint64_t m = __ballot(valid && hit), me = __ballot(valid && x == h);
-        t += __popcll((m >> (grp * G)) & gmask);
-        const uint64_t mine = (me >> (grp * G)) & gmask;
-        if (mine) mpos = ou + k0 + (__ffsll((unsigned long long)mine) - 1);
-      }
-      if (has && gl == 0) write_edge(kind, oh + le[j], mpos, t, du, dh, sims, counts);
+    for (int g = 0; g < NG; ++g) r.longest = max(r.longest, __builtin_amdgcn_readlane(r.q.du, g * G));
+    return r;
+  };
+  auto after = [&](const Rows &r) {
+    Rows n = r;
+    n.k += G * L;
+    if (n.k >= r.longest) {
+      n.j += WAVES * NG;
+      n.k = 0;
+      if (n.j < nlow) n = rows_at(n.j);
     }
+    return n;
+  };
+  auto fetch = [&](int32_t x[L], const Rows &r) {
+#pragma unroll
+    for (int j = 0; j < L; ++j) x[j] = adj[r.q.ou + max(min(r.k + gl + j * G, r.q.du - 1), 0)];
+  };
+  int32_t acc = 0, pos = -1;  // of this lane: common neighbours, the position of h
+  auto probe = [&](const int32_t x[L], const Rows &r) {
+    int4 v[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) v[j] = buckets[hash_bucket(x[j], bbits)];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      const int32_t i = r.k + gl + j * G;
+      const bool valid = i < r.q.du;
+      bool hit = v[j].x == x[j] || v[j].y == x[j] || v[j].z == x[j] || v[j].w == x[j];
+      if (__ballot(valid && !hit && v[j].w != kEmpty)) {
+        uint32_t b = hash_bucket(x[j], bbits);
+        int4 t = v[j];
+        while (!hit && t.w != kEmpty) {  // ends at x or at a bucket with room
+          b = (b + 1) & bmask;
+          t = buckets[b];
+          hit = t.x == x[j] || t.y == x[j] || t.z == x[j] || t.w == x[j];
+        }
+      }
+      acc += valid && hit;
+      if (valid && x[j] == h) pos = i;
+    }
+  };
+  auto finish = [&](const Rows &r) {
+    int32_t t = acc;
+    t += __builtin_amdgcn_update_dpp(0, t, 0x111, 0xf, 0xf, true);  // row_shr:1, 2, 4, 8
+    t += __builtin_amdgcn_update_dpp(0, t, 0x112, 0xf, 0xf, true);
+    t += __builtin_amdgcn_update_dpp(0, t, 0x114, 0xf, 0xf, true);
+    t += __builtin_amdgcn_update_dpp(0, t, 0x118, 0xf, 0xf, true);
+    if (G == 32) t += __builtin_amdgcn_update_dpp(0, t, 0x142, 0xa, 0xf, true);  // row_bcast:15 into rows 1, 3
+    t = __shfl(t, lane | (G - 1), kWave);
+    if (r.q.du > 0 && (gl == 0 || pos >= 0)) {
+      const int64_t c = (int64_t)t + 2;
+      const double x = similarity(kind, c, (int64_t)r.q.du + 1, (int64_t)dh + 1);
+      if (gl == 0) {
+        sims[oh + r.q.e] = x;
+        if (counts) counts[oh + r.q.e] = (int32_t)c;
+      }
+      if (pos >= 0) {
+        sims[r.q.ou + pos] = x;
+        if (counts) counts[r.q.ou + pos] = (int32_t)c;
+      }
+    }
+    acc = 0;
+    pos = -1;
+  };
+  if (wave * NG >= nlow) return;
+  int32_t xa[L], xb[L];
+  Rows a = rows_at(wave * NG), b;
+  fetch(xa, a);
+  for (;;) {
+    b = after(a);
+    fetch(xb, b);
+    probe(xa, a);
+    if (b.j != a.j) finish(a);
+    if (b.j >= nlow) break;
+    a = after(b);
+    fetch(xa, a);
+    probe(xb, b);
+    if (a.j != b.j) finish(b);
+    if (a.j >= nlow) break;
   }
 }
 
@@ -1091,7 +1122,6 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
   if (!plan || plan->n != n || plan->nnz != nnz || !plan->host)
     return fail(SCAN_EINVAL, "plan made for another graph");
-  const int32_t *small_list = plan->small_list, *heavy_list = plan->heavy_list;
   const BigChunk *big_list = (const BigChunk *)plan->big_list;
   PlanCounts *pc = (PlanCounts *)plan->counts;
   // The host reads the work counts to size the grids: one block per vertex
@@ -1210,8 +1240,8 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   SCAN_TRY(mark(stats ? stats->ev_small_begin : nullptr, ss));
   if (h.small || h.heavy) {
     const int cap = std::min<int>(cfg.small_max, kLightDeg);  // light rows: LDS sized for them
-    const int spread1 = h.big ? kSpreadLight : kSpreadLightAlone;
-    const size_t lds = small_lds_bytes(cfg.small_max, kSpreadHeavy), lds1 = small_lds_bytes(cap, spread1);
+    const int spread = small_lds_bytes(cfg.small_max, kSpread) > kSmallLdsMax ? kSpreadLarge : kSpread;
+    const size_t lds = small_lds_bytes(cfg.small_max, spread), lds1 = small_lds_bytes(cap, kSpread);
     if (lds > (size_t)lds_max || lds1 > (size_t)lds_max) return fail(SCAN_EINVAL, "small_max too large for LDS");
     if (lds > 65536)
       SCAN_HIP_TRY(hipFuncSetAttribute((const void *)k_small_owner<kSmallWaves>,
@@ -1221,11 +1251,10 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1));
     if (h.heavy)  // the longer rows first
       k_small_owner<kSmallWaves><<<h.heavy, kSmallWaves * kWave, lds, sh>>>(
-          heavy_list, &pc->heavy, nullptr, cfg.small_max, kSpreadHeavy, off, deg, adj, kind, sims, counts,
-          cfg.skip_deg);
+          plan->heavy_list, cfg.small_max, spread, off, adj, kind, sims, counts, cfg.skip_deg);
     if (h.small)
-      k_small_owner<1><<<h.small, kWave, lds1, sl>>>(small_list, &pc->small, nullptr, cap, spread1, off, deg, adj,
-                                                     kind, sims, counts, cfg.skip_deg);
+      k_small_owner<1><<<h.small, kWave, lds1, sl>>>(plan->small_list, cap, kSpread, off, adj, kind, sims, counts,
+                                                     cfg.skip_deg);
     SCAN_HIP_TRY(hipGetLastError());
   }
   if (sl != ss) SCAN_TRY(stream_wait(ss, sl));  // the end event covers both

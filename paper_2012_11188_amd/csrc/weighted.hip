@@ -198,7 +198,7 @@ static inline size_t w_small_lds(int cap) {
 }
 
 template <int WAVES>
-__global__ __launch_bounds__(WAVES * kWave) void k_w_small(const int32_t *list, int cap, const int64_t *off,
+__global__ __launch_bounds__(WAVES * kWave) void k_w_small(const SmallOwner *list, int cap, const int64_t *off,
                                                            const int32_t *deg, const int32_t *adj, const double *w,
                                                            const double *S, double *sims, int32_t skip) {
   extern __shared__ unsigned char smem[];
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_w_small(const int32_t *list, 
   uint16_t *tpos = le + cap;                // [2^tbits] their positions
   __shared__ int32_t s_nlow;
   const int lane = lane_id(), wave = threadIdx.x / kWave, row = lane / 16, gl = lane % 16;
-  const int32_t h = list[blockIdx.x];
+  const int32_t h = list[blockIdx.x].h;
   const int32_t dh = deg[h];
   const int64_t oh = off[h];
   int tbits = 6;

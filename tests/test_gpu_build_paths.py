@@ -128,3 +128,25 @@ def test_range_lengths(tune, first):
     g = graphgen.from_edges(n, place[np.concatenate(edges)].astype(np.int32))
     ix = scan.scan_build_index(*device_csr(g), scan.COSINE, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
     assert_index_equal(ix, oracle.build_index(g, scan.COSINE, threads=8), g)
+
+
+# rows around a step of the light kernel's groups (64 ids) and of the heavy
+# one's (128), the largest of each, and ids that fill whole hash buckets (the
+# bucket is the top bits of id * 2654435761): more than one bucket holds
+@pytest.mark.parametrize("tune", [None, {"small_max": 4096}, {"small_max": 1}, {"small_max": 700, "wbits": 10}])
+@pytest.mark.parametrize("degree", [3, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257])
+def test_small_owner_rows(degree, tune):
+    from gpu_util import device_csr
+
+    n = 1 << 17
+    ids = np.arange(n, dtype=np.uint64)
+    top = ((ids * 2654435761) & 0xFFFFFFFF) >> 24
+    same = np.flatnonzero((top == 7) | (top == 8))[:degree]  # close in the table
+    rng = np.random.default_rng(degree)
+    rest = rng.choice(np.setdiff1d(np.arange(n), same), degree + 40, replace=False)
+    edges = [(a, b) for i, a in enumerate(same[:40]) for b in same[i + 1:]]  # a clique and its further members
+    edges += [(a, b) for a, b in zip(same, rest)]
+    edges += [(int(rest[0]), int(b)) for b in rest[1:degree]] + [(int(rest[1]), int(b)) for b in rest[5:degree]]
+    g = graphgen.from_edges(n, np.array(edges, np.int64).astype(np.int32))
+    ix = scan.scan_build_index(*device_csr(g), scan.COSINE, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
+    assert_index_equal(ix, oracle.build_index(g, scan.COSINE, threads=8), g)
