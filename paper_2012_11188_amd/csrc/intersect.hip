@@ -190,23 +190,27 @@ __device__ __forceinline__ void write_edge(int kind, int64_t s, int64_t mirror, 
 // neighbours into an LDS list, and the lower neighbours' rows are streamed
 // through the table: groups of lanes take one lower neighbour each (several
 // rows per step, since these rows are short), kSmallLoads ids per lane and
-// step, with the next step's ids in flight. Bound by latency: a vertex is a
-// chain of four dependent reads (list entry, ids, their offsets, rows) and a
-// lookup should be one LDS read, so a bucket is read whole and all of a lane's
-// lookups are issued before the first is waited for. (One slot per read, a
-// step's lookups one after the other, six dependent reads a vertex: builds of
-// 12 SBM graphs 6.74 ms, now 6.07; R-MAT of 60,000 vertices 546 and 507 us;
-// R-MAT-20, beside the large owners, 6.60 and 6.41 ms. Two loads of 32 lanes
-// instead of four of 16 for the light rows: 6.49 ms for the SBM graphs.)
+// step, with the next step's ids in flight. Bound by the vector units (30
+// instructions per 64 lookups) and by latency: a vertex is a chain of four
+// dependent reads (list entry, ids, their offsets, rows) and a lookup should
+// be one LDS read, so a bucket is read whole and several lookups are issued
+// before the first is waited for. (One slot per read, a step's lookups one
+// after the other, six dependent reads a vertex: builds of 12 SBM graphs 6.74
+// ms, now 5.51; R-MAT of 60,000 vertices 546 and 500 us; R-MAT-20, beside the
+// large owners, 6.60 and 6.32 ms. Groups of 16 and 32 lanes instead of 8 and
+// 16, 5.79 ms for the SBM graphs; four lookups in flight, 5.65; a full 32-bit
+// product in the hash, 5.54.)
 
 constexpr int kSmallWaves = 4;
-constexpr int kLightGroup = 16;  // lanes per lower neighbour in the one-wavefront kernel
-constexpr int kHeavyGroup = 32;  // and in the kSmallWaves kernel
-constexpr int kSmallLoads = 4;
+constexpr int kLightGroup = 8;   // lanes per lower neighbour in the one-wavefront kernel
+constexpr int kHeavyGroup = 16;  // and in the kSmallWaves kernel
+constexpr int kSmallLoads = 4;   // ids in flight per lane
+constexpr int kSmallLookups = 2;  // LDS reads in flight per lane
 constexpr int32_t kEmpty = -1;
 
 __device__ __forceinline__ uint32_t hash_bucket(int32_t x, int bbits) {
-  return ((uint32_t)x * 2654435761u) >> (32 - bbits);  // Fibonacci hashing
+  // Fibonacci hashing of the low 24 bits (a product at the full rate)
+  return __builtin_amdgcn_ubfe(__umul24((uint32_t)x, 10368889u), 24 - bbits, bbits);
 }
 
 // Hash table slots per row entry (at least), the kernels' `spread`: a full
@@ -277,7 +281,9 @@ __global__ __launch_bounds__(WAVES * kWave) void k_small_owner(const SmallOwner 
   // Each group of G lanes takes one lower neighbour (NG per wavefront, the
   // wavefronts take successive sets); a missing row has length 0. Reads past a
   // row's end read its last id again.
-  constexpr int G = WAVES == 1 ? kLightGroup : kHeavyGroup, NG = kWave / G, L = kSmallLoads;
+  constexpr int G = WAVES == 1 ? kLightGroup : kHeavyGroup, NG = kWave / G;
+  constexpr int L = kSmallLoads, P = kSmallLookups;
+  static_assert(G == 8 || G == 16, "sums within a row of 16 lanes");
   const int grp = lane / G, gl = lane % G;
   struct Rows {  // a step: the rows from j, ids from k
     int32_t j, k, longest;
@@ -306,35 +312,38 @@ __global__ __launch_bounds__(WAVES * kWave) void k_small_owner(const SmallOwner 
   };
   int32_t acc = 0, pos = -1;  // of this lane: common neighbours, the position of h
   auto probe = [&](const int32_t x[L], const Rows &r) {
-    int4 v[L];
 #pragma unroll
-    for (int j = 0; j < L; ++j) v[j] = buckets[hash_bucket(x[j], bbits)];
-    __builtin_amdgcn_sched_barrier(0);
+    for (int j0 = 0; j0 < L; j0 += P) {
+      if (j0 && r.k + j0 * G >= r.longest) break;  // uniform
+      int4 v[P];
 #pragma unroll
-    for (int j = 0; j < L; ++j) {
-      const int32_t i = r.k + gl + j * G;
-      const bool valid = i < r.q.du;
-      bool hit = v[j].x == x[j] || v[j].y == x[j] || v[j].z == x[j] || v[j].w == x[j];
-      if (__ballot(valid && !hit && v[j].w != kEmpty)) {
-        uint32_t b = hash_bucket(x[j], bbits);
-        int4 t = v[j];
-        while (!hit && t.w != kEmpty) {  // ends at x or at a bucket with room
-          b = (b + 1) & bmask;
-          t = buckets[b];
-          hit = t.x == x[j] || t.y == x[j] || t.z == x[j] || t.w == x[j];
+      for (int j = 0; j < P; ++j) v[j] = buckets[hash_bucket(x[j0 + j], bbits)];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < P; ++j) {
+        const int32_t i = r.k + gl + (j0 + j) * G, y = x[j0 + j];
+        const bool valid = i < r.q.du;
+        bool hit = v[j].x == y || v[j].y == y || v[j].z == y || v[j].w == y;
+        if (__ballot(valid && !hit && v[j].w != kEmpty)) {
+          uint32_t b = hash_bucket(y, bbits);
+          int4 t = v[j];
+          while (!hit && t.w != kEmpty) {  // ends at x or at a bucket with room
+            b = (b + 1) & bmask;
+            t = buckets[b];
+            hit = t.x == y || t.y == y || t.z == y || t.w == y;
+          }
         }
+        acc += valid && hit;
+        if (valid && y == h) pos = i;
       }
-      acc += valid && hit;
-      if (valid && x[j] == h) pos = i;
     }
   };
   auto finish = [&](const Rows &r) {
     int32_t t = acc;
-    t += __builtin_amdgcn_update_dpp(0, t, 0x111, 0xf, 0xf, true);  // row_shr:1, 2, 4, 8
+    t += __builtin_amdgcn_update_dpp(0, t, 0x111, 0xf, 0xf, true);  // row_shr:1, 2, 4 (, 8)
     t += __builtin_amdgcn_update_dpp(0, t, 0x112, 0xf, 0xf, true);
     t += __builtin_amdgcn_update_dpp(0, t, 0x114, 0xf, 0xf, true);
-    t += __builtin_amdgcn_update_dpp(0, t, 0x118, 0xf, 0xf, true);
-    if (G == 32) t += __builtin_amdgcn_update_dpp(0, t, 0x142, 0xa, 0xf, true);  // row_bcast:15 into rows 1, 3
+    if (G == 16) t += __builtin_amdgcn_update_dpp(0, t, 0x118, 0xf, 0xf, true);
     t = __shfl(t, lane | (G - 1), kWave);
     if (r.q.du > 0 && (gl == 0 || pos >= 0)) {
       const int64_t c = (int64_t)t + 2;

@@ -131,8 +131,8 @@ def test_range_lengths(tune, first):
 
 
 # rows around a step of the light kernel's groups (64 ids) and of the heavy
-# one's (128), the largest of each, and ids that fill whole hash buckets (the
-# bucket is the top bits of id * 2654435761): more than one bucket holds
+# one's (128), the largest of each, and ids that fill whole hash buckets (by
+# the top bits of the low 24 of id * 10368889): more than one bucket holds
 @pytest.mark.parametrize("tune", [None, {"small_max": 4096}, {"small_max": 1}, {"small_max": 700, "wbits": 10}])
 @pytest.mark.parametrize("degree", [3, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257])
 def test_small_owner_rows(degree, tune):
@@ -140,7 +140,7 @@ def test_small_owner_rows(degree, tune):
 
     n = 1 << 17
     ids = np.arange(n, dtype=np.uint64)
-    top = ((ids * 2654435761) & 0xFFFFFFFF) >> 24
+    top = ((ids * 10368889) & 0xFFFFFF) >> 16
     same = np.flatnonzero((top == 7) | (top == 8))[:degree]  # close in the table
     rng = np.random.default_rng(degree)
     rest = rng.choice(np.setdiff1d(np.arange(n), same), degree + 40, replace=False)
