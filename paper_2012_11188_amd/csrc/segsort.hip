@@ -297,34 +297,57 @@ __global__ void k_sort_copy(const int64_t *seg_off, const int32_t *list, const i
   }
 }
 
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
-  uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-  lo = __shfl_xor(lo, m, kWave);
-  hi = __shfl_xor(hi, m, kWave);
-  return ((uint64_t)hi << 32) | lo;
+// v of lane ^ M, by lane moves in registers (an LDS permute takes the LDS pipe,
+// which three of them per exchange filled: 12 SBM graphs, rows of 33..64 ids
+// sorted in 385 us by permutes, 263 by moves).
+template <int M>
+__device__ __forceinline__ int32_t lane_xor(int32_t v) {
+  if constexpr (M == 1) return __builtin_amdgcn_update_dpp(0, v, 0xb1, 0xf, 0xf, true);  // quad_perm 1, 0, 3, 2
+  if constexpr (M == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4e, 0xf, 0xf, true);  // quad_perm 2, 3, 0, 1
+  if constexpr (M == 4) {  // row_shl:4 in the quads 0 and 2 of a row, row_shr:4 in 1 and 3
+    const int32_t t = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, true);
+    return __builtin_amdgcn_update_dpp(t, v, 0x114, 0xf, 0xa, false);
+  }
+  if constexpr (M == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);  // row_ror:8
+  if constexpr (M == 16) {  // {rows 0, 0, 2, 2; rows 1, 1, 3, 3}
+    const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    return (int32_t)(threadIdx.x & 16 ? r[0] : r[1]);
+  }
+  if constexpr (M == 32) {  // {low half twice; high half twice}
+    const auto r = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return (int32_t)(threadIdx.x & 32 ? r[0] : r[1]);
+  }
+}
+
+// Lanes that keep the smaller of an exchange.
+template <int S, int SIZE, int STRIDE>
+constexpr uint64_t keep_smaller() {
+  uint64_t m = 0;
+  for (int l = 0; l < kWave; ++l)
+    if ((((l % S) & SIZE) == 0) == (((l % S) & STRIDE) == 0)) m |= 1ull << l;
+  return m;
+}
+
+template <int S, int SIZE, int STRIDE>
+__device__ __forceinline__ void bitonic_exchanges(uint64_t &k, int32_t &id) {
+  const uint64_t ok = (uint64_t)(uint32_t)lane_xor<STRIDE>((int32_t)(uint32_t)k) |
+                      (uint64_t)(uint32_t)lane_xor<STRIDE>((int32_t)(uint32_t)(k >> 32)) << 32;
+  const int32_t oid = lane_xor<STRIDE>(id);
+  // (equal pairs are padding on both sides: it does not matter which is kept)
+  const bool smaller = __builtin_amdgcn_inverse_ballot_w64(keep_smaller<S, SIZE, STRIDE>());
+  if (key_less(ok, oid, k, id) == smaller) {
+    k = ok;
+    id = oid;
+  }
+  if constexpr (STRIDE > 1) bitonic_exchanges<S, SIZE, STRIDE / 2>(k, id);
 }
 
 // Bitonic sort of one (key, id) per lane within groups of S lanes, ascending
-// (pos = lane within the group; every exchange stride is below S, so it stays
-// inside the group).
-template <int S>
-__device__ __forceinline__ void group_bitonic(uint64_t &k, int32_t &id, int pos) {
-#pragma unroll
-  for (int size = 2; size <= S; size <<= 1) {
-#pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      uint64_t ok = shfl_xor_u64(k, stride);
-      int32_t oid = __shfl_xor(id, stride, kWave);
-      bool asc = (pos & size) == 0;
-      bool lower = (pos & stride) == 0;
-      bool other_less = key_less(ok, oid, k, id);
-      bool take = (lower == asc) ? other_less : key_less(k, id, ok, oid);
-      if (take) {
-        k = ok;
-        id = oid;
-      }
-    }
-  }
+// (every exchange stride is below S, so it stays inside the group).
+template <int S, int SIZE = 2>
+__device__ __forceinline__ void group_bitonic(uint64_t &k, int32_t &id) {
+  bitonic_exchanges<S, SIZE, SIZE / 2>(k, id);
+  if constexpr (SIZE < S) group_bitonic<S, SIZE * 2>(k, id);
 }
 
 // Segments of at most S elements; a wavefront sorts kWave / S of them, one
@@ -348,7 +371,7 @@ __device__ __forceinline__ void sort_group(int64_t w, int32_t count, const int64
     k = desc_key(kin[o + pos]);
     id = iin[o + pos];
   }
-  group_bitonic<S>(k, id, pos);
+  group_bitonic<S>(k, id);
   if (pos < len) {
     kout[o + pos] = key_to_sim(k);
     iout[o + pos] = id;
@@ -719,9 +742,33 @@ __device__ __forceinline__ MergePair merge_pair(const int64_t *seg_off, const in
   return m;
 }
 
+// The same for four merges by one wavefront, one on each row of 16 lanes (16
+// candidates at a time). Every row of lanes takes part in every round.
+__device__ __forceinline__ int64_t row_co_rank(const uint64_t *KA, const int32_t *IA, int64_t la, const uint64_t *KB,
+                                               const int32_t *IB, int64_t lb, int64_t o) {
+  const int gl = threadIdx.x & 15, shift = threadIdx.x & 48;
+  int64_t lo = o > lb ? o - lb : 0, hi = o < la ? o : la;
+  while (__any(lo < hi)) {
+    const int64_t step = lo < hi ? (hi - lo + 14) / 15 : 1;  // 15 * step >= hi - lo
+    const int64_t p = lo + (int64_t)gl * step;
+    bool t = true;  // positions at or past hi count as true
+    if (p < hi) {
+      const int64_t j = o - p - 1;
+      t = key_less(KB[j], IB[j], KA[p], IA[p]);
+    }
+    const int f = __ffs((uint32_t)(__ballot(t) >> shift) & 0xffff) - 1;  // the row's last lane samples at or past hi
+    const int64_t nhi = min(hi, lo + (int64_t)f * step);
+    if (f > 0) lo += (int64_t)(f - 1) * step + 1;
+    hi = f > 0 ? nhi : lo;
+  }
+  return lo;
+}
+
 // Merge splits of pass q: split[t] = elements of run A among the outputs of
-// its pair that precede tile t's first output. One wavefront per tile, so
-// the dependent searches of all tiles run concurrently, ahead of the merge.
+// its pair that precede tile t's first output. 16 lanes per tile, so the
+// dependent searches of all tiles run concurrently, ahead of the merge (a
+// wavefront per tile saves a round of five but reads four times the lines:
+// 12 SBM graphs, eight passes, 434 us, now 195).
 __global__ __launch_bounds__(256) void k_big_split(const int64_t *seg_off, const int32_t *big_list,
                                                    const int32_t *tile_seg, const int64_t *tile_first,
                                                    const int32_t *ntilesp, int q, const int32_t *max_passesp,
@@ -730,15 +777,17 @@ __global__ __launch_bounds__(256) void k_big_split(const int64_t *seg_off, const
   const int max_passes = *max_passesp;
   if (q > max_passes) return;
   const int64_t ntiles = *ntilesp;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / kWave;
-  for (int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; t < ntiles; t += nw) {
-    const MergePair m = merge_pair(seg_off, big_list, tile_seg, tile_first, t, q, max_passes);
-    if (m.i < 1) continue;  // uniform across the wavefront
+  const int64_t rows = ((int64_t)gridDim.x * blockDim.x) / 16;
+  const int64_t r0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / 16;
+  for (int64_t t0 = r0 & ~(int64_t)3; t0 < ntiles; t0 += rows) {  // uniform across the wavefront
+    const int64_t t = t0 + (r0 & 3);
+    const MergePair m = merge_pair(seg_off, big_list, tile_seg, tile_first, min(t, ntiles - 1), q, max_passes);
+    const bool in = t < ntiles && m.i >= 1;
     const uint64_t *sK = (m.i & 1) ? KA : KB;
     const int32_t *sI = (m.i & 1) ? IA : IB;
-    const int64_t r = wave_co_rank(sK + m.o + m.a0, sI + m.o + m.a0, m.la, sK + m.o + m.b0, sI + m.o + m.b0,
-                                   m.lb, m.ostart);
-    if ((threadIdx.x & (kWave - 1)) == 0) split[t] = r;
+    const int64_t r = row_co_rank(sK + m.o + m.a0, sI + m.o + m.a0, in ? m.la : 0, sK + m.o + m.b0,
+                                  sI + m.o + m.b0, in ? m.lb : 0, in ? m.ostart : 0);
+    if (in && (threadIdx.x & 15) == 0) split[t] = r;
   }
 }
 
@@ -983,7 +1032,7 @@ scan_status sort_run(const SortClasses &c, const int64_t *seg_off, int64_t total
     const bool own = ntiles <= kOwnSplitTiles;
     for (int q = 1; q <= h.max_passes; ++q) {
       if (!own)
-        k_big_split<<<grid_for(ntiles * kWave, 256), 256, 0, bs>>>(seg_off, big_list, c.tile_seg, c.tile_first,
+        k_big_split<<<grid_for(ntiles * 16, 256), 256, 0, bs>>>(seg_off, big_list, c.tile_seg, c.tile_first,
                                                                   &st->big_tiles, q, &st->max_passes, KA, IA, KB,
                                                                   IB, split);
       const auto merge = own ? k_big_merge<true> : k_big_merge<false>;
