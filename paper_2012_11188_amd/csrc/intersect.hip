@@ -443,14 +443,15 @@ __device__ __forceinline__ int64_t wave_lower_bound(const int32_t *row, int64_t 
 // from radj: adj itself, or the same rows with ids numbered without the
 // isolated vertices (cid), in the same order.
 //
-// No unit is saturated: on R-MAT-20, alone, 3.1 ms with the vector units and
-// the LDS each at 48 %, 11 GB read from the Infinity Cache at 3.6 of 7.6 TB/s
-// (random kilobytes, measured), a quarter of the wavefronts' time waiting for
-// their turn to issue. What helped was fewer instructions and fewer waits per
-// id and per range (before, with the hub product: R-MAT-20 4.13 ms, R-MAT-23
-// 330; now 3.70 and 268): LDS reads in groups, short ranges together, ranges
-// past the end read as id 0 and taken out of the sums, claims not waited for,
-// the next chunk's data read ahead. Two workgroups of half the size where the
+// Bound by the reads behind the L2s: on R-MAT-20, alone, 3.1 ms for 22 GB at
+// 7.1 of the 7.6 TB/s that random kilobytes reach from the Infinity Cache; on
+// R-MAT-23 1.67 TB at 5.8 of 6.9 TB/s. The vector units and the LDS are each
+// at 48 %, and a quarter of the wavefronts' time is waiting to issue. What
+// brought it there was fewer instructions and fewer waits per id and per range
+// (before, with the hub product: R-MAT-20 4.13 ms, R-MAT-23 330; now 3.70 and
+// 268): LDS reads in groups, short ranges together, ranges past the end read
+// as id 0 and taken out of the sums, claims not waited for, the next chunk's
+// data read ahead. Two workgroups of half the size where the
 // bitmap leaves room (2^19 vertices) were slower, 3.29 against 3.12 ms a build.
 template <bool kOneWindow>
 __global__ __launch_bounds__(kBigThreads) void k_big_owner(

@@ -29,3 +29,11 @@ def test_ari_matches_sklearn():
         b = np.where(rng.random(n) < 0.7, a, rng.integers(-1, k, n))
         la, lb = bench._labels(a), bench._labels(b)
         assert bench.adjusted_rand_index(a, b) == pytest.approx(metrics.adjusted_rand_score(la, lb), abs=1e-12)
+
+
+def test_source_hashes():
+    """The marks that cut the kernels' source are in the sources."""
+    import bench
+
+    assert len(bench.kernel_source_hash()) == 64 and len(bench.library_source_hash()) == 64
+    assert bench.counter_traffic({"small_max": 1, "spc": 1, "wbits": 1}, "none")[0] is None
