@@ -40,13 +40,15 @@ __global__ void k_hub_flags(const int32_t *deg, int64_t n, int32_t row_deg, int3
 }
 
 __global__ void k_hub_maps(const int32_t *deg, int64_t n, int32_t row_deg, int32_t col_deg, const int64_t *P,
-                           int32_t *row, int32_t *col, int32_t *verts) {
+                           VertexRecord *records, int32_t *col, int32_t *verts) {
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
     const int32_t d = deg[v];
     const int64_t p = P[v];
     col[v] = d >= col_deg ? (int32_t)(uint32_t)p : -1;
-    row[v] = d >= row_deg ? (int32_t)(p >> 32) : -1;
-    if (d >= row_deg) verts[p >> 32] = (int32_t)v;
+    if (d >= row_deg) {
+      records[v].hub = (int32_t)(p >> 32);
+      verts[p >> 32] = (int32_t)v;
+    }
   }
 }
 
@@ -276,13 +278,13 @@ HubShape choose_hubs(const PlanCounts &pc, int64_t nnz, bool one_window) {
 
 scan_status prepare_hubs(const HubShape &shape, int64_t n, const int64_t *off, const int32_t *deg,
                          const int32_t *adj, const int32_t *radj, int32_t wbits, int32_t nwin, int32_t *win,
-                         DevArena &arena, hipStream_t s, HubView *out) {
+                         VertexRecord *records, DevArena &arena, hipStream_t s, HubView *out) {
   HubView h;
   h.rows = shape.rows;
   h.cols = (shape.cols + kColBlock - 1) / kColBlock * kColBlock;
   h.stride = (shape.rows + kTile - 1) / kTile * kTile;
   int64_t *flags, *P, *ws;
-  int32_t *row, *col, *verts, *rest;
+  int32_t *col, *verts, *rest;
   HubRow *row_of;
   uint4 *bits;
   uint16_t *pre, *D;
@@ -290,7 +292,6 @@ scan_status prepare_hubs(const HubShape &shape, int64_t n, const int64_t *off, c
   SCAN_TRY(arena.alloc(&flags, n));
   SCAN_TRY(arena.alloc(&P, n + 1));
   SCAN_TRY(arena.alloc(&ws, scan_workspace_elems(n)));
-  SCAN_TRY(arena.alloc(&row, n));
   SCAN_TRY(arena.alloc(&col, n));
   SCAN_TRY(arena.alloc(&verts, h.rows));
   SCAN_TRY(arena.alloc(&row_of, h.rows));
@@ -299,7 +300,6 @@ scan_status prepare_hubs(const HubShape &shape, int64_t n, const int64_t *off, c
   SCAN_TRY(arena.alloc(&pre, (int64_t)h.rows * (h.cols / 128)));
   SCAN_TRY(arena.alloc(&D, (int64_t)h.stride * h.stride));
   SCAN_TRY(arena.alloc(&cursor, 1));
-  h.row = row;
   h.col = col;
   h.row_of = row_of;
   h.rest = rest;
@@ -309,7 +309,7 @@ scan_status prepare_hubs(const HubShape &shape, int64_t n, const int64_t *off, c
   SCAN_HIP_TRY(hipMemsetAsync(cursor, 0, 8, s));
   k_hub_flags<<<grid_for(n, 256, 4096), 256, 0, s>>>(deg, n, shape.row_deg, shape.col_deg, flags);
   SCAN_TRY(exclusive_scan64(flags, P, n, ws, s));
-  k_hub_maps<<<grid_for(n, 256, 4096), 256, 0, s>>>(deg, n, shape.row_deg, shape.col_deg, P, row, col, verts);
+  k_hub_maps<<<grid_for(n, 256, 4096), 256, 0, s>>>(deg, n, shape.row_deg, shape.col_deg, P, records, col, verts);
   k_hub_rows<<<h.stride, kRowThreads, 0, s>>>(h, verts, off, adj, radj, wbits, nwin, win, cursor);
   const int tiles = h.stride / kTile;
   k_hub_product<<<tiles * (tiles + 1) / 2, 256, 0, s>>>(h, D);

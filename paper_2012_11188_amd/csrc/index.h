@@ -71,6 +71,10 @@ struct SmallOwner {
   int32_t h, dh;  // vertex, degree
   int64_t oh;     // first slot of its row
 };
+struct VertexRecord {  // what the large owners read of a neighbour, in one line
+  int32_t deg, hub;    // degree, hub row or -1
+  int64_t off;         // first slot of its row
+};
 struct BigChunk {
   int32_t h;
   int32_t k;    // slots [k*spc, (k+1)*spc) of row h
@@ -81,7 +85,8 @@ struct BigChunk {
 struct IntersectPlan {
   int64_t n = 0, nnz = 0;
   bool one_graph = false;  // set by the caller
-  SmallOwner *small_list = nullptr, *heavy_list = nullptr;
+  SmallOwner *lists = nullptr;          // n entries: the light ones first, the heavy ones at the end
+  VertexRecord *records = nullptr;      // n entries, for the intersection to fill
   void *big_list = nullptr, *counts = nullptr;  // device chunk list and counts
   const void *host = nullptr;                   // the host's copy of the counts
   // helper streams already ordered after the plan (set by the caller), used
@@ -111,7 +116,6 @@ struct HubRow {
 struct HubView {
   int32_t rows = 0, cols = 0;          // cols padded to a multiple of 256
   int32_t stride = 0;                  // rows padded to a multiple of 256
-  const int32_t *row = nullptr;        // per vertex: its row, or -1
   const int32_t *col = nullptr;        // per vertex: its column, or -1
   const HubRow *row_of = nullptr;
   const int32_t *rest = nullptr;
@@ -123,10 +127,10 @@ struct HubView {
   }
 };
 HubShape choose_hubs(const PlanCounts &pc, int64_t nnz, bool one_window);
-// win (several id windows): window starts of the rows' rests, rows x (nwin + 1).
+// The rows' numbers go into records. win (several id windows): window starts of the rows' rests, rows x (nwin + 1).
 scan_status prepare_hubs(const HubShape &shape, int64_t n, const int64_t *off, const int32_t *deg,
                          const int32_t *adj, const int32_t *radj, int32_t wbits, int32_t nwin, int32_t *win,
-                         DevArena &arena, hipStream_t s, HubView *out);
+                         VertexRecord *records, DevArena &arena, hipStream_t s, HubView *out);
 
 // a2-a4: ownership plan, then intersection + similarity for every edge,
 // written into both CSR slots of sims (and counts if non-null).

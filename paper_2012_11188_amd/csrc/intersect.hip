@@ -113,7 +113,7 @@ constexpr int kPlanPer = 8;  // consecutive vertices per thread and tile
 // staging pass). The block scans its counts, reserves list space with one
 // global atomic per list, and writes the entries in vertex order.
 __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, const int64_t *off, int64_t n, int small_max,
-                                                       int spc, SmallOwner *small_list, SmallOwner *heavy_list,
+                                                       int spc, SmallOwner *lists,
                                                        BigChunk *big_list, PlanCounts *pc, int32_t words,
                                                        int32_t *host) {
   __shared__ int32_t last;
@@ -154,8 +154,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, const
     int32_t ps = base_small + os, ph = base_heavy + oh, pb = base_big + ob;
 #pragma unroll
     for (int k = 0; k < kPlanPer; ++k) {
-      if (code[k] == -1) small_list[ps++] = SmallOwner{(int32_t)(v0 + k), deg[v0 + k], off[v0 + k]};
-      if (code[k] == -2) heavy_list[ph++] = SmallOwner{(int32_t)(v0 + k), deg[v0 + k], off[v0 + k]};
+      if (code[k] == -1) lists[ps++] = SmallOwner{(int32_t)(v0 + k), deg[v0 + k], off[v0 + k]};
+      if (code[k] == -2) lists[n - 1 - ph++] = SmallOwner{(int32_t)(v0 + k), deg[v0 + k], off[v0 + k]};
       for (int32_t j = 0; j < code[k]; ++j) big_list[pb++] = BigChunk{(int32_t)(v0 + k), j, deg[v0 + k], 0, off[v0 + k]};
     }
   }
@@ -456,8 +456,8 @@ __device__ __forceinline__ int64_t wave_lower_bound(const int32_t *row, int64_t 
 template <bool kOneWindow>
 __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     const BigChunk *chunks, PlanCounts *pc, int spc, int wbits, int64_t n,
-    const int64_t *off, const int32_t *deg, const int32_t *adj, const int32_t *radj, const int64_t *cid,
-    const int32_t *wt, int32_t nwin, HubView hub, int kind, double *sims, int32_t *counts, int32_t skip) {
+    const VertexRecord *records, const int32_t *adj, const int32_t *radj, const int64_t *cid, const int32_t *wt,
+    int32_t nwin, HubView hub, int kind, double *sims, int32_t *counts, int32_t skip) {
   extern __shared__ unsigned char smem[];
   const int64_t W = (int64_t)1 << wbits;
   const int nwords = (int)(W >> 5);
@@ -531,7 +531,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
   int64_t ou = 0;                            // and its first slot
   int32_t un = 0, du_n = 0, r_n = -1;        // the next chunk's slot: vertex, degree, hub row
   int64_t ou_n = 0;
-  int32_t of_n = 0;                          // the next owner's hub row and column, and its id among the streamed ones
+  int32_t of_n = -1;                         // the next owner's hub row and column, and its id among the streamed ones
   int32_t hc = 0, hx = 0;                    // this one's
   bool hubs = false;                         // this chunk's slot is an edge between hubs, and then:
   HubRow hq{0, 0, 0};
@@ -609,9 +609,10 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     }
     // The next chunk's slots, and what follows of the chain.
     auto advance = [&]() {
-      du_n = deg[un];
-      ou_n = off[un];
-      if (hub.rows) r_n = hub.row[un];
+      const VertexRecord q = records[un];  // (one line a neighbour instead of three)
+      du_n = q.deg;
+      r_n = q.hub;
+      ou_n = q.off;
       if (own_tab) own_n = lane <= nwin ? wt[(int64_t)nxt.h * (nwin + 1) + lane] : INT32_MAX;
       c2 = c3;
       d2 = ((const int32_t *)(chunks + max(0, min(c3, nchunks - 1))))[min(lane, (int)(sizeof(BigChunk) / 4) - 1)];
@@ -940,8 +941,8 @@ __global__ __launch_bounds__(kBigThreads) void k_big_owner(
     const Owner two = owner_of(c2, d2);
     if (two.m) {
       un = adj[two.s0 + min(tid, two.m - 1)];
-      const int32_t *at = lane == 0 ? hub.row + two.h : lane == 1 ? hub.col + two.h : (const int32_t *)(cid + two.h);
-      if (lane < 2 ? hub.rows > 0 : lane == 2 && cid) of_n = *at;
+      const int32_t *at = lane == 0 ? &records[two.h].hub : lane == 1 ? hub.col + two.h : (const int32_t *)(cid + two.h);
+      if (lane == 0 || (lane == 1 && hub.rows) || (lane == 2 && cid)) of_n = *at;
     }
     // This chunk's edges.
     if (low_c) {
@@ -1060,6 +1061,13 @@ __global__ __launch_bounds__(256) void k_window_table(const int64_t *off, const 
   }
 }
 
+__global__ void k_vertex_records(const int64_t *off, int64_t n, VertexRecord *records) {
+  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t o = off[v];
+    records[v] = VertexRecord{(int32_t)(off[v + 1] - o), -1, o};
+  }
+}
+
 // Ids without the isolated vertices, in the same order.
 __global__ void k_id_flags(const int32_t *deg, int64_t n, int32_t *flags) {
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
@@ -1108,14 +1116,14 @@ scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, c
   if (nnz == 0) return SCAN_OK;
   BigChunk *big_list;
   PlanCounts *pc = (PlanCounts *)counts;
-  SCAN_TRY(arena.alloc(&p.small_list, n));
-  SCAN_TRY(arena.alloc(&p.heavy_list, n));
+  SCAN_TRY(arena.alloc(&p.lists, n));
+  SCAN_TRY(arena.alloc(&p.records, n));
   SCAN_TRY(arena.alloc(&big_list, nnz / cfg.spc + std::min(n, nnz / cfg.small_max) + 1));
   p.big_list = big_list;
   p.counts = counts;
   p.host = host;
   k_plan<<<grid_for(n, kPlanThreads * kPlanPer, 2048), kPlanThreads, 0, s>>>(
-      deg, off, n, cfg.small_max, cfg.spc, p.small_list, p.heavy_list, big_list, pc, words, (int32_t *)host);
+      deg, off, n, cfg.small_max, cfg.spc, p.lists, big_list, pc, words, (int32_t *)host);
   SCAN_HIP_TRY(hipEventRecord(ready, s));
   return SCAN_OK;
 }
@@ -1181,10 +1189,11 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
       k_window_table<<<grid_for(n * kWave, 256), 256, 0, s>>>(off, renamed ? renamed : adj, n, wbits, nwin, wt);
     }
   }
+  if (h.big) k_vertex_records<<<grid_for(n, 256, 4096), 256, 0, s>>>(off, n, plan->records);
   HubView hub;
   if (shape.rows && (nwin == 1 || wt) &&
       prepare_hubs(shape, n, off, deg, adj, renamed ? renamed : adj, wbits, nwin,
-                   wt ? wt + (int64_t)(nwin + 1) * n : nullptr, tmp, s, &hub) != SCAN_OK)
+                   wt ? wt + (int64_t)(nwin + 1) * n : nullptr, plan->records, tmp, s, &hub) != SCAN_OK)
     hub = HubView{};  // no memory for it: every row is streamed whole
   if (big_lds_bytes(wbits, cfg.spc) > (size_t)lds_max) return fail(SCAN_EINVAL, "chunk size too large for LDS");
   if (stats) {
@@ -1235,10 +1244,10 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
     const int grid = (int)std::min<int64_t>((int64_t)cus * per_cu, h.big);
     SCAN_TRY(mark(stats ? stats->ev_big_begin : nullptr, s));
     if (one)
-      k_big_owner<true><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, off, deg, adj, radj, cid, nullptr,
+      k_big_owner<true><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, plan->records, adj, radj, cid, nullptr,
                                                        nwin, hub, kind, sims, counts, cfg.skip_deg);
     else
-      k_big_owner<false><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, off, deg, adj, radj, cid, wt,
+      k_big_owner<false><<<grid, kBigThreads, lds, s>>>(big_list, pc, cfg.spc, wbits, n, plan->records, adj, radj, cid, wt,
                                                         nwin, hub, kind, sims, counts, cfg.skip_deg);
     SCAN_HIP_TRY(hipGetLastError());
     SCAN_TRY(mark(stats ? stats->ev_big_end : nullptr, s));
@@ -1261,9 +1270,9 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1));
     if (h.heavy)  // the longer rows first
       k_small_owner<kSmallWaves><<<h.heavy, kSmallWaves * kWave, lds, sh>>>(
-          plan->heavy_list, cfg.small_max, spread, off, adj, kind, sims, counts, cfg.skip_deg);
+          plan->lists + (n - h.heavy), cfg.small_max, spread, off, adj, kind, sims, counts, cfg.skip_deg);
     if (h.small)
-      k_small_owner<1><<<h.small, kWave, lds1, sl>>>(plan->small_list, cap, kSpread, off, adj, kind, sims, counts,
+      k_small_owner<1><<<h.small, kWave, lds1, sl>>>(plan->lists, cap, kSpread, off, adj, kind, sims, counts,
                                                      cfg.skip_deg);
     SCAN_HIP_TRY(hipGetLastError());
   }

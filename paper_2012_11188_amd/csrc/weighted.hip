@@ -809,9 +809,9 @@ static scan_status weighted_by_plan(const IntersectPlan &plan, int64_t n, int64_
   constexpr int kHeavyWaves = 4;
   if (c.heavy)
     k_w_small<kHeavyWaves><<<c.heavy, kHeavyWaves * kWave, w_small_lds(kWbSmallMax), sh>>>(
-        plan.heavy_list, kWbSmallMax, off, deg, adj, w, S, sims, skip);
+        plan.lists + (n - c.heavy), kWbSmallMax, off, deg, adj, w, S, sims, skip);
   if (c.small)
-    k_w_small<1><<<c.small, kWave, w_small_lds(kLightDeg), sl>>>(plan.small_list, kLightDeg, off, deg, adj, w, S,
+    k_w_small<1><<<c.small, kWave, w_small_lds(kLightDeg), sl>>>(plan.lists, kLightDeg, off, deg, adj, w, S,
                                                                  sims, skip);
   SCAN_HIP_TRY(hipGetLastError());
   return SCAN_OK;
