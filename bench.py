@@ -164,7 +164,7 @@ def autotune(scan, graphs, kind, tune_arg, reps=2):
     """Returns (tune dict, info). --tune auto runs the autotuner (untimed)."""
     t = parse_tune(tune_arg)
     if t is not None:
-        full = {"small_max": t.get("small_max", 256), "spc": t.get("spc", 512), "wbits": t.get("wbits", 20)}
+        full = {"small_max": t.get("small_max", 256), "spc": t.get("spc", 768), "wbits": t.get("wbits", 20)}
         return full, {"source": "given"}
     t0 = time.perf_counter()
     best = scan.scan_autotune(graphs, kind, reps=reps)

@@ -243,7 +243,7 @@ scan_status scan_build_index_lsh(const scan_csr *g, scan_sim_kind kind, const sc
  *              their row in LDS (1..4096; default 256, or 512 above 2^21
  *              vertices when spc is zero too)
  *   spc        row slots per work chunk of a larger owner (1..1024; default
- *              512, or 768 above 2^21 vertices when small_max is zero too)
+ *              768, or 1024 above 2^21 vertices when small_max is zero too)
  *   wbits      LDS bitmap window of 2^wbits vertex ids for larger owners
  *              (10..24; default 20); lowered to what LDS holds and to the id
  *              space; when the ids span several windows each chunk sweeps the
