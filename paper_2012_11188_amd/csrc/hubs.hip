@@ -235,9 +235,13 @@ __global__ __launch_bounds__(256, 1) void k_hub_product(HubView hub, uint16_t *D
 // of its lower end's ids that are columns (the columns' share of all slots),
 // and the product takes rounds of 256 workgroups. On R-MAT-20 the model's
 // edges and ids are within 12% of the counted ones. The rates are the
-// large-owner kernel's time per streamed id and the product's measured one.
+// large-owner kernel's time per streamed id and the product's measured one; a
+// gain below 0.1 ms is left alone. Builds without it and with: R-MAT of 60,000
+// vertices (not chosen) 0.53 ms, R-MAT-20 (5,120 rows) 6.98 and 6.80 ms,
+// R-MAT-23 417 and 383 ms (11,520 rows); with the faster large-owner kernel,
+// 11,520 and 44,544 rows 305 and 291 ms. kHubMaxRows bounds D to 4.8 GB.
 HubShape choose_hubs(const PlanCounts &pc, int64_t nnz, bool one_window) {
-  const double per_id = one_window ? 0.5e-12 : 1.0e-12;  // seconds
+  const double per_id = one_window ? 0.5e-12 : 0.6e-12;  // seconds
   const double per_round_col = 8.0 / 2.3e9 / 0.6;        // a round's seconds per column
   const double per_slot = 20e-12, fixed = 60e-6;         // building the rows; the launches
   double c[kDegBins], d[kDegBins];

@@ -103,7 +103,7 @@ scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, c
                            void *counts, int32_t words, void *host, hipEvent_t ready, IntersectPlan &plan);
 
 // Common neighbours among hubs by matrix product (hubs.hip).
-constexpr int32_t kHubMaxRows = 32768, kHubMaxCols = 65536;  // counts of common columns fit 16 bits
+constexpr int32_t kHubMaxRows = 49152, kHubMaxCols = 65536;  // counts of common columns fit 16 bits
 constexpr int32_t kHubMaxWindows = 63;
 struct HubShape {
   int32_t rows = 0, cols = 0;        // their numbers (0: no product)
