@@ -445,7 +445,7 @@ __device__ __forceinline__ int64_t wave_lower_bound(const int32_t *row, int64_t 
 //
 // Bound by the reads behind the L2s: on R-MAT-20, alone, 3.05 ms for 20 GB at
 // 6.6 of the 7.6 TB/s that random kilobytes reach from the Infinity Cache; on
-// R-MAT-23 1.68 TB at 6.7 of 6.9 TB/s. The vector units and the LDS are each
+// R-MAT-23 1.45 TB at 6.7 of 6.9 TB/s. The vector units and the LDS are each
 // at 48 %, and a quarter of the wavefronts' time is waiting to issue. What
 // brought it there was fewer instructions and fewer waits per id and per range
 // (before, with the hub product: R-MAT-20 4.13 ms, R-MAT-23 330; now 3.70 and
