@@ -230,11 +230,26 @@ static void release_slots(scan_index *ix, std::vector<scan_index::PooledSlot *> 
   got.clear();
 }
 
+// The workspaces are pooled and their marks count epochs, so a recorded
+// launch could not be replayed: a capturing stream is refused, before anything
+// is allocated on it (recorded, a workspace's allocation and the clearing of
+// its marks would run only when the graph does, if ever) and before the
+// completion event of a pooled workspace is recorded into the capture (nothing
+// would wait for its last use any more).
+static scan_status refuse_capture(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  SCAN_HIP_TRY(hipStreamIsCapturing(s, &cap));
+  if (cap != hipStreamCaptureStatusNone)
+    return fail(SCAN_EDEVICE, "queries cannot be captured into a graph (scan_query_noalloc can)");
+  return SCAN_OK;
+}
+
 static scan_status query_impl(const scan_index *cix, int32_t count, const int32_t *mu,
                               const double *eps, int32_t *memberships, uint8_t *is_core,
                               int32_t out_on_device, hipStream_t s) {
   scan_index *ix = const_cast<scan_index *>(cix);
   const int64_t n = ix->n;
+  SCAN_TRY(refuse_capture(s));
   std::vector<scan_index::PooledSlot *> got;
   SCAN_TRY(acquire_slots(ix, count, s, got));
   std::vector<QuerySlot *> slots(count);
@@ -466,6 +481,7 @@ scan_status scan_sweep_modularity(const scan_index *ix, int32_t count, const int
     return SCAN_OK;
   }
   hipStream_t s = stream ? (hipStream_t)stream : ix->stream;
+  SCAN_TRY(refuse_capture(s));
   const int32_t B = std::min(batch, count);
   DevArena tmp(s);
   int32_t *memb;

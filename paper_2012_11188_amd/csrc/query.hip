@@ -740,12 +740,6 @@ void free_query_slot(QuerySlot *slot, hipStream_t s) {
 scan_status run_queries(const scan_index *ix, int32_t count, const int32_t *mu, const double *eps,
                         int32_t *const *memberships, uint8_t *const *is_core, QuerySlot *const *slots,
                         hipStream_t s) {
-  // The workspaces are pooled and their marks count epochs, so a recorded
-  // launch could not be replayed: refuse a capturing stream.
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  SCAN_HIP_TRY(hipStreamIsCapturing(s, &cap));
-  if (cap != hipStreamCaptureStatusNone)
-    return fail(SCAN_EDEVICE, "queries cannot be captured into a graph (scan_query_noalloc can)");
   for (int32_t i0 = 0; i0 < count; i0 += kArgDescs) {
     const int32_t c = std::min<int32_t>(kArgDescs, count - i0);
     DescsInArgs d{};

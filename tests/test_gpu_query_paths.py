@@ -80,3 +80,46 @@ def test_small_index_edges(n, p):
     oix = oracle.build_index(g, oracle.COSINE, threads=8)
     vals = np.unique(oix.sim) if g.nnz else np.array([0.5])
     assert_queries_equal(gix, oix, [(mu, float(e)) for mu in (2, 3, 17, 40) for e in vals[:: max(1, len(vals) // 6)]])
+
+
+# A refused call leaves nothing behind: no workspace in the pool whose memory
+# or cleared marks exist only inside the captured graph, and no event of a
+# pooled workspace recorded there.
+@pytest.mark.parametrize("warm", [False, True])
+@pytest.mark.parametrize("n,call", [(300, "one"), (3000, "one"), (3000, "host"), (3000, "batch"), (3000, "sweep")])
+def test_queries_after_refused_capture(n, call, warm):
+    import torch
+
+    g = graphgen.sbm(n, 6, 60.0 / n, 4.0 / n, 11)
+    gix = gpu_build(g)
+    oix = oracle.build_index(g, oracle.COSINE, threads=8)
+    memb = torch.zeros(n, dtype=torch.int32, device="cuda")
+    core = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    s = torch.cuda.Stream()
+    if warm:
+        scan.scan_query_ex(gix, 3, 0.2, memb, core, stream=s)
+    torch.cuda.synchronize()
+    graph, filled = torch.cuda.CUDAGraph(), torch.zeros(n, dtype=torch.int32, device="cuda")
+    with torch.cuda.graph(graph, stream=s):
+        filled.fill_(7)
+        with pytest.raises(scan.ScanError, match="captured"):
+            if call == "one":
+                scan.scan_query_ex(gix, 3, 0.2, memb, core, stream=s)
+            elif call == "host":
+                scan.scan_query_ex(gix, 3, 0.2, stream=s, out_on_device=False)
+            elif call == "batch":
+                scan.scan_query_batch(gix, [3, 4, 5], [0.2, 0.3, 0.1], stream=s)
+            else:
+                scan.scan_sweep_modularity(gix, [3, 4], [0.2, 0.3], stream=s)
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(filled.min()) == 7 and int(filled.max()) == 7
+        filled.zero_()
+        for mu, eps in ((2, 0.1), (3, 0.2), (5, 0.3)):
+            for stream in (s, None):
+                scan.scan_query_ex(gix, mu, eps, memb, core, stream=stream)
+                torch.cuda.synchronize()
+                want = oracle.query(oix, mu, eps)
+                assert np.array_equal(memb.cpu().numpy(), want[0]) and np.array_equal(core.cpu().numpy(), want[1])
+    gix.free()
