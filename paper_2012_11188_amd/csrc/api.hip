@@ -188,19 +188,29 @@ static scan_status acquire_slots(scan_index *ix, int count, hipStream_t s,
       got.push_back(p);
     }
   }
+  // A workspace joins the pool once all of the call's are there: until its
+  // marks are cleared on s, no other stream may take it.
+  const size_t reused = got.size();
   while ((int)got.size() < count) {
     auto *p = new scan_index::PooledSlot();
-    scan_status st = alloc_query_slot(ix, &p->slot, s);
+    const scan_status st = alloc_query_slot(ix, &p->slot, s);
     if (st != SCAN_OK) {
       delete p;
-      for (auto *q : got) q->busy = false;
+      for (size_t i = 0; i < got.size(); ++i) {
+        if (i < reused) {
+          got[i]->busy = false;
+        } else {
+          free_query_slot(&got[i]->slot, s);
+          delete got[i];
+        }
+      }
       got.clear();
       return st;
     }
     p->busy = true;
-    ix->pool.push_back(p);
     got.push_back(p);
   }
+  ix->pool.insert(ix->pool.end(), got.begin() + reused, got.end());
   return SCAN_OK;
 }
 
