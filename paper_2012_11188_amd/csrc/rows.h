@@ -1,0 +1,28 @@
+// Where the kernels' reads of a row go, also of a row that is shorter than its
+// readers or empty. Graphs are not checked unless SCAN_VALIDATE asks for it, so
+// a vertex without neighbours of its own may still be met as one; what comes
+// out for such a graph is not defined, but every read stays inside its arrays.
+// Plain functions, so that they can be checked without a GPU.
+#pragma once
+
+#include <stdint.h>
+
+#ifdef __HIPCC__
+#define SCAN_ROWS_FN __host__ __device__ __forceinline__
+#else
+#define SCAN_ROWS_FN static inline
+#endif
+
+namespace scan {
+
+// First slot of a row that starts at `off`; an empty one (which may start
+// where the slots end) stands at slot 0.
+SCAN_ROWS_FN int64_t row_start(int64_t off, int32_t deg) { return deg > 0 ? off : 0; }
+
+// Position p of a row; past its end its last one (0 where it has none).
+SCAN_ROWS_FN int32_t row_position(int32_t p, int32_t deg) {
+  const int32_t top = deg > 0 ? deg - 1 : 0;
+  return p < top ? p : top;
+}
+
+}  // namespace scan
