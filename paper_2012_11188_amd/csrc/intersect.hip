@@ -1073,19 +1073,20 @@ __global__ void k_vertex_records(const int64_t *off, int64_t n, VertexRecord *re
   }
 }
 
-// Ids without the isolated vertices, in the same order.
+// Ids without the isolated vertices (`used` are left), in the same order.
 __global__ void k_id_flags(const int32_t *deg, int64_t n, int32_t *flags) {
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
     flags[v] = deg[v] > 0;
 }
-__global__ __launch_bounds__(256) void k_rename(const int32_t *adj, int64_t nnz, const int64_t *cid, int32_t *out) {
+__global__ __launch_bounds__(256) void k_rename(const int32_t *adj, int64_t nnz, const int64_t *cid, int32_t used,
+                                                int32_t *out) {
   constexpr int kPer = 4;  // ids per thread in flight
   for (int64_t s0 = blockIdx.x * (int64_t)(kPer * 256) + threadIdx.x; s0 < nnz; s0 += (int64_t)gridDim.x * kPer * 256) {
     int32_t x[kPer];
 #pragma unroll
     for (int k = 0; k < kPer; ++k) x[k] = s0 + k * 256 < nnz ? adj[s0 + k * 256] : 0;
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) x[k] = (int32_t)cid[x[k]];
+    for (int k = 0; k < kPer; ++k) x[k] = used_number(cid[x[k]], used);
 #pragma unroll
     for (int k = 0; k < kPer; ++k)
       if (s0 + k * 256 < nnz) out[s0 + k * 256] = x[k];
@@ -1171,7 +1172,7 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
         tmp.alloc(&cid, n + 1) == SCAN_OK && tmp.alloc(&ws, scan_workspace_elems(n)) == SCAN_OK) {
       k_id_flags<<<grid_for(n, 256), 256, 0, s>>>(deg, n, flags);
       SCAN_TRY(exclusive_scan(flags, cid, n, ws, s));
-      k_rename<<<grid_for(nnz, 1024), 256, 0, s>>>(adj, nnz, cid, renamed);
+      k_rename<<<grid_for(nnz, 1024), 256, 0, s>>>(adj, nnz, cid, h.rows, renamed);
       wbits = rbits;
       nwin = windows(h.rows, rbits);
     } else {

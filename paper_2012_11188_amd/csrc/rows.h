@@ -25,4 +25,12 @@ SCAN_ROWS_FN int32_t row_position(int32_t p, int32_t deg) {
   return p < top ? p : top;
 }
 
+// The number of a vertex among the `used` ones with neighbours, from the count
+// of those before it. One without (met as a neighbour all the same) may have
+// them all before it; its number stays below `used` too, as the id windows and
+// the bitmap reach no further.
+SCAN_ROWS_FN int32_t used_number(int64_t before, int32_t used) {
+  return (int32_t)(before < used ? before : used - 1);
+}
+
 }  // namespace scan
