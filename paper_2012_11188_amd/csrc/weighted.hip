@@ -43,6 +43,7 @@
 #include <climits>
 
 #include "index.h"
+#include "rows.h"
 
 namespace scan {
 namespace {
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_w_small(const SmallOwner *lis
       le[j] = (uint16_t)i;
       lid[j] = u;
       ldu[j] = d;
-      lou[j] = off[u];
+      lou[j] = row_start(off[u], d);
     }
   }
   __syncthreads();
@@ -258,12 +259,12 @@ __global__ __launch_bounds__(WAVES * kWave) void k_w_small(const SmallOwner *lis
     const int32_t j = min(j0 + row, nlow - 1);
     const bool has = j0 + row < nlow;
     WEdge e{lid[j], has ? ldu[j] : 0, lou[j], tw[le[j]], 0.0, false};
-    const int32_t top = ldu[j] - 1, steps = (quad_max(e.du) + 15) / 16;
+    const int32_t du = ldu[j], steps = (quad_max(e.du) + 15) / 16;
     int64_t mpos = -1;
     int32_t x;
     double wl;
     auto fetch = [&](int32_t s) {
-      const int64_t q = e.ou + min(s * 16 + gl, top);
+      const int64_t q = e.ou + row_position(s * 16 + gl, du);
       x = adj[q];
       wl = w[q];
     };
@@ -411,7 +412,7 @@ __global__ __launch_bounds__(kWbThreads) void k_w_big(const BigChunk *chunks, Pl
         le_e[k] = (uint16_t)tid;
         le_l[k] = u;
         le_du[k] = du;
-        le_ou[k] = off[u];
+        le_ou[k] = row_start(off[u], du);
         le_mpos[k] = -1;
         atomicAdd(&sh->cls[length_class(du)], 1);
       }
@@ -478,14 +479,15 @@ __global__ __launch_bounds__(kWbThreads) void k_w_big(const BigChunk *chunks, Pl
       if (q >= nlow) break;
       const bool has = q + row < nlow;
       const int k = order[min(q + row, nlow - 1)];
-      const int32_t ldu = le_du[k], top = ldu - 1;
+      const int32_t ldu = le_du[k], top = row_position(INT_MAX, ldu);
       WEdge e{le_l[k], has ? ldu : 0, le_ou[k], w[s0 + le_e[k]], 0.0, false};
       const int32_t steps = (quad_max(e.du) + 15) / 16;
       // Slots fit 32 bits, their weights' bytes too. A step's position is a
       // scalar, so an id's byte takes one add and one clamp, and the same add
       // tells whether it lies in the row.
       const uint32_t eo = (uint32_t)e.ou, ho = (uint32_t)oh;
-      const uint32_t id0 = (eo + gl) * 4u, id_top = (eo + (uint32_t)top) * 4u, id_end = has ? id_top + 1 : 0;
+      const uint32_t id0 = (eo + gl) * 4u, id_top = (eo + (uint32_t)top) * 4u,
+                     id_end = has && ldu > 0 ? id_top + 1 : 0;
       auto fetch = [&](int32_t s) -> int32_t {
         return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(ar, (int)min(id0 + (uint32_t)s * 64u, id_top), 0, 0);
       };

@@ -17,11 +17,11 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 PROGRAM = r"""
 #include <cstdio>
 #include "rows.h"
-int main() {  // "off deg" lines, then for each the reads of positions 0..299
+int main() {  // "off deg" lines, then for each the reads of positions 0..298 and of the last one
   long long off; int deg;
   while (std::scanf("%lld %d", &off, &deg) == 2)
     for (int p = 0; p < 300; ++p)
-      std::printf("%lld\n", (long long)(scan::row_start(off, deg) + scan::row_position(p, deg)));
+      std::printf("%lld\n", (long long)(scan::row_start(off, deg) + scan::row_position(p < 299 ? p : 0x7fffffff, deg)));
 }
 """
 
