@@ -166,6 +166,10 @@ scan_status scan_set_allocator(scan_alloc_fn alloc, scan_release_fn release, voi
  * returns; a device-resident one is read until `stream` passes the build, so
  * free it in stream order on `stream` (or with hipFree) and do not write it
  * from another stream before then.
+ * Device memory beside the index is temporary. The product over hub rows and,
+ * with several id windows, ids numbered without the isolated vertices take
+ * some where it can be had, after what the build needs; where it cannot, the
+ * build goes on without them.
  * Errors: SCAN_EINVAL (null g/out/pointers with n > 0, n < 0, nnz < 0, odd
  * nnz, offset_bits not 32/64, unknown kind or flag, n or nnz too large for
  * int32 ids / the chosen offsets), SCAN_EGRAPH (SCAN_VALIDATE only),

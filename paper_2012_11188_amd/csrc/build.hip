@@ -639,9 +639,11 @@ class HostPack {
     if (!v.empty()) std::memcpy(buf_.data() + at, v.data(), v.size() * sizeof(T));
     return at;
   }
-  scan_status upload(SharedArena &a, DevArena &tmp, hipStream_t s, unsigned char **dev) {
-    SCAN_TRY(tmp.alloc(dev, (int64_t)std::max<size_t>(buf_.size(), 16)));
-    return upload_pinned(a, *dev, buf_.data(), buf_.size(), s);
+  scan_status alloc(DevArena &tmp, unsigned char **dev) const {
+    return tmp.alloc(dev, (int64_t)std::max<size_t>(buf_.size(), 16));
+  }
+  scan_status upload(SharedArena &a, unsigned char *dev, hipStream_t s) const {
+    return upload_pinned(a, dev, buf_.data(), buf_.size(), s);
   }
   template <class T>
   static const T *at(const unsigned char *dev, size_t off) {
@@ -815,7 +817,10 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
   if (ns && stream_wait(ns, s) != SCAN_OK) ns = nullptr;
   JoinOnExit join_ns{s, ns};
   SortClasses no_cls;
-  if (NNZ > 0) SCAN_TRY(sort_classify(off_u, N, NNZ, tmp, ctl_no, ns ? ns : s, no_cls));
+  if (NNZ > 0) {
+    SCAN_TRY(sort_reserve(N, NNZ, tmp, ctl_no, no_cls));
+    SCAN_TRY(sort_classify(off_u, ns ? ns : s, no_cls));
+  }
   // a2: the ownership plan needs only the degrees; its counts come back with
   // the maximum degrees. (The classification before it runs beside it; after
   // it, it ran into the placement of the intersection's persistent workgroups:
@@ -897,6 +902,16 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     if (flags & SCAN_KEEP_COUNTS) counts = (int32_t *)(block + o_counts);
   }
   if (!sims) SCAN_TRY(tmp.alloc(&sims, NNZ));
+  // What the core order needs of the same sizes: its unsorted entries and the
+  // vertices by rank.
+  double *co_key = nullptr;
+  int32_t *co_id = nullptr;
+  RankInfo *d_sv = nullptr;
+  if (NNZ > 0) {
+    SCAN_TRY(tmp.alloc(&co_key, NNZ));
+    SCAN_TRY(tmp.alloc(&co_id, NNZ));
+    SCAN_TRY(tmp.alloc(&d_sv, N));
+  }
 
   // Tiles of the core-order kernels (they need no maximum degree): built
   // here, while the device runs the degree pass and the plan.
@@ -936,13 +951,14 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
                 *d_ng = nullptr, *d_obase = nullptr, *d_vbase = nullptr, *d_ebase = nullptr;
   const VTile *d_vt = nullptr;
   const RTile *d_rt = nullptr;
+  unsigned char *dpack = nullptr;
   int64_t *d_corel = nullptr;  // per-graph core-order offsets (the indexes' co_off)
-  // The tables go to the device in one copy on stream st, and the core-order
-  // offsets are allocated: after the intersection is launched, so that
-  // nothing stands between the read-back above and that launch.
-  auto upload_tables = [&](hipStream_t st) -> scan_status {
-    unsigned char *dpack;
-    SCAN_TRY(pack.upload(*arena, tmp, st, &dpack));
+  // The memory of the tables and of the core-order offsets, and one copy of
+  // the tables to the device on stream st: after the intersection is
+  // launched, so that nothing stands between the read-back above and that
+  // launch.
+  auto alloc_tables = [&]() -> scan_status {
+    SCAN_TRY(pack.alloc(tmp, &dpack));
     d_hbase = pack.at<int64_t>(dpack, p_hbase);
     d_Ebase = pack.at<int64_t>(dpack, p_Ebase);
     d_cobase = pack.at<int64_t>(dpack, p_cobase);
@@ -965,55 +981,53 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     const hipStream_t cs = ns ? ns : s;
     JoinOnExit join_cs{s, cs};
     int32_t *d_hist, *d_cursor, *d_tiles_of;
-    RankInfo *d_sv;
-    int64_t *d_E, *d_seg, *d_nz, *d_tile_first, *scan_ws;
-    double *co_key;
-    int32_t *co_id;
+    int64_t *d_E, *d_seg, *d_nz, *d_tile_first, *scan_ws, *P, *X, *XS, *ws;
     SortClasses co_cls;
     const int64_t nrt = (int64_t)rt.size();
-    auto co_prep = [&]() -> scan_status {  // cs is ordered after the degrees
-      if (G == 1 && N <= kPrepOneN && hdmax[0] <= kPrepOneDeg) {
-        SCAN_TRY(arena_alloc(*arena, &d_corel, cobase[G]));
-        SCAN_TRY(tmp.alloc(&d_seg, segbase[G] + 1));
-        SCAN_TRY(tmp.alloc(&d_nz, 1));
-        SCAN_TRY(tmp.alloc(&d_sv, N));
-        SCAN_TRY(tmp.alloc(&d_tile_first, nrt + 1));
-        SCAN_TRY(tmp.alloc(&co_key, NNZ));
-        SCAN_TRY(tmp.alloc(&co_id, NNZ));
-        // one graph: every base is zero
-        d_vbase = d_ebase = d_cobase = (const int64_t *)ctl_zero;
-        k_co_prep_one<<<1, kPrepOneThreads, 0, cs>>>(deg, off_u, (int32_t)N, NNZ, (int32_t)hdmax[0], d_corel, d_seg,
-                                                     d_nz, d_sv, (int32_t)nrt, d_tile_first);
-        return sort_classify(d_seg, segbase[G], NNZ, tmp, ctl_co, cs, co_cls);
-      }
-      SCAN_TRY(upload_tables(cs));
-      SCAN_TRY(tmp.alloc(&d_hist, 2 * hbase[G]));  // and the cursors
-      d_cursor = d_hist + hbase[G];
-      SCAN_TRY(tmp.alloc(&d_E, Ebase[G]));
+    const bool prep_one = G == 1 && N <= kPrepOneN && hdmax[0] <= kPrepOneDeg;
+    bool co_reserved = false;
+    auto co_reserve = [&]() -> scan_status {  // the memory of co_prep
+      if (co_reserved) return SCAN_OK;
       SCAN_TRY(tmp.alloc(&d_seg, segbase[G] + 1));
       SCAN_TRY(tmp.alloc(&d_nz, G));
-      SCAN_TRY(tmp.alloc(&d_sv, std::max<int64_t>(N, 1)));
-      SCAN_TRY(tmp.alloc(&d_tiles_of, std::max<int64_t>(nrt, 1)));
       SCAN_TRY(tmp.alloc(&d_tile_first, nrt + 1));
-      SCAN_TRY(tmp.alloc(&scan_ws, scan_workspace_elems(std::max<int64_t>(nrt, 1))));
-      SCAN_TRY(tmp.alloc(&co_key, NNZ));
-      SCAN_TRY(tmp.alloc(&co_id, NNZ));
-      SCAN_HIP_TRY(hipMemsetAsync(d_hist, 0, (size_t)hbase[G] * 8, cs));
-      if (!vt.empty())
-        k_graph_hist<<<grid_for((int64_t)vt.size(), 1, 8192), 256, 0, cs>>>(d_vt, (int64_t)vt.size(), deg, d_hbase,
-                                                                           d_dmax, d_hist);
-      {
-        int64_t *P, *X, *XS, *ws;
+      if (prep_one) {
+        SCAN_TRY(arena_alloc(*arena, &d_corel, cobase[G]));
+        // one graph: every base is zero
+        d_vbase = d_ebase = d_cobase = (const int64_t *)ctl_zero;
+      } else {
+        SCAN_TRY(alloc_tables());
+        SCAN_TRY(tmp.alloc(&d_hist, 2 * hbase[G]));  // and the cursors
+        d_cursor = d_hist + hbase[G];
+        SCAN_TRY(tmp.alloc(&d_E, Ebase[G]));
+        SCAN_TRY(tmp.alloc(&d_tiles_of, std::max<int64_t>(nrt, 1)));
+        SCAN_TRY(tmp.alloc(&scan_ws, scan_workspace_elems(std::max<int64_t>(nrt, 1))));
         SCAN_TRY(tmp.alloc(&P, hbase[G] + 1));
         SCAN_TRY(tmp.alloc(&X, std::max<int64_t>(segbase[G], 1)));
         SCAN_TRY(tmp.alloc(&XS, segbase[G] + 1));
         SCAN_TRY(tmp.alloc(&ws, scan_workspace_elems(std::max<int64_t>(hbase[G], segbase[G]))));
-        SCAN_TRY(exclusive_scan(d_hist, P, hbase[G], ws, cs));
-        k_co_counts<<<grid_for(Ebase[G], 256), 256, 0, cs>>>(P, d_hbase, d_Ebase, d_segbase, d_ng, G, d_E, X);
-        SCAN_TRY(exclusive_scan64(X, XS, segbase[G], ws, cs));
-        k_co_offsets<<<grid_for(cobase[G], 256), 256, 0, cs>>>(XS, d_cobase, d_segbase, d_ebase, d_hbase, d_hist, d_ng,
-                                                              G, d_corel, d_seg, d_nz);
       }
+      SCAN_TRY(sort_reserve(segbase[G], NNZ, tmp, ctl_co, co_cls));  // the core-order segments
+      co_reserved = true;
+      return SCAN_OK;
+    };
+    auto co_prep = [&]() -> scan_status {  // cs is ordered after the degrees
+      SCAN_TRY(co_reserve());
+      if (prep_one) {
+        k_co_prep_one<<<1, kPrepOneThreads, 0, cs>>>(deg, off_u, (int32_t)N, NNZ, (int32_t)hdmax[0], d_corel, d_seg,
+                                                     d_nz, d_sv, (int32_t)nrt, d_tile_first);
+        return sort_classify(d_seg, cs, co_cls);
+      }
+      SCAN_TRY(pack.upload(*arena, dpack, cs));
+      SCAN_HIP_TRY(hipMemsetAsync(d_hist, 0, (size_t)hbase[G] * 8, cs));
+      if (!vt.empty())
+        k_graph_hist<<<grid_for((int64_t)vt.size(), 1, 8192), 256, 0, cs>>>(d_vt, (int64_t)vt.size(), deg, d_hbase,
+                                                                           d_dmax, d_hist);
+      SCAN_TRY(exclusive_scan(d_hist, P, hbase[G], ws, cs));
+      k_co_counts<<<grid_for(Ebase[G], 256), 256, 0, cs>>>(P, d_hbase, d_Ebase, d_segbase, d_ng, G, d_E, X);
+      SCAN_TRY(exclusive_scan64(X, XS, segbase[G], ws, cs));
+      k_co_offsets<<<grid_for(cobase[G], 256), 256, 0, cs>>>(XS, d_cobase, d_segbase, d_ebase, d_hbase, d_hist, d_ng,
+                                                            G, d_corel, d_seg, d_nz);
       if (!vt.empty())
         k_co_rank<<<grid_for((int64_t)vt.size(), 1, 8192), 256, 0, cs>>>(d_vt, (int64_t)vt.size(), deg, d_hbase,
                                                                        d_Ebase, d_dmax, d_E, d_cursor, d_ng, d_vbase,
@@ -1022,7 +1036,7 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
         k_co_tiles<<<grid_for(nrt, 256), 256, 0, cs>>>(d_rt, nrt, d_sv, d_vbase, d_nz, d_tiles_of);
         SCAN_TRY(exclusive_scan(d_tiles_of, d_tile_first, nrt, scan_ws, cs));
       }
-      return sort_classify(d_seg, segbase[G], NNZ, tmp, ctl_co, cs, co_cls);  // the core-order segments
+      return sort_classify(d_seg, cs, co_cls);
     };
 
     // a2-a4: ownership plan, intersection and similarity over the union.
@@ -1045,7 +1059,8 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
       SCAN_TRY(weighted_similarity_all(N, NNZ, off_u, deg, adj_u, w_dev, sims, tmp, s, prof ? &ist : nullptr,
                                        planned ? &plan : nullptr, device, icfg.skip_deg));
     } else {
-      SCAN_TRY(intersect_all(icfg, N, NNZ, off_u, deg, adj_u, kind, sims, counts, device, s, &ist, co_prep, &plan));
+      SCAN_TRY(intersect_all(icfg, N, NNZ, off_u, deg, adj_u, kind, sims, counts, device, s, &ist, co_reserve,
+                             co_prep, &plan));
     }
     if (lsh) SCAN_TRY(lsh_overwrite(lsh_dev, N, NNZ, off_u, adj_u, weighted ? w_dev : nullptr, kind, sims, tmp, s));
     mark(3);
@@ -1074,7 +1089,8 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     mark(5);
   } else {
     // no edges: every co_off is zero
-    SCAN_TRY(upload_tables(s));
+    SCAN_TRY(alloc_tables());
+    SCAN_TRY(pack.upload(*arena, dpack, s));
     SCAN_HIP_TRY(hipMemsetAsync(d_corel, 0, (size_t)cobase[G] * 8, s));
     for (int k = 2; k < 10; ++k) mark(k);
   }

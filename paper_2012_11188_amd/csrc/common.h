@@ -197,16 +197,16 @@ void pinned_give(const PinnedBlock &b);
 void *pinned_get();
 void pinned_put(void *p);
 
-// A segmented sort in two steps. sort_classify enqueues, on stream s, the
-// classification of the segments [seg_off[i], seg_off[i+1]) (total elements)
-// by length (the class lists live in `arena`, which must outlive sort_run; the
-// class sizes in `stats`, kSortStatsBytes of zeroed device memory), which
-// also writes the class sizes to pinned host memory. sort_run then waits on
-// the host for those sizes (they size the grids; classified early, they are
-// there before they are needed) and enqueues on s the sort of every segment
-// by key descending, id ascending (ids distinct within a segment), reading
-// key_in/id_in and writing key_out/id_out (no aliasing). s and the stream of
-// sort_classify may differ.
+// A segmented sort in three steps. sort_reserve takes the memory of the class
+// lists from `arena`, which must outlive sort_run (nseg segments, total
+// elements; the class sizes go to `stats`, kSortStatsBytes of zeroed device
+// memory). sort_classify enqueues, on stream s, the classification of the
+// segments [seg_off[i], seg_off[i+1]) by length, which also writes the class
+// sizes to pinned host memory. sort_run then waits on the host for those sizes
+// (they size the grids; classified early, they are there before they are
+// needed) and enqueues on s the sort of every segment by key descending, id
+// ascending (ids distinct within a segment), reading key_in/id_in and writing
+// key_out/id_out (no aliasing). s and the stream of sort_classify may differ.
 constexpr size_t kSortStatsBytes = 64;
 struct SortClasses {
   int64_t nseg = 0;
@@ -224,11 +224,11 @@ struct SortClasses {
   SortClasses &operator=(const SortClasses &) = delete;
   ~SortClasses();
 };
-scan_status sort_classify(const int64_t *seg_off, int64_t nseg, int64_t total, DevArena &arena, void *stats,
-                          hipStream_t s, SortClasses &c);
+scan_status sort_reserve(int64_t nseg, int64_t total, DevArena &arena, void *stats, SortClasses &c);
+scan_status sort_classify(const int64_t *seg_off, hipStream_t s, SortClasses &c);
 scan_status sort_run(const SortClasses &c, const int64_t *seg_off, int64_t total, const double *key_in,
                      const int32_t *id_in, double *key_out, int32_t *id_out, hipStream_t s);
-// Both steps on s.
+// All steps on s.
 scan_status segmented_sort(const int64_t *seg_off, int64_t nseg, int64_t total,
                            const double *key_in, const int32_t *id_in, double *key_out,
                            int32_t *id_out, hipStream_t s);

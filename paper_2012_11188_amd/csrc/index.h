@@ -138,12 +138,15 @@ scan_status prepare_hubs(const HubShape &shape, int64_t n, const int64_t *off, c
 // written into both CSR slots of sims (and counts if non-null).
 // after_launch (may be empty) runs on the host once every intersection
 // kernel is enqueued, so that the host enqueues other work (on streams it has
-// ordered itself) while the device intersects. plan is one made by
+// ordered itself) while the device intersects. reserve (may be empty) takes
+// the memory that after_launch needs: it runs before memory is taken that the
+// intersection can do without, and may run again or not at all. plan is one made by
 // intersect_plan on s with the same cfg, n, nnz and deg, whose counts are on
 // the host.
 scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, const int64_t *off,
                           const int32_t *deg, const int32_t *adj, int kind, double *sims,
                           int32_t *counts, int device, hipStream_t s, IntersectStats *stats,
+                          const std::function<scan_status()> &reserve = {},
                           const std::function<scan_status()> &after_launch = {},
                           const IntersectPlan *plan = nullptr);
 

@@ -1137,10 +1137,9 @@ scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, c
 scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, const int64_t *off,
                           const int32_t *deg, const int32_t *adj, int kind, double *sims,
                           int32_t *counts, int device, hipStream_t s, IntersectStats *stats,
+                          const std::function<scan_status()> &reserve,
                           const std::function<scan_status()> &after_launch, const IntersectPlan *plan) {
-  if (nnz == 0) {
-      return after_launch ? after_launch() : SCAN_OK;
-  }
+  if (nnz == 0) return after_launch ? after_launch() : SCAN_OK;
   int lds_max = 65536, cus = 256;
   (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
@@ -1152,8 +1151,12 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   // lets the hardware balance the uneven rows, which persistent grids with a
   // static split do not.
   const PlanCounts h = *(const PlanCounts *)plan->host;
-  DevArena tmp(s);
-  int wbits = window_bits(cfg, n, lds_max);
+  // Memory that the build can do without (ids numbered anew, the hub product)
+  // is taken after what it needs, and given back where that is refused: a
+  // build fits wherever it would fit without them.
+  DevArena tmp(s), ids_mem(s), hub_mem(s);
+  const int wbits_all = window_bits(cfg, n, lds_max);
+  int wbits = wbits_all;
   auto windows = [](int64_t ids, int bits) { return (int32_t)((ids + ((int64_t)1 << bits) - 1) >> bits); };
   int32_t nwin = windows(n, wbits);
   int32_t *wt = nullptr, *renamed = nullptr;
@@ -1168,16 +1171,20 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
     const int rbits = window_bits(cfg, h.rows, lds_max);
     int32_t *flags;
     int64_t *ws;
-    if (windows(h.rows, rbits) < nwin && tmp.alloc(&renamed, nnz) == SCAN_OK && tmp.alloc(&flags, n) == SCAN_OK &&
-        tmp.alloc(&cid, n + 1) == SCAN_OK && tmp.alloc(&ws, scan_workspace_elems(n)) == SCAN_OK) {
-      k_id_flags<<<grid_for(n, 256), 256, 0, s>>>(deg, n, flags);
-      SCAN_TRY(exclusive_scan(flags, cid, n, ws, s));
-      k_rename<<<grid_for(nnz, 1024), 256, 0, s>>>(adj, nnz, cid, h.rows, renamed);
-      wbits = rbits;
-      nwin = windows(h.rows, rbits);
-    } else {
-      renamed = nullptr;
-      cid = nullptr;
+    if (windows(h.rows, rbits) < nwin) {
+      if (reserve) SCAN_TRY(reserve());
+      if (ids_mem.alloc(&renamed, nnz) == SCAN_OK && ids_mem.alloc(&flags, n) == SCAN_OK &&
+          ids_mem.alloc(&cid, n + 1) == SCAN_OK && ids_mem.alloc(&ws, scan_workspace_elems(n)) == SCAN_OK) {
+        k_id_flags<<<grid_for(n, 256), 256, 0, s>>>(deg, n, flags);
+        SCAN_TRY(exclusive_scan(flags, cid, n, ws, s));
+        k_rename<<<grid_for(nnz, 1024), 256, 0, s>>>(adj, nnz, cid, h.rows, renamed);
+        wbits = rbits;
+        nwin = windows(h.rows, rbits);
+      } else {
+        ids_mem.release();
+        renamed = nullptr;
+        cid = nullptr;
+      }
     }
   }
   // Common neighbours among hubs by matrix product, where that saves enough.
@@ -1186,21 +1193,39 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   HubShape shape;
   if (h.big && plan->one_graph && cfg.skip_deg == 0x7fffffff && (nwin == 1 || (table && nwin <= kHubMaxWindows)))
     shape = choose_hubs(h, nnz, nwin == 1);
-  if (h.big && nwin > 1) {
+  if (shape.rows && reserve) SCAN_TRY(reserve());
+  if (h.big && table) {
     // The window table, unless it would exceed kMaxWindowTable bytes or the
     // searched ranges are asked for; then chunks search them per window.
     // The rows of the hubs' rests follow those of the vertices.
-    if (table && (size_t)(nwin + 1) * (size_t)n * 4 <= kMaxWindowTable) {
-      SCAN_TRY(tmp.alloc(&wt, (int64_t)(nwin + 1) * (n + shape.rows)));
-      k_window_table<<<grid_for(n * kWave, 256), 256, 0, s>>>(off, renamed ? renamed : adj, n, wbits, nwin, wt);
+    auto table_for = [&](int64_t rows) -> scan_status {
+      if ((size_t)(nwin + 1) * (size_t)n * 4 > kMaxWindowTable) return SCAN_OK;
+      return tmp.alloc(&wt, (int64_t)(nwin + 1) * rows);
+    };
+    scan_status st = table_for(n + shape.rows);
+    if (st == SCAN_ENOMEM && shape.rows) {
+      shape = HubShape{};
+      st = table_for(n);
     }
+    if (st == SCAN_ENOMEM && renamed) {
+      ids_mem.release();
+      renamed = nullptr;
+      cid = nullptr;
+      wbits = wbits_all;
+      nwin = windows(n, wbits);
+      st = table_for(n);
+    }
+    SCAN_TRY(st);
+    if (wt) k_window_table<<<grid_for(n * kWave, 256), 256, 0, s>>>(off, renamed ? renamed : adj, n, wbits, nwin, wt);
   }
   if (h.big) k_vertex_records<<<grid_for(n, 256, 4096), 256, 0, s>>>(off, n, plan->records);
   HubView hub;
   if (shape.rows && (nwin == 1 || wt) &&
       prepare_hubs(shape, n, off, deg, adj, renamed ? renamed : adj, wbits, nwin,
-                   wt ? wt + (int64_t)(nwin + 1) * n : nullptr, plan->records, tmp, s, &hub) != SCAN_OK)
-    hub = HubView{};  // no memory for it: every row is streamed whole
+                   wt ? wt + (int64_t)(nwin + 1) * n : nullptr, plan->records, hub_mem, s, &hub) != SCAN_OK) {
+    hub_mem.release();  // no memory for it: every row is streamed whole
+    hub = HubView{};
+  }
   if (big_lds_bytes(wbits, cfg.spc) > (size_t)lds_max) return fail(SCAN_EINVAL, "chunk size too large for LDS");
   if (stats) {
     stats->wbits = wbits;

@@ -954,7 +954,7 @@ SortClasses::~SortClasses() {
   pinned_put(host);
 }
 
-scan_status sort_plan(int64_t nseg, int64_t total, DevArena &arena, void *stats, SortClasses &c) {
+scan_status sort_reserve(int64_t nseg, int64_t total, DevArena &arena, void *stats, SortClasses &c) {
   static_assert(sizeof(SortStats) <= kPinnedBlock, "class sizes fit a pinned block");
   c.nseg = nseg;
   if (nseg <= 0) return SCAN_OK;
@@ -971,22 +971,15 @@ scan_status sort_plan(int64_t nseg, int64_t total, DevArena &arena, void *stats,
   return SCAN_OK;
 }
 
-scan_status sort_classified(SortClasses &c, hipStream_t s) {
+scan_status sort_classify(const int64_t *seg_off, hipStream_t s, SortClasses &c) {
   c.stream = s;
   if (c.nseg <= 0) return SCAN_OK;
   SCAN_HIP_TRY(hipEventCreateWithFlags(&c.ready, hipEventDisableTiming));
-  SCAN_HIP_TRY(hipEventRecord(c.ready, s));
-  return SCAN_OK;
-}
-
-scan_status sort_classify(const int64_t *seg_off, int64_t nseg, int64_t total, DevArena &arena, void *stats,
-                          hipStream_t s, SortClasses &c) {
-  SCAN_TRY(sort_plan(nseg, total, arena, stats, c));
-  if (nseg > 0)
-    k_classify<<<grid_for(nseg, kClassTile, 2048), 256, 0, s>>>(seg_off, nseg, c.lists, nseg, (SortStats *)stats,
+  k_classify<<<grid_for(c.nseg, kClassTile, 2048), 256, 0, s>>>(seg_off, c.nseg, c.lists, c.nseg, (SortStats *)c.stats,
                                                                 c.big_tiles_of, c.tile_first, c.tile_seg, c.max_tiles,
                                                                 (SortStats *)c.host);
-  return sort_classified(c, s);
+  SCAN_HIP_TRY(hipEventRecord(c.ready, s));
+  return SCAN_OK;
 }
 
 scan_status segmented_sort(const int64_t *seg_off, int64_t nseg, int64_t total,
@@ -998,7 +991,8 @@ scan_status segmented_sort(const int64_t *seg_off, int64_t nseg, int64_t total,
   unsigned char *stats;
   SCAN_TRY(arena.alloc(&stats, kSortStatsBytes));
   SCAN_HIP_TRY(hipMemsetAsync(stats, 0, kSortStatsBytes, s));
-  SCAN_TRY(sort_classify(seg_off, nseg, total, arena, stats, s, c));
+  SCAN_TRY(sort_reserve(nseg, total, arena, stats, c));
+  SCAN_TRY(sort_classify(seg_off, s, c));
   return sort_run(c, seg_off, total, key_in, id_in, key_out, id_out, s);
 }
 

@@ -10,7 +10,7 @@ import graphgen
 import oracle
 import paper_2012_11188_amd as scan
 from alloc_hooks import hooks
-from gpu_util import gpu_build
+from gpu_util import assert_index_equal, device_csr, gpu_build
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +44,58 @@ def test_batch_without_all_workspaces(warm, refused):
             torch.cuda.synchronize()
             assert np.array_equal(got.cpu().numpy(), want)
         gix.free()
+
+
+def least_memory(h, run, check):
+    """The least peak of `run` over refusals of memory that it can do without
+    (one call after the other is refused for good where the run still succeeds
+    and holds less); every answer is checked."""
+    h.start()
+    check(run())
+    refused, least, calls, k = [], h.peak, h.calls, 0
+    while k < calls:
+        h.start(refuse=refused + [k])
+        try:
+            got = run()
+        except scan.ScanError as e:
+            assert e.status == scan.SCAN_ENOMEM
+        else:
+            check(got)
+            if h.peak < least:
+                refused, least, calls = refused + [k], h.peak, h.calls
+        assert h.held == 0
+        k += 1
+    return least, len(refused)
+
+
+# A build succeeds within the memory that it needs without the hub product and
+# without ids numbered anew: what it needs is taken first. Dense rows of at
+# most 4096 slots, whose sorts take no memory of their own, so that the peak is
+# the intersection's; ids in one window, several, and ranges searched.
+@pytest.mark.parametrize("n,tune", [(2400, None), (4000, {"wbits": 10}),
+                                    (4000, {"wbits": 10, "flags": scan.SCAN_TUNE_SEARCH_WINDOWS})])
+def test_builds_fit_without_optional_memory(n, tune):
+    import torch
+
+    used = 2400
+    rng = np.random.default_rng(n)
+    place = np.sort(rng.permutation(n)[:used])
+    u, v = np.nonzero(np.triu(rng.random((used, used)) < 0.6, 1))
+    g = graphgen.from_edges(n, np.stack([place[u], place[v]], 1).astype(np.int32))
+    oix = oracle.build_index(g, oracle.COSINE, threads=8)
+    csr = device_csr(g)
+
+    def run():
+        ix = scan.scan_build_index(*csr, scan.COSINE, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
+        torch.cuda.synchronize()
+        return ix
+
+    def check(ix):
+        assert_index_equal(ix, oix, g)
+        ix.free()
+
+    with hooks() as h:
+        least, refused = least_memory(h, run, check)
+        assert refused, "nothing that the build can do without"
+        h.start(budget=least)
+        check(run())
