@@ -355,9 +355,10 @@ scan_status scan_query_modularity(const scan_index *ix, const int32_t *membershi
 /* The parameter selection of Section 7.3.4: the modularity (as above) of
  * the clustering of each (mu[i], eps[i]), i < count (host arrays), run as
  * batched queries of up to `batch` (1..256) on `stream`; q[i] (host) is
- * written. Synchronous. Device memory: batch * n * 12 + n * 128 + nnz / 32
- * + count * 24 bytes (batch * n * 4 + n * 8 + count * 24 where no more can be
- * had). Errors: SCAN_EINVAL for a null pointer, a bad batch, or an
+ * written. Synchronous. Device memory, beside the queries' workspaces: batch *
+ * n * 12 + n * 128 + nnz / 32 + count * 24 bytes, or batch * n * 4 + n * 8 +
+ * count * 24 where no more can be had; chunks of 32 MiB hold what is smaller
+ * than 8. Errors: SCAN_EINVAL for a null pointer, a bad batch, or an
  * invalid (mu, eps) (nothing is run then). */
 scan_status scan_sweep_modularity(const scan_index *ix, int32_t count, const int32_t *mu,
                                   const double *eps, int32_t batch, double *q, void *stream);

@@ -497,6 +497,13 @@ scan_status scan_sweep_modularity(const scan_index *ix, int32_t count, const int
   int32_t *memb;
   int64_t *dsum, *terms;
   SCAN_TRY(tmp.alloc(&memb, (int64_t)B * n));
+  SCAN_TRY(tmp.alloc(&terms, (int64_t)3 * count));
+  // The queries' workspaces too before anything that the sweep can do without.
+  {
+    std::vector<scan_index::PooledSlot *> got;
+    SCAN_TRY(acquire_slots(const_cast<scan_index *>(ix), B, s, got));
+    release_slots(const_cast<scan_index *>(ix), got, s);
+  }
   // Degree sums for a whole batch of clusterings, and the workspace that
   // scores many at once, where memory allows; else one clustering at a time.
   ModularitySweep ms;
@@ -505,7 +512,6 @@ scan_status scan_sweep_modularity(const scan_index *ix, int32_t count, const int
     D = 1;
     SCAN_TRY(tmp.alloc(&dsum, n));
   }
-  SCAN_TRY(tmp.alloc(&terms, (int64_t)3 * count));
   const bool many = D > 1 && plan_modularity_sweep(ix, tmp, s, &ms) == SCAN_OK;
   zero64(dsum, (int64_t)D * n, s);
   zero64(terms, (int64_t)3 * count, s);

@@ -46,23 +46,37 @@ def test_batch_without_all_workspaces(warm, refused):
         gix.free()
 
 
-def least_memory(h, run, check):
+def attempt(h, setup, run, refuse=(), budget=None):
+    """run(setup()) with the hooks' limits on the run alone."""
+    import torch
+
+    given = setup()
+    torch.cuda.synchronize()
+    h.start(refuse, budget)
+    try:
+        got = run(given)
+        torch.cuda.synchronize()
+        return got
+    finally:
+        h.refuse, h.budget = frozenset(), None
+
+
+def least_memory(h, setup, run, check):
     """The least peak of `run` over refusals of memory that it can do without
     (one call after the other is refused for good where the run still succeeds
-    and holds less); every answer is checked."""
-    h.start()
-    check(run())
+    and holds less), and the number of those; every answer is checked."""
+    check(attempt(h, setup, run))
     refused, least, calls, k = [], h.peak, h.calls, 0
     while k < calls:
-        h.start(refuse=refused + [k])
         try:
-            got = run()
+            got = attempt(h, setup, run, refused + [k])
         except scan.ScanError as e:
             assert e.status == scan.SCAN_ENOMEM
         else:
+            peak, made = h.peak, h.calls
             check(got)
-            if h.peak < least:
-                refused, least, calls = refused + [k], h.peak, h.calls
+            if peak < least:
+                refused, least, calls = refused + [k], peak, made
         assert h.held == 0
         k += 1
     return least, len(refused)
@@ -75,8 +89,6 @@ def least_memory(h, run, check):
 @pytest.mark.parametrize("n,tune", [(2400, None), (4000, {"wbits": 10}),
                                     (4000, {"wbits": 10, "flags": scan.SCAN_TUNE_SEARCH_WINDOWS})])
 def test_builds_fit_without_optional_memory(n, tune):
-    import torch
-
     used = 2400
     rng = np.random.default_rng(n)
     place = np.sort(rng.permutation(n)[:used])
@@ -85,17 +97,42 @@ def test_builds_fit_without_optional_memory(n, tune):
     oix = oracle.build_index(g, oracle.COSINE, threads=8)
     csr = device_csr(g)
 
-    def run():
-        ix = scan.scan_build_index(*csr, scan.COSINE, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
-        torch.cuda.synchronize()
-        return ix
+    def run(_):
+        return scan.scan_build_index(*csr, scan.COSINE, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
 
     def check(ix):
         assert_index_equal(ix, oix, g)
         ix.free()
 
     with hooks() as h:
-        least, refused = least_memory(h, run, check)
+        least, refused = least_memory(h, lambda: None, run, check)
         assert refused, "nothing that the build can do without"
-        h.start(budget=least)
-        check(run())
+        check(attempt(h, lambda: None, run, budget=least))
+
+
+# A sweep succeeds within the memory that it needs for one clustering at a
+# time: the queries' workspaces are taken before the tables that score many.
+@pytest.mark.parametrize("batch", [5, 32])
+def test_sweeps_fit_without_optional_memory(batch):
+    g = graphgen.sbm(120000, 300, 0.02, 0.00001, 7)
+    grid = [(mu, eps) for mu in (2, 3, 5, 9) for eps in (0.05, 0.1, 0.15, 0.2, 0.25, 0.3, 0.4, 0.5)]
+    csr = device_csr(g)
+
+    def run(ix):  # (an index without workspaces)
+        try:
+            return scan.scan_sweep_modularity(ix, [m for m, _ in grid], [e for _, e in grid], batch=batch)
+        finally:
+            ix.free()
+
+    want = []
+
+    def check(q):
+        if not want:
+            want.append(q)
+            assert len(np.unique(q)) > 4
+        assert np.array_equal(q, want[0])
+
+    with hooks() as h:
+        least, refused = least_memory(h, lambda: scan.scan_build_index(*csr), run, check)
+        assert refused, "nothing that the sweep can do without"
+        check(attempt(h, lambda: scan.scan_build_index(*csr), run, budget=least))
