@@ -827,6 +827,7 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
   // R-MAT-20 7.08 instead of 6.96 ms a build.)
   IntersectPlan plan;
   plan.one_graph = G == 1;
+  plan.weighted = weighted;
   const bool planned = NNZ > 0 && (!weighted || weighted_planned(N, NNZ));
   const IntersectConfig pcfg = weighted ? weighted_config(cfg) : cfg;
   if (planned) {
@@ -1062,6 +1063,11 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
       SCAN_TRY(intersect_all(icfg, N, NNZ, off_u, deg, adj_u, kind, sims, counts, device, s, &ist, co_reserve,
                              co_prep, &plan));
     }
+    // (s is past the kernels that read the plan; the sorts need more memory
+    // than the intersection, unless all rows and segments are short)
+    tmp.drop(plan.lists);
+    tmp.drop(plan.records);
+    tmp.drop(plan.big_list);
     if (lsh) SCAN_TRY(lsh_overwrite(lsh_dev, N, NNZ, off_u, adj_u, weighted ? w_dev : nullptr, kind, sims, tmp, s));
     mark(3);
     if (prof) {

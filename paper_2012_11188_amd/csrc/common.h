@@ -109,14 +109,14 @@ class DevArena {
     if (bytes >= kChunk / 4) {  // large: its own allocation
       void *q = dev_alloc(bytes, stream_);
       if (!q) return fail(SCAN_ENOMEM, "device allocation of %zu bytes failed", bytes);
-      items_.push_back({q, bytes});
+      items_.push_back({q, bytes, false});
       *p = (T *)q;
       return SCAN_OK;
     }
     if (used_ + bytes > cap_) {  // new chunk
       void *q = dev_alloc(kChunk, stream_);
       if (!q) return fail(SCAN_ENOMEM, "device allocation of %zu bytes failed", kChunk);
-      items_.push_back({q, kChunk});
+      items_.push_back({q, kChunk, true});
       cur_ = (unsigned char *)q;
       used_ = 0;
       cap_ = kChunk;
@@ -124,6 +124,16 @@ class DevArena {
     *p = (T *)(cur_ + used_);
     used_ += bytes;
     return SCAN_OK;
+  }
+  // Gives p back early where it has an allocation of its own (what is carved
+  // from a chunk stays); the stream is past all work on it.
+  void drop(const void *p) {
+    for (size_t i = 0; i < items_.size(); ++i)
+      if (items_[i].p == p && !items_[i].chunk) {
+        dev_free(items_[i].p, items_[i].bytes, stream_);
+        items_.erase(items_.begin() + i);
+        return;
+      }
   }
   void release() {
     for (auto &it : items_) dev_free(it.p, it.bytes, stream_);
@@ -136,6 +146,7 @@ class DevArena {
   struct Item {
     void *p;
     size_t bytes;
+    bool chunk;
   };
   hipStream_t stream_;
   std::vector<Item> items_;

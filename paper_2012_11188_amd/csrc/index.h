@@ -87,6 +87,7 @@ struct BigChunk {
 struct IntersectPlan {
   int64_t n = 0, nnz = 0;
   bool one_graph = false;  // set by the caller
+  bool weighted = false;   // the weighted kernels will run (set by the caller): no records
   SmallOwner *lists = nullptr;          // n entries: the light ones first, the heavy ones at the end
   VertexRecord *records = nullptr;      // n entries, for the intersection to fill
   void *big_list = nullptr, *counts = nullptr;  // device chunk list and counts

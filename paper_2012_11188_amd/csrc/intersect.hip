@@ -1123,7 +1123,7 @@ scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, c
   BigChunk *big_list;
   PlanCounts *pc = (PlanCounts *)counts;
   SCAN_TRY(arena.alloc(&p.lists, n));
-  SCAN_TRY(arena.alloc(&p.records, n));
+  if (!p.weighted) SCAN_TRY(arena.alloc(&p.records, n));
   SCAN_TRY(arena.alloc(&big_list, nnz / cfg.spc + std::min(n, nnz / cfg.small_max) + 1));
   p.big_list = big_list;
   p.counts = counts;

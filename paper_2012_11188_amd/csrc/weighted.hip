@@ -852,6 +852,7 @@ scan_status weighted_similarity_all(int64_t n, int64_t nnz, const int64_t *off, 
       k_w_owner<<<(unsigned)units, kWThreads, 0, s>>>(off, deg, adj, w, S, row_of, n, nnz, sims, skip_deg);
     }
     SCAN_HIP_TRY(hipGetLastError());
+    tmp.drop(S);
   } else {
     SCAN_TRY(mark(stats ? stats->ev_small_end : nullptr));
     SCAN_TRY(mark(stats ? stats->ev_big_begin : nullptr));

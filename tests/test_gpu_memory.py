@@ -136,3 +136,25 @@ def test_sweeps_fit_without_optional_memory(batch):
         least, refused = least_memory(h, lambda: scan.scan_build_index(*csr), run, check)
         assert refused, "nothing that the sweep can do without"
         check(attempt(h, lambda: scan.scan_build_index(*csr), run, budget=least))
+
+
+# Most of a large build's memory is what its sorts hold, 68 bytes per slot with
+# the index (similarities by slot, by row and by segment, and the merges' two
+# copies); beside them per vertex the offsets (8), degrees (4), ranks (16) and
+# the lists of the row sort (60), and two chunks of 32 MiB. What the
+# intersection alone needs (32 bytes per vertex) is not held then.
+@pytest.mark.parametrize("weighted", [False, True])
+def test_memory_of_a_large_build(weighted):
+    import torch
+
+    n = 1 << 20
+    rng = np.random.default_rng(3)
+    g = graphgen.from_edges(n, rng.integers(0, n, (2 * n, 2)).astype(np.int32))
+    off, adj = device_csr(g)
+    w = torch.rand(g.nnz, dtype=torch.float64, device="cuda")
+    with hooks() as h:
+        h.start()
+        ix = scan.scan_build_index_weighted(off, adj, w) if weighted else scan.scan_build_index(off, adj)
+        torch.cuda.synchronize()
+        assert h.peak <= 68 * g.nnz + (8 + 4 + 16 + 60) * n + 2 * (32 << 20)
+        ix.free()
