@@ -379,6 +379,11 @@ scan_status scan_index_device_ptr(const scan_index *ix, scan_array what, const v
  * finish). SCAN_EINVAL if the index was built without SCAN_PROFILE. */
 scan_status scan_index_build_profile(const scan_index *ix, scan_build_profile *out);
 
+/* Diagnostic: the rows and columns of the matrix product over hub rows that
+ * the index's build formed (0 and 0: none), known once the build call has
+ * returned. SCAN_EINVAL for a null pointer. */
+scan_status scan_index_hub_product(const scan_index *ix, int32_t *rows, int32_t *cols);
+
 /* Frees the index after the work enqueued on its stream completes.
  * NULL is a no-op. */
 void scan_index_free(scan_index *ix);

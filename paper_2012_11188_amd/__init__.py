@@ -87,7 +87,7 @@ EXPORTS = [
     "scan_server_submit_ex", "scan_server_poll", "scan_server_wait", "scan_server_destroy", "scan_last_error",
     "scan_version", "scan_similarity_values", "scan_index_build_profile", "scan_build_index_ex",
     "scan_autotune", "scan_segmented_sort", "scan_query_roles", "scan_query_modularity",
-    "scan_sweep_modularity", "scan_query_noalloc",
+    "scan_sweep_modularity", "scan_query_noalloc", "scan_index_hub_product",
 ]
 
 _lib = None
@@ -142,6 +142,7 @@ def load_library(path: str = LIB_PATH):
         "scan_version": ([], ctypes.c_char_p),
         "scan_similarity_values": ([i32, i64, vp, vp, vp, vp], i32),
         "scan_index_build_profile": ([vp, P(_Profile)], i32),
+        "scan_index_hub_product": ([vp, P(i32), P(i32)], i32),
     }
     for name, (args, res) in sig.items():
         f = getattr(lib, name)
@@ -491,6 +492,14 @@ def scan_index_build_profile(ix: Index) -> dict:
     p = _Profile()
     _check(load_library().scan_index_build_profile(ix._h, ctypes.byref(p)))
     return {name: getattr(p, name) for name, _ in _Profile._fields_}
+
+
+def scan_index_hub_product(ix: Index) -> tuple[int, int]:
+    """Rows and columns of the build's product over hub rows (diagnostic;
+    (0, 0): it formed none)."""
+    rows, cols = ctypes.c_int32(), ctypes.c_int32()
+    _check(load_library().scan_index_hub_product(ix._h, ctypes.byref(rows), ctypes.byref(cols)))
+    return rows.value, cols.value
 
 
 def scan_index_device_ptr(ix: Index, what: int):

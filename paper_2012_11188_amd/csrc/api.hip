@@ -591,6 +591,13 @@ scan_status scan_index_build_profile(const scan_index *ix, scan_build_profile *o
   return SCAN_OK;
 }
 
+scan_status scan_index_hub_product(const scan_index *ix, int32_t *rows, int32_t *cols) {
+  if (!ix || !rows || !cols) return fail(SCAN_EINVAL, "null argument");
+  *rows = ix->hub_rows;
+  *cols = ix->hub_cols;
+  return SCAN_OK;
+}
+
 void scan_index_free(scan_index *ix) {
   if (!ix) return;
   {

@@ -973,6 +973,7 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     return arena_alloc(*arena, &d_corel, cobase[G]);
   };
 
+  IntersectStats ist;
   if (NNZ > 0) {
     // a6, first part: core-order sizes and offsets (from the degree
     // histograms, on the device) and the degree-rank list. These read only the
@@ -1041,7 +1042,6 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     };
 
     // a2-a4: ownership plan, intersection and similarity over the union.
-    IntersectStats ist;
     if (prof) {
       ist.ev_small_begin = prof->ev[6];
       ist.ev_small_end = prof->ev[7];
@@ -1134,6 +1134,8 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     if (counts) ix->counts = counts + ebase[g];
     ix->arena = arena;
     ix->prof = prof;
+    ix->hub_rows = ist.hub_rows;
+    ix->hub_cols = ist.hub_cols;
     ix->bytes = (gs[g].n + 1) * 8 + gs[g].nnz * 24 + (int64_t)(hdmax[g] + 3) * 8 +
                 ((flags & SCAN_KEEP_SIMS) ? gs[g].nnz * 8 : 0) + (counts ? gs[g].nnz * 4 : 0);
     outs[g] = ix;

@@ -30,6 +30,7 @@ struct IntersectConfig {
 struct IntersectStats {
   int32_t wbits = 0;
   int32_t launches = 0;
+  int32_t hub_rows = 0, hub_cols = 0;  // of the product over hub rows (0: none)
   // Optional pinned host int32[4]: receives (light vertices, bitmap chunks,
   // -, heavy vertices) asynchronously, in stream order.
   int32_t *host_counts = nullptr;
@@ -263,6 +264,7 @@ struct scan_index {
   std::shared_ptr<scan::SharedArena> arena;        // owns the arrays above
   std::shared_ptr<scan::BuildProfileEvents> prof;  // SCAN_PROFILE only
   int64_t bytes = 0;                               // device bytes of this index's arrays
+  int32_t hub_rows = 0, hub_cols = 0;              // of the build's hub product
   // Query workspace pool: a slot may be reused once its last use completed
   // (event) or when the new use is on the same stream. The slots of one call
   // share its event.

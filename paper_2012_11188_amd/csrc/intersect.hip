@@ -1220,15 +1220,17 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   }
   if (h.big) k_vertex_records<<<grid_for(n, 256, 4096), 256, 0, s>>>(off, n, plan->records);
   HubView hub;
-  if (shape.rows && (nwin == 1 || wt) &&
-      prepare_hubs(shape, n, off, deg, adj, renamed ? renamed : adj, wbits, nwin,
-                   wt ? wt + (int64_t)(nwin + 1) * n : nullptr, plan->records, hub_mem, s, &hub) != SCAN_OK) {
-    hub_mem.release();  // no memory for it: every row is streamed whole
-    hub = HubView{};
+  if (shape.rows && (nwin == 1 || wt)) {
+    const scan_status st = prepare_hubs(shape, n, off, deg, adj, renamed ? renamed : adj, wbits, nwin,
+                                        wt ? wt + (int64_t)(nwin + 1) * n : nullptr, plan->records, hub_mem, s, &hub);
+    if (st != SCAN_OK && st != SCAN_ENOMEM) return st;
+    if (st == SCAN_ENOMEM) hub_mem.release();  // every row is streamed whole
   }
   if (big_lds_bytes(wbits, cfg.spc) > (size_t)lds_max) return fail(SCAN_EINVAL, "chunk size too large for LDS");
   if (stats) {
     stats->wbits = wbits;
+    stats->hub_rows = hub.rows;
+    stats->hub_cols = hub.rows ? shape.cols : 0;
     stats->launches = (h.small > 0) + (h.heavy > 0) + (h.big > 0);
     if (stats->host_counts) {
       stats->host_counts[0] = h.small;

@@ -150,3 +150,58 @@ def test_small_owner_rows(degree, tune):
     g = graphgen.from_edges(n, np.array(edges, np.int64).astype(np.int32))
     ix = scan.scan_build_index(*device_csr(g), scan.COSINE, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS, tune=tune)
     assert_index_equal(ix, oracle.build_index(g, scan.COSINE, threads=8), g)
+
+
+# The product over hub rows is formed where the cases above mean it to be: all
+# vertices of a dense core are its rows and columns. It is not with searched
+# ranges, several graphs or approximate similarities, nor where its memory is
+# refused; the index is the same. (2037 ids: one window, or two of 1024.)
+@pytest.mark.parametrize("how,tune", [("one", None), ("one", {"wbits": 10}), ("refused", None), ("refused", {"wbits": 10}),
+                                      ("none", {"wbits": 10, "flags": scan.SCAN_TUNE_SEARCH_WINDOWS}),
+                                      ("two", None), ("lsh", None)])
+def test_hub_product_is_formed(how, tune):
+    from alloc_hooks import hooks
+    from gpu_util import device_csr
+
+    core, rim = 1537, 500
+    rng = np.random.default_rng(core)
+    place = rng.permutation(core + rim)
+    u, v = np.nonzero(np.triu(rng.random((core, core)) < 0.7, 1))
+    edges = [np.stack([place[u], place[v]], 1),
+             np.stack([place[core + np.arange(rim)], place[core + (np.arange(rim) + 1) % rim]], 1)]
+    g = graphgen.from_edges(core + rim, np.concatenate(edges).astype(np.int32))
+    csr = device_csr(g)
+    flags = scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS
+    if how == "two":
+        assert [scan.scan_index_hub_product(ix) for ix in scan.scan_build_index_batch([csr, csr])] == [(0, 0)] * 2
+        return
+    if how == "lsh":
+        perm = graphgen.permutation(g.n, 3)
+        import torch
+
+        ix = scan.scan_build_index_lsh(*csr, scan.JACCARD, 64, perm=torch.from_numpy(perm).cuda())
+        assert scan.scan_index_hub_product(ix) == (0, 0)
+        return
+    oix = oracle.build_index(g, oracle.COSINE, threads=8)
+    want = (core, core) if how == "one" else (0, 0)
+    if how != "refused":
+        ix = scan.scan_build_index(*csr, scan.COSINE, flags, tune=tune)
+        assert scan.scan_index_hub_product(ix) == want
+        assert_index_equal(ix, oix, g)
+        return
+    without = 0
+    with hooks() as h:
+        h.start()
+        scan.scan_build_index(*csr, scan.COSINE, flags, tune=tune).free()
+        for k in range(h.calls):
+            h.start(refuse=[k])
+            try:
+                ix = scan.scan_build_index(*csr, scan.COSINE, flags, tune=tune)
+            except scan.ScanError as e:
+                assert e.status == scan.SCAN_ENOMEM
+                continue
+            if scan.scan_index_hub_product(ix) == want:
+                without += 1
+                assert_index_equal(ix, oix, g)
+            ix.free()
+    assert without >= 1
