@@ -244,10 +244,11 @@ scan_status scan_build_index_lsh(const scan_csr *g, scan_sim_kind kind, const sc
  * intersections). Every setting gives the same index bit for bit; they only
  * change speed. A zero field takes its default.
  *   small_max  owners of degree <= small_max use one wavefront each, with
- *              their row in LDS (1..4096; default 256, or 512 above 2^21
- *              vertices when spc is zero too)
+ *              their row in LDS (1..4096; default 256, or 512 where more
+ *              than 2^20 vertices have neighbours and spc is zero too)
  *   spc        row slots per work chunk of a larger owner (1..1024; default
- *              768, or 1024 above 2^21 vertices when small_max is zero too)
+ *              768, or 1024 where more than 2^20 vertices have neighbours and
+ *              small_max is zero too)
  *   wbits      LDS bitmap window of 2^wbits vertex ids for larger owners
  *              (10..24; default 20); lowered to what LDS holds and to the id
  *              space; when the ids span several windows each chunk sweeps the

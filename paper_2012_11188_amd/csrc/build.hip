@@ -81,13 +81,14 @@ constexpr int64_t kPrepTile = 4096;
 
 __global__ __launch_bounds__(kPrepThreads) void k_union_prepare(const GraphDesc *gd, const PrepTile *tiles,
                                                                 int64_t ntiles, int copy_adj, int64_t *off_u,
-                                                                int32_t *deg_u, int32_t *adj_u, unsigned *dmax_g) {
-  __shared__ unsigned wmax[kPrepThreads / kWave];
+                                                                int32_t *deg_u, int32_t *adj_u, unsigned *dmax_g,
+                                                                int32_t *rows) {
+  __shared__ unsigned wmax[kPrepThreads / kWave], wrows[kPrepThreads / kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const PrepTile tl = tiles[t];
     const GraphDesc d = gd[tl.g];
-    unsigned ml = 0;  // the tile's maximum degree
+    unsigned ml = 0, nr = 0;  // the tile's maximum degree and vertices with neighbours
     for (int64_t j = tl.i0 + threadIdx.x; j < tl.i1; j += blockDim.x) {
       if (j <= d.n) {
         int64_t o, o1 = 0;
@@ -103,6 +104,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_union_prepare(const GraphDesc 
           const int64_t deg = o1 - o;
           deg_u[d.vbase + j] = (int32_t)deg;
           ml = max(ml, (unsigned)(deg > 0 ? deg : 0));
+          nr += deg > 0;
         }
       } else if (copy_adj) {
         const int64_t s = j - (d.n + 1);
@@ -110,14 +112,26 @@ __global__ __launch_bounds__(kPrepThreads) void k_union_prepare(const GraphDesc 
       }
     }
 #pragma unroll
-    for (int k = kWave / 2; k > 0; k >>= 1) ml = max(ml, (unsigned)__shfl_xor((int)ml, k, kWave));
-    __syncthreads();  // wmax is reused across tiles
-    if (lane == 0) wmax[wave] = ml;
+    for (int k = kWave / 2; k > 0; k >>= 1) {
+      ml = max(ml, (unsigned)__shfl_xor((int)ml, k, kWave));
+      nr += (unsigned)__shfl_xor((int)nr, k, kWave);
+    }
+    __syncthreads();  // wmax and wrows are reused across tiles
+    if (lane == 0) {
+      wmax[wave] = ml;
+      wrows[wave] = nr;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-      unsigned m = 0;
-      for (int w = 0; w < kPrepThreads / kWave; ++w) m = max(m, wmax[w]);
-      if (m) atomicMax(&dmax_g[tl.g], m);
+      unsigned m = 0, r = 0;
+      for (int w = 0; w < kPrepThreads / kWave; ++w) {
+        m = max(m, wmax[w]);
+        r += wrows[w];
+      }
+      if (m) {
+        atomicMax(&dmax_g[tl.g], m);
+        atomicAdd(rows, (int32_t)r);
+      }
     }
   }
 }
@@ -561,13 +575,6 @@ void index_release(scan_index *ix) {
 
 namespace {
 
-// Intersection shapes of builds over several id windows, where the caller
-// leaves them open: every chunk sweeps the windows, so the largest chunks pay
-// (a thread per slot; R-MAT-23 with 512, 768 and 1024: 338, 327 and 316 ms a
-// build; owners of up to 256 and 1024 among the small ones: 327 and 390).
-constexpr int64_t kWideN = (int64_t)1 << 21;
-constexpr int32_t kWideSmallMax = 512, kWideSpc = 1024;
-
 // A pinned block and the event after its last use by the device; waits for
 // that use before the block goes back to the pool.
 struct PinnedHold {
@@ -657,9 +664,8 @@ class HostPack {
 }  // namespace
 
 scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint32_t flags,
-                              hipStream_t s, const IntersectConfig &asked, scan_index **outs,
+                              hipStream_t s, const IntersectConfig &cfg, scan_index **outs,
                               const double *weights, const LshSpec *lsh) {
-  IntersectConfig cfg = asked;
   if (G < 0 || (G > 0 && (!gs || !outs))) return fail(SCAN_EINVAL, "bad batch arguments");
   for (int32_t g = 0; g < G; ++g) {
     outs[g] = nullptr;
@@ -694,10 +700,6 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     item_base[g + 1] = item_base[g] + gs[g].n + 1 + (copy_adj ? gs[g].nnz : 0);
   }
   const int64_t N = vbase[G], NNZ = ebase[G];
-  if (cfg.auto_shapes && N > kWideN) {
-    cfg.small_max = kWideSmallMax;
-    cfg.spc = kWideSpc;
-  }
   if (N > 0x7fffffffLL) return fail(SCAN_EINVAL, "batch has more than 2^31-1 vertices in total");
   int device = 0;
   (void)hipGetDevice(&device);
@@ -786,7 +788,8 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
     const int64_t total = item_base[G];
     if (total > 0)
       k_union_prepare<<<grid_for((int64_t)ptiles.size(), 1, 4096), kPrepThreads, 0, s>>>(
-          d_gd, d_ptiles, (int64_t)ptiles.size(), copy_adj ? 1 : 0, off_u, deg, adj_u, d_dmax);
+          d_gd, d_ptiles, (int64_t)ptiles.size(), copy_adj ? 1 : 0, off_u, deg, adj_u, d_dmax,
+          &((PlanCounts *)ctl_plan)->rows);
   }
   if (flags & SCAN_VALIDATE) {
     int32_t *d_err;

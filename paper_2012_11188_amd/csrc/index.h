@@ -20,7 +20,7 @@ struct IntersectConfig {
   int32_t spc = 768;
   int32_t wbits = 20;       // LDS bitmap window of 2^wbits ids (clamped to LDS)
   // small_max and spc were left to the build, which then goes by the number of
-  // vertices (build.hip).
+  // vertices with neighbours (kWideRows).
   bool auto_shapes = true;
   bool search_windows = false;  // several windows: search row ranges instead of tabling them
   int32_t skip_deg = 0x7fffffff;  // edges whose endpoints both exceed this degree are left unwritten
@@ -42,11 +42,26 @@ struct IntersectStats {
 };
 
 // a2: the ownership plan, enqueued on s. The work lists live in `arena`, which
-// must outlive intersect_all; `counts` is kPlanCountBytes of zeroed device
-// memory, and what follows it belongs to the caller: the plan's last step
+// must outlive intersect_all; `counts` is kPlanCountBytes of device memory
+// (PlanCounts, zero but for rows), and what follows it belongs to the caller: the plan's last step
 // copies `words` int32 from `counts` to pinned `host` memory, and `ready` is
 // recorded then. The caller waits for it before
 // intersect_all.
+//
+// The shapes of a build that leaves them open follow from the number of
+// vertices with neighbours, counted by the degree pass (PlanCounts::rows, set
+// before the plan): above kWideRows, a window of the bitmap, the ids stay in
+// several windows also when numbered without the isolated vertices; every
+// chunk then sweeps the windows, so fewer, larger chunks pay (a thread per
+// slot), and owners that one wavefront can take. Builds with small_max / spc
+// of 256 / 768 and 512 / 1024, in ms: several windows, R-MAT-23 312 and 286,
+// R-MAT of 4M vertices 42.6 and 38.7, of 2M (1.1M with neighbours) 15.5 and
+// 15.5, of 2.2M 12.2 and 12.5, random graphs of 2.2M vertices and degree 300
+// 276 and 158, degree 600 506 and 519; one window, R-MAT-20 among 4M ids 6.5
+// and 7.0, R-MAT of 1.5M (0.8M with neighbours) 8.0 and 9.1, 100,000 vertices
+// of degree 400 among 2.2M ids 8.2 and 10.5.
+constexpr int32_t kWideRows = 1 << 20;
+constexpr int32_t kWideSmallMax = 512, kWideSpc = 1024;
 constexpr int32_t kDegBins = 192;  // eight per octave from degree 128 up
 constexpr size_t kPlanCountBytes = 32 + 4 * (size_t)kDegBins;
 // Least degree of bin b (b = kDegBins: past every degree).
@@ -65,8 +80,8 @@ struct PlanCounts {
   int32_t counter;  // work counter of the large-owner kernel
   int32_t heavy;    // vertices of degree kLightDeg+1..small_max
   int32_t done;     // workgroups of k_plan that have finished
-  int32_t rows;     // vertices with neighbours
-  int32_t pad[2];
+  int32_t rows;     // vertices with neighbours (counted before the plan)
+  int32_t small_max, spc;  // the shapes that the plan took
   int32_t bins[kDegBins];  // vertices by degree, from 128 up
 };
 static_assert(sizeof(PlanCounts) == kPlanCountBytes, "the maximum degrees follow the counts");

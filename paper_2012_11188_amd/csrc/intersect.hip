@@ -107,33 +107,45 @@ __device__ __forceinline__ int32_t block_excl_scan(int32_t v, int32_t *wsum, int
 constexpr int kPlanThreads = 256;
 constexpr int kPlanPer = 8;  // consecutive vertices per thread and tile
 
+// The shapes of a build, and those of one with more than wide_rows vertices
+// with neighbours.
+struct PlanShapes {
+  int32_t small_max, spc;
+  int32_t wide_rows, wide_small_max, wide_spc;
+};
+
 // Tiles of kPlanThreads * kPlanPer vertices: a vertex of degree 1..small_max
 // goes to the small list, a larger one is cut into chunks of spc row slots.
 // Whether a vertex owns any edge is left to the intersection kernels (they
 // read the neighbour degrees anyway; a vertex that owns nothing costs one
 // staging pass). The block scans its counts, reserves list space with one
 // global atomic per list, and writes the entries in vertex order.
-__global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, const int64_t *off, int64_t n, int small_max,
-                                                       int spc, SmallOwner *lists,
+__global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, const int64_t *off, int64_t n,
+                                                       PlanShapes shapes, SmallOwner *lists,
                                                        BigChunk *big_list, PlanCounts *pc, int32_t words,
                                                        int32_t *host) {
   __shared__ int32_t last;
   __shared__ int32_t wsum[kPlanThreads / kWave];
-  __shared__ int32_t tot_small, tot_heavy, tot_big, base_small, base_heavy, base_big, rows;
+  __shared__ int32_t tot_small, tot_heavy, tot_big, base_small, base_heavy, base_big;
   __shared__ int32_t bins[kDegBins];
   static_assert(kDegBins <= kPlanThreads, "a thread per degree bin");
+  const bool wide = pc->rows > shapes.wide_rows;
+  const int32_t small_max = wide ? shapes.wide_small_max : shapes.small_max;
+  const int32_t spc = wide ? shapes.wide_spc : shapes.spc;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {  // (read by the last workgroup)
+    __hip_atomic_store(&pc->small_max, small_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&pc->spc, spc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   if (threadIdx.x < kDegBins) bins[threadIdx.x] = 0;
   __syncthreads();
   constexpr int64_t kTile = (int64_t)kPlanThreads * kPlanPer;
   for (int64_t t0 = (int64_t)blockIdx.x * kTile; t0 < n; t0 += (int64_t)gridDim.x * kTile) {
     const int64_t v0 = t0 + (int64_t)threadIdx.x * kPlanPer;
     int32_t code[kPlanPer];  // 0 nothing, -1 light, -2 heavy small, else number of chunks
-    int32_t ns = 0, nh = 0, nb = 0, nr = 0;
-    if (threadIdx.x == 0) rows = 0;
+    int32_t ns = 0, nh = 0, nb = 0;
 #pragma unroll
     for (int k = 0; k < kPlanPer; ++k) {
       const int32_t dh = v0 + k < n ? deg[v0 + k] : 0;
-      nr += __popcll(__ballot(dh != 0));
       if (dh >= 128) atomicAdd(&bins[deg_bin(dh)], 1);
       code[k] = dh == 0 ? 0 : dh <= min(small_max, kLightDeg) ? -1 : dh <= small_max ? -2 : (dh + spc - 1) / spc;
       ns += code[k] == -1;
@@ -141,7 +153,6 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, const
       nb += code[k] > 0 ? code[k] : 0;
     }
     __syncthreads();  // wsum and the totals are reused across tiles
-    if (lane_id() == 0) atomicAdd(&rows, nr);
     const int32_t os = block_excl_scan(ns, wsum, &tot_small);
     const int32_t oh = block_excl_scan(nh, wsum, &tot_heavy);
     const int32_t ob = block_excl_scan(nb, wsum, &tot_big);
@@ -149,7 +160,6 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const int32_t *deg, const
       base_small = tot_small ? atomicAdd(&pc->small, tot_small) : 0;
       base_heavy = tot_heavy ? atomicAdd(&pc->heavy, tot_heavy) : 0;
       base_big = tot_big ? atomicAdd(&pc->big, tot_big) : 0;
-      atomicAdd(&pc->rows, rows);
     }
     __syncthreads();
     int32_t ps = base_small + os, ph = base_heavy + oh, pb = base_big + ob;
@@ -1124,17 +1134,24 @@ scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, c
   PlanCounts *pc = (PlanCounts *)counts;
   SCAN_TRY(arena.alloc(&p.lists, n));
   if (!p.weighted) SCAN_TRY(arena.alloc(&p.records, n));
-  SCAN_TRY(arena.alloc(&big_list, nnz / cfg.spc + std::min(n, nnz / cfg.small_max) + 1));
+  PlanShapes shapes{cfg.small_max, cfg.spc, INT_MAX, cfg.small_max, cfg.spc};
+  if (cfg.auto_shapes && n > kWideRows) {
+    shapes.wide_rows = kWideRows;
+    shapes.wide_small_max = kWideSmallMax;
+    shapes.wide_spc = kWideSpc;
+  }
+  SCAN_TRY(arena.alloc(&big_list, nnz / std::min(shapes.spc, shapes.wide_spc) +
+                                      std::min(n, nnz / std::min(shapes.small_max, shapes.wide_small_max)) + 1));
   p.big_list = big_list;
   p.counts = counts;
   p.host = host;
   k_plan<<<grid_for(n, kPlanThreads * kPlanPer, 2048), kPlanThreads, 0, s>>>(
-      deg, off, n, cfg.small_max, cfg.spc, p.lists, big_list, pc, words, (int32_t *)host);
+      deg, off, n, shapes, p.lists, big_list, pc, words, (int32_t *)host);
   SCAN_HIP_TRY(hipEventRecord(ready, s));
   return SCAN_OK;
 }
 
-scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, const int64_t *off,
+scan_status intersect_all(const IntersectConfig &asked, int64_t n, int64_t nnz, const int64_t *off,
                           const int32_t *deg, const int32_t *adj, int kind, double *sims,
                           int32_t *counts, int device, hipStream_t s, IntersectStats *stats,
                           const std::function<scan_status()> &reserve,
@@ -1151,6 +1168,9 @@ scan_status intersect_all(const IntersectConfig &cfg, int64_t n, int64_t nnz, co
   // lets the hardware balance the uneven rows, which persistent grids with a
   // static split do not.
   const PlanCounts h = *(const PlanCounts *)plan->host;
+  IntersectConfig cfg = asked;
+  cfg.small_max = h.small_max;
+  cfg.spc = h.spc;
   // Memory that the build can do without (ids numbered anew, the hub product)
   // is taken after what it needs, and given back where that is refused: a
   // build fits wherever it would fit without them.

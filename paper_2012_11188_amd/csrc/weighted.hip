@@ -786,6 +786,7 @@ IntersectConfig weighted_config(const IntersectConfig &cfg) {
   c.small_max = kWbSmallMax;
   c.spc = kWbSpc;
   c.wbits = kWbMaxBits;
+  c.auto_shapes = false;
   return c;
 }
 

@@ -205,3 +205,26 @@ def test_hub_product_is_formed(how, tune):
                 assert_index_equal(ix, oix, g)
             ix.free()
     assert without >= 1
+
+
+# shapes left open: small owners up to 512 and chunks of 1024 slots where more
+# than 2^20 vertices have neighbours, 256 and 768 else, whatever the ids span
+@pytest.mark.parametrize("used,n,wide", [((1 << 20) + 1, (1 << 20) + 1, True), ((1 << 20) + 1, (1 << 21) + 77, True),
+                                         (1 << 20, 1 << 20, False), (1 << 20, (1 << 21) + 77, False)])
+def test_open_shapes(used, n, wide):
+    from gpu_util import device_csr
+
+    step = n / used
+    place = (np.arange(used) * step).astype(np.int64)
+    ring = np.stack([place, place[(np.arange(used) + 1) % used]], 1)
+    hubs = [np.stack([np.full(d - 2, place[h]), place[3 * h + 7 + 5 * np.arange(d - 2)]], 1)
+            for h, d in ((11, 257), (1000, 512), (50000, 513), (90000, 900))]
+    g = graphgen.from_edges(n, np.concatenate([ring, *hubs]).astype(np.int32))
+    assert int((g.degrees() > 0).sum()) == used
+    deg = g.degrees()
+    ix = scan.scan_build_index(*device_csr(g), scan.COSINE, scan.SCAN_KEEP_SIMS | scan.SCAN_KEEP_COUNTS | scan.SCAN_PROFILE)
+    p = scan.scan_index_build_profile(ix)
+    small, spc = (512, 1024) if wide else (256, 768)
+    assert p["small_owners"] == int(((deg > 0) & (deg <= small)).sum())
+    assert p["big_chunks"] == int((-(-deg[deg > small] // spc)).sum())
+    assert_index_equal(ix, oracle.build_index(g, oracle.COSINE, threads=8), g)
