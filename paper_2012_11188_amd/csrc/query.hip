@@ -384,12 +384,19 @@ __global__ __launch_bounds__(256) void k_q_output(IndexView ix, Descs qd) {
 }
 
 // Small indexes: a whole query in one workgroup, union-find and marks in LDS.
-// The dependent launches above are then most of a query's time (2,000
-// vertices, 28,000 slots: 47 us a query with them, 28 us with this kernel);
-// kSmallN is what the LDS holds with kRowGroup edges per core, and past
-// kSmallNnz slots one CU's reads take longer than the launches.
+// The dependent launches above are then most of a query's time; kSmallN is
+// what the LDS holds with kRowGroup edges per core. Its time goes with the
+// slots that it reads, up to kSmallNnz of them (two queries, with every vertex
+// a core and with few or none, this kernel and the launches in us: 2,048
+// vertices of degree 8 42 and 51, 40 and 52; 16 78 and 61, 32 and 53; 64 112
+// and 62, 17 and 29; the cores are few in most queries). Rows past kSmallRow
+// entries are read by a wavefront each, most of them one after the other, so
+// with such rows half of the slots are the limit (a clique of 256, 65,280
+// slots, 47 and 38; of 362, 130,682 slots, 75 and 42; 2,048 vertices and 30
+// hubs joined to all, 121,950 slots, 146 and 56).
 constexpr int kSmallN = 2048;
 constexpr int64_t kSmallNnz = 64 * kSmallN;
+constexpr int64_t kSmallRow = 256, kSmallRowNnz = 32 * kSmallN;
 constexpr int kSmallAhead = 4;  // cores that a lane group takes at once
 
 __device__ __forceinline__ int32_t lds_find(int32_t *parent, int32_t x) {
@@ -517,7 +524,7 @@ __global__ __launch_bounds__(kQThreads) void k_q_small(IndexView ix, Descs qd) {
 template <class Descs>
 static void launch_queries(const scan_index *ix, const Descs &d, int32_t count, hipStream_t s) {
   IndexView v{ix->n, ix->dmax, ix->off, ix->no_ids, ix->no_sim, ix->co_off, ix->co_ids, ix->co_thr};
-  if (ix->n <= kSmallN && ix->nnz <= kSmallNnz) {
+  if (ix->n <= kSmallN && ix->nnz <= (ix->dmax <= kSmallRow ? kSmallNnz : kSmallRowNnz)) {
     k_q_small<<<dim3(1, count), kQThreads, 0, s>>>(v, d);
     return;
   }

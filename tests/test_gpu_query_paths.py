@@ -123,3 +123,16 @@ def test_queries_after_refused_capture(n, call, warm):
                 want = oracle.query(oix, mu, eps)
                 assert np.array_equal(memb.cpu().numpy(), want[0]) and np.array_equal(core.cpu().numpy(), want[1])
     gix.free()
+
+
+# the one-workgroup kernel with rows past 256 entries: up to 32 * 2048 slots;
+# hubs joined to all others, and cliques of 256 and 257
+@pytest.mark.parametrize("n,hubs", [(2048, 1), (2048, 16), (2048, 17), (2048, 30), (256, 256), (257, 257), (257, 256)])
+def test_small_index_long_rows(n, hubs):
+    u, v = np.meshgrid(np.arange(hubs), np.arange(n), indexing="ij")
+    g = graphgen.from_edges(n, np.stack([u.ravel(), v.ravel()], 1)[u.ravel() != v.ravel()].astype(np.int32))
+    gix = gpu_build(g)
+    oix = oracle.build_index(g, oracle.COSINE, threads=8)
+    vals = np.unique(oix.sim)
+    assert_queries_equal(gix, oix, [(mu, float(e)) for mu in (2, 3, hubs, hubs + 1, n) if mu > 1
+                                    for e in [0.0, *vals[:: max(1, len(vals) // 4)]]])
