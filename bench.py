@@ -46,7 +46,28 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def byte_model(st: dict, split: dict, s_off: int, deg=None, small_max: int = 256) -> dict:
+def hub_split(g, rows: int, cols: int, small_max: int) -> dict:
+    """What the product over hub rows takes from the large owners: the edges
+    between two of its rows (owners above small_max), and the ids of their
+    lower ends' rows that are columns, which nobody streams. Rows and columns
+    are the vertices of highest degree, cut between two degrees."""
+    if not rows:
+        return {"edges": 0, "answered": 0}
+    deg = np.diff(g.off)
+    ranked = np.sort(deg)[::-1]
+    is_row, is_col = deg >= ranked[rows - 1], deg >= ranked[cols - 1]
+    assert int(is_row.sum()) == rows and int(is_col.sum()) == cols
+    r = np.flatnonzero(is_row)
+    u = np.repeat(r, deg[r])
+    first = np.cumsum(deg[r]) - deg[r]
+    v = g.adj[np.arange(len(u)) + np.repeat(g.off[r] - first, deg[r])]
+    answered = np.zeros(g.n, np.int64)
+    answered[r] = np.add.reduceat(is_col[v].astype(np.int64), first)
+    low = is_row[v] & (deg[v] > small_max) & ((deg[u] < deg[v]) | ((deg[u] == deg[v]) & (u < v)))
+    return {"edges": int(low.sum()), "answered": int(answered[u[low]].sum())}
+
+
+def byte_model(st: dict, split: dict, s_off: int, deg=None, small_max: int = 256, hub=None) -> dict:
     """Algorithmic bytes, fixed before measurement.
 
     Build, the survey's model (labelled "model" in the output): CSR read once,
@@ -63,9 +84,13 @@ def byte_model(st: dict, split: dict, s_off: int, deg=None, small_max: int = 256
     Owner kernels, memory model: every lower neighbour's row streamed once per
     owned edge (4 B per id: 4 W), every owner slot staged once (its id, the
     neighbour's degree and offset: 16 B per slot of an owner of that class),
-    both similarity slots of every owned edge written (16 B per edge). The
-    survey's 8 W + 16 E is kept beside it."""
+    both similarity slots of every owned edge written (16 B per edge). Ids that
+    the hub product answers (hub_split) are not streamed; an edge between hubs
+    reads its count, the bits before its column, their prefix and where the
+    rest lies instead (2 + 16 + 2 + 16 B). The survey's 8 W + 16 E, over all
+    ids of the min-side rule, is kept beside it."""
     n, nnz, wmin = st["n"], st["nnz"], st["w_min"]
+    hub = hub or {"edges": 0, "answered": 0}
     s_big = s_small = 0
     if deg is not None:
         s_big = int(deg[deg > small_max].sum())
@@ -75,7 +100,8 @@ def byte_model(st: dict, split: dict, s_off: int, deg=None, small_max: int = 256
         "build": s_off * (n + 1) + 56 * nnz + 4 * wmin,
         "floor": s_off * (n + 1) + 28 * nnz,
         "k_big_owner_model": 8 * split["w_big"] + 16 * split["edges_big"],
-        "k_big_owner": 4 * split["w_big"] + 16 * s_big + 16 * split["edges_big"],
+        "k_big_owner": 4 * (split["w_big"] - hub["answered"]) + 16 * s_big + 16 * split["edges_big"] +
+                       36 * hub["edges"],
         "k_small_owner_model": 8 * split["w_small"] + 16 * split["edges_small"],
         "k_small_owner": 4 * split["w_small"] + 16 * s_small + 16 * split["edges_small"],
     }
@@ -175,27 +201,26 @@ def autotune(scan, graphs, kind, tune_arg, reps=2):
 
 def kernel_roofline(bm, phases, tune, workload):
     """Roofline of the dominant kernel, k_big_owner: achieved = its
-    memory-model bytes per launch / its hipEvent duration and that of the span
-    before it, which holds the hub product: the model's ids are those of the
-    min-side rule, and the product answers part of them in the kernel's place.
+    memory-model bytes per launch (byte_model) / its hipEvent duration.
     traffic = the measured bytes between L2 and memory per launch (rocprofv3
-    counters, calibrated), over the launch alone; model_frac = the survey's
-    8 W + 16 E model, whose probe half is served from LDS (so it may exceed
-    1)."""
+    counters, calibrated). model_frac = the survey's 8 W + 16 E model, over the
+    launch and the span before it, which holds the hub product: the model's
+    ids are those of the min-side rule, part of which the product answers, and
+    their probe half is served from LDS, so it may exceed 1."""
     big_ms = phases["intersect_big_ms"]
-    launch_sec = big_ms * 1e-3
-    sec = launch_sec + phases["plan_ms"] * 1e-3
+    sec = big_ms * 1e-3
+    span_ms = big_ms + phases["plan_ms"]
     achieved = bm["k_big_owner"] / sec / 1e9
     traffic, why = counter_traffic(tune, workload)
     return {"bound": "hbm", "kernel": "k_big_owner", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": why,
-            "traffic_frac": (traffic / launch_sec / 1e9 / HBM_PEAK_GBS) if traffic else None,
+            "traffic_frac": (traffic / sec / 1e9 / HBM_PEAK_GBS) if traffic else None,
             "bytes_per_launch": bm["k_big_owner"],
-            "bytes_model": "4 B per lower-row id of the min-side rule (streamed, or answered by the hub product) + "
-                           "16 B per owner slot + 16 B per owned edge",
-            "launch_ms": big_ms, "span_ms": sec * 1e3,
+            "bytes_model": "4 B per streamed lower-row id + 16 B per owner slot + 16 B per owned edge + 36 B per edge "
+                           "between rows of the hub product",
+            "launch_ms": big_ms, "model_span_ms": span_ms,
             "model_bytes_per_launch": bm["k_big_owner_model"],
-            "model_frac": bm["k_big_owner_model"] / sec / 1e9 / HBM_PEAK_GBS,
+            "model_frac": bm["k_big_owner_model"] / (span_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
             "traffic_over_algorithmic": (traffic / bm["k_big_owner"]) if traffic else None}
 
 
@@ -622,7 +647,6 @@ def rmat_workload(args, scan, torch, graphgen):
     kinds = [scan.COSINE] if scale == 20 else [scan.COSINE, scan.JACCARD]
     tune, tinfo = autotune(scan, [(off, adj)], scan.COSINE, args.tune, reps=2 if scale == 20 else 1)
     split = graphgen.owner_split(g, tune["small_max"])
-    bm = byte_model(st, split, s_off, np.diff(g.off), tune["small_max"])
     results = {}
     for kind in kinds:
         ms, dev_ms, profs, ixs = timed_builds(
@@ -632,6 +656,9 @@ def rmat_workload(args, scan, torch, graphgen):
         log(f"kind {kind}: {ms:.2f} ms/step wall, device {dev_ms:.2f} ms/step, phases {phases}")
         results[kind] = (ms, dev_ms, phases, ixs[0])
     ms, dev_ms, phases, ix = results[scan.COSINE]
+    rows, cols = scan.scan_index_hub_product(ix)
+    hub = hub_split(g, rows, cols, tune["small_max"])
+    bm = byte_model(st, split, s_off, np.diff(g.off), tune["small_max"], hub)
     value = g.num_edges / (ms * 1e-3)
     workload = f"rmat{scale}_cosine_index_build"
     config = {"workload": workload, "scale": scale, "edge_factor": ef, "abcd": [0.57, 0.19, 0.19, 0.05],
@@ -640,7 +667,7 @@ def rmat_workload(args, scan, torch, graphgen):
               "offsets": "int32" if s_off == 4 else "int64", "ids": "int32", "similarity": "cosine",
               "tune": tune}
     extra = {"phases_ms": phases, "device_ms_per_step": dev_ms,
-             "tune": dict(tinfo, **tune), "owner_split": split,
+             "tune": dict(tinfo, **tune), "owner_split": split, "hub_product": dict(rows=rows, cols=cols, **hub),
              "roofline": kernel_roofline(bm, phases, tune, workload),
              "build_roofline": build_roofline(bm, phases["total_ms"], workload, tune),
              "k_small_owner": {"bytes": bm["k_small_owner"], "model_bytes": bm["k_small_owner_model"],

@@ -37,3 +37,36 @@ def test_source_hashes():
 
     assert len(bench.kernel_source_hash()) == 64 and len(bench.library_source_hash()) == 64
     assert bench.counter_traffic({"small_max": 1, "spc": 1, "wbits": 1}, "none")[0] is None
+
+
+def test_hub_split():
+    """Edges between product rows and their answered ids, against the sets; the
+    kernel's bytes leave the answered ids out."""
+    import graphgen
+
+    g = graphgen.rmat(9, 12, seed=4)
+    deg = np.diff(g.off)
+    ranked = np.sort(deg)[::-1]
+    rows = int((deg >= ranked[60]).sum())
+    cols = int((deg >= ranked[150]).sum())
+    small_max = int(ranked[40])
+    is_row, is_col = deg >= ranked[60], deg >= ranked[150]
+    edges = answered = 0
+    for u in np.flatnonzero(is_row):
+        row = g.adj[g.off[u]:g.off[u + 1]]
+        for h in row:
+            if is_row[h] and deg[h] > small_max and (deg[u], u) < (deg[h], h):
+                edges += 1
+                answered += int(is_col[row].sum())
+    hub = bench.hub_split(g, rows, cols, small_max)
+    assert hub == {"edges": edges, "answered": answered} and edges > 100
+    assert bench.hub_split(g, 0, 0, small_max) == {"edges": 0, "answered": 0}
+    split, st = graphgen.owner_split(g, small_max), graphgen.degree_stats(g)
+    whole = bench.byte_model(st, split, 4, deg, small_max)
+    less = bench.byte_model(st, split, 4, deg, small_max, hub)
+    assert whole["k_big_owner"] - less["k_big_owner"] == 4 * answered - 36 * edges
+    assert {k: v for k, v in whole.items() if k != "k_big_owner"} == {k: v for k, v in less.items() if k != "k_big_owner"}
+    phases = {"intersect_big_ms": 2.0, "plan_ms": 1.0}
+    roof = bench.kernel_roofline(less, phases, {"small_max": small_max, "spc": 1, "wbits": 1}, "none")
+    assert roof["achieved"] == pytest.approx(less["k_big_owner"] / 2e-3 / 1e9)
+    assert roof["model_frac"] == pytest.approx(less["k_big_owner_model"] / 3e-3 / 1e9 / bench.HBM_PEAK_GBS)
