@@ -39,7 +39,7 @@ METRIC = "index-build edges/s (R-MAT-20); query p50/p99 ms, batched vs one-at-a-
 def counters_file(workload: str) -> str:
     """profiles/k_big_owner_<graph>_counters.txt for workload <graph>_..."""
     return os.path.join(ROOT, "profiles", f"k_big_owner_{workload.split('_')[0]}_counters.txt")
-KERNEL_SRC = os.path.join(ROOT, "paper_2012_11188_amd", "csrc", "intersect.hip")
+CSRC = os.path.join(ROOT, "paper_2012_11188_amd", "csrc")
 
 
 def log(*a):
@@ -124,10 +124,19 @@ def tune_str(t: dict) -> str:
 
 
 def kernel_source_hash() -> str:
-    """sha256 of the intersection kernels' source: intersect.hip up to its
-    first host function."""
-    src = open(KERNEL_SRC, encoding="utf-8").read()
-    return hashlib.sha256(src[:src.index("// Host side.")].encode()).hexdigest()
+    """sha256 of what the large-owner kernel's traffic follows from: the
+    intersection's source with its host side, the hub product's, and the
+    headers (record layouts, limits, shapes)."""
+    return _source_hash(lambda name: name in ("intersect.hip", "hubs.hip") or name.endswith(".h"))
+
+
+def _source_hash(wanted) -> str:
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(CSRC)):
+        if wanted(name):
+            h.update(name.encode())
+            h.update(open(os.path.join(CSRC, name), "rb").read())
+    return h.hexdigest()
 
 
 def counter_traffic(tune: dict, workload: str):
@@ -226,13 +235,7 @@ def kernel_roofline(bm, phases, tune, workload):
 
 def library_source_hash() -> str:
     """sha256 over every source file of the library (csrc/, sorted by name)."""
-    d = os.path.join(ROOT, "paper_2012_11188_amd", "csrc")
-    h = hashlib.sha256()
-    for name in sorted(os.listdir(d)):
-        if name.endswith((".hip", ".h")):
-            h.update(name.encode())
-            h.update(open(os.path.join(d, name), "rb").read())
-    return h.hexdigest()
+    return _source_hash(lambda name: name.endswith((".hip", ".h")))
 
 
 def build_counter_traffic(workload: str, tune: dict):

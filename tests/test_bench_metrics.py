@@ -70,3 +70,20 @@ def test_hub_split():
     roof = bench.kernel_roofline(less, phases, {"small_max": small_max, "spc": 1, "wbits": 1}, "none")
     assert roof["achieved"] == pytest.approx(less["k_big_owner"] / 2e-3 / 1e9)
     assert roof["model_frac"] == pytest.approx(less["k_big_owner_model"] / 3e-3 / 1e9 / bench.HBM_PEAK_GBS)
+
+
+@pytest.mark.parametrize("name,kernel", [("intersect.hip", True), ("hubs.hip", True), ("index.h", True),
+                                         ("common.h", True), ("rows.h", True), ("query.hip", False)])
+def test_kernel_hash_covers_its_sources(tmp_path, monkeypatch, name, kernel):
+    """A change to any source that the large-owner kernel's traffic follows
+    from makes counters taken before it stale; one elsewhere does not."""
+    import shutil
+
+    src = tmp_path / "csrc"
+    shutil.copytree(bench.CSRC, src)
+    monkeypatch.setattr(bench, "CSRC", str(src))
+    before = bench.kernel_source_hash(), bench.library_source_hash()
+    with open(src / name, "a") as f:
+        f.write("// more\n")
+    after = bench.kernel_source_hash(), bench.library_source_hash()
+    assert (before[0] != after[0]) == kernel and before[1] != after[1]
