@@ -14,8 +14,9 @@ Workloads (--workload):
 
 One step = one full index build (degrees, ownership plan, intersection + FP64
 similarity, neighbour order, core order) from a CSR resident in HBM to the
-index resident in HBM. Prints ONE JSON line on stdout; progress goes to
-stderr.
+index resident in HBM. Prints ONE JSON line on stdout; progress and
+the long lists (every query, every rate of the serving ladders, every trial)
+go to stderr.
 
   python bench.py [--gpus 1] [--steps 5] [--warmup 1] [--workload rmat20]
 """
@@ -636,6 +637,28 @@ def record(value, steps, warmup, ms, dtype, config, **extra):
     return rec
 
 
+DETAIL = ("per_query", "ladder", "trials")  # lists that grow with the options
+
+
+def headline(rec):
+    """The record without its long lists (a reader that keeps the last few
+    thousand characters of stdout must get the whole line), and those."""
+    detail = {}
+
+    def strip(x, path):
+        if isinstance(x, dict):
+            out = {}
+            for k, v in x.items():
+                if k in DETAIL:
+                    detail[".".join((*path, k))] = v
+                else:
+                    out[k] = strip(v, (*path, k))
+            return out
+        return [strip(v, (*path, str(i))) for i, v in enumerate(x)] if isinstance(x, list) else x
+
+    return strip(rec, ()), detail
+
+
 def rmat_workload(args, scan, torch, graphgen):
     scale, ef = (20, 16) if args.workload == "rmat20" else (23, 32)
     s_off = 4 if scale == 20 else 8
@@ -885,7 +908,10 @@ def main():
         rec = sbm_batch_workload(args, scan, torch, graphgen)
     else:
         rec = rmat_workload(args, scan, torch, graphgen)
-    print(json.dumps(rec), flush=True)
+    line, detail = headline(rec)
+    for name, rows in detail.items():
+        log(f"{name}: {json.dumps(rows)}")
+    print(json.dumps(line), flush=True)
 
 
 if __name__ == "__main__":

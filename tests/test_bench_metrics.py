@@ -87,3 +87,30 @@ def test_kernel_hash_covers_its_sources(tmp_path, monkeypatch, name, kernel):
         f.write("// more\n")
     after = bench.kernel_source_hash(), bench.library_source_hash()
     assert (before[0] != after[0]) == kernel and before[1] != after[1]
+
+
+def test_headline_is_one_short_line():
+    """The printed line keeps the contract's fields and every summary, and does
+    not grow with the number of queries, rates or trials."""
+    import json
+
+    row = {"offered_qps": 1234.5678901234567, "achieved_qps": 1234.5678901234567, "p50_ms": 0.12345678901234567,
+           "p99_ms": 0.12345678901234567}
+
+    def rec(k):
+        return bench.record(1.5e9, 20, 5, 6.1, "f64", {"workload": "w", "tune": {"spc": 1}}, roofline={"frac": 0.5},
+                            query={"queries": k, "batched": {"p50_ms": 0.5}, "per_query": [row] * k},
+                            approx_quality=[{"graph": "g", "simhash_cosine": {"ari_mean": 0.9, "trials": [row] * k}}],
+                            serving={"device": {"batched": {"max_slots": 4, "ladder": [row] * k},
+                                                "batched_max_qps_within_budget": 5.0}})
+
+    line, detail = bench.headline(rec(3))
+    for key in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                "vs_baseline", "dtype", "data", "config"):
+        assert line[key] == rec(3)[key]
+    assert line["approx_quality"] == [{"graph": "g", "simhash_cosine": {"ari_mean": 0.9}}]
+    assert line["serving"]["device"] == {"batched": {"max_slots": 4}, "batched_max_qps_within_budget": 5.0}
+    assert {k: len(v) for k, v in detail.items()} == {"query.per_query": 3, "serving.device.batched.ladder": 3,
+                                                      "approx_quality.0.simhash_cosine.trials": 3}
+    assert len(json.dumps(bench.headline(rec(5000))[0])) < len(json.dumps(line)) + 10
+    assert len(json.dumps(rec(200))) > 20000
