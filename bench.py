@@ -480,7 +480,7 @@ def weighted_timing(scan, torch, graphgen, g, off, adj, st, steps):
     tc = time.perf_counter() - t
     return {"value": g.num_edges / (ms * 1e-3), "unit": "edges/s", "ms_per_step": ms, "device_ms_per_step": dev_ms,
             "phases_ms": phases, "weights": "uniform [0.05, 1), seed 2020, symmetric",
-            "square_sums_ms": phases["intersect_small_ms"], "k_w_owner": {
+            "square_sums_ms": phases["intersect_small_ms"], "owner_products": {
                 "bytes": nbytes, "launch_ms": owner_ms, "achieved_gbs": nbytes / max(owner_ms, 1e-6) / 1e6,
                 "frac": nbytes / max(owner_ms, 1e-6) / 1e6 / HBM_PEAK_GBS},
             "cpu_baseline": {"value": k / tc, "unit": "edges/s", "cores": 1, "kind": "oracle",

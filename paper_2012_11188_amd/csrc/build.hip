@@ -367,8 +367,12 @@ __global__ void k_co_tiles(const RTile *rt, int64_t nrt, const RankInfo *sv_all,
 // kPrepOneDeg, in one workgroup and one launch: the counts, offsets, ranks and
 // tiles of a small graph are a few microseconds of work, and the twelve
 // launches of the general way, with the upload of their tables, were most of a
-// small build (2,000 vertices: 200 us under the profiler, this kernel 8). Past these sizes they run beside a longer
-// intersection, and one workgroup would not.
+// small build (2,000 vertices: 200 us under the profiler, this kernel 8). With
+// more vertices one workgroup takes longer, and the launches run beside a
+// longer intersection. Builds with this kernel and with the launches, in us:
+// 2,000 vertices 222 and 245, 16,384 of an R-MAT graph 294 and 327, of a random
+// one 243 and 260, all of one degree (whose counts meet at one address) 258 and
+// 264; 32,768 344 and 351, 279 and 279, 301 and 278.
 constexpr int kPrepOneN = 32768, kPrepOneDeg = 4096, kPrepOneThreads = 1024;
 
 // Exclusive sum over the workgroup of one value per thread.
@@ -834,8 +838,8 @@ scan_status build_index_batch(const scan_csr *gs, int32_t G, int32_t kind, uint3
   const bool planned = NNZ > 0 && (!weighted || weighted_planned(N, NNZ));
   const IntersectConfig pcfg = weighted ? weighted_config(cfg) : cfg;
   if (planned) {
-    SCAN_TRY(intersect_plan(pcfg, N, NNZ, off_u, deg, adj_u, device, tmp, s, ctl_plan, (int32_t)(ctl_back / 4),
-                            back.block.p, back.ready, plan));
+    SCAN_TRY(intersect_plan(pcfg, N, NNZ, off_u, deg, tmp, s, ctl_plan, (int32_t)(ctl_back / 4), back.block.p,
+                            back.ready, plan));
   } else {
     SCAN_HIP_TRY(hipMemcpyAsync(back.block.p, ctl_plan, ctl_back, hipMemcpyDeviceToHost, s));
     SCAN_HIP_TRY(hipEventRecord(back.ready, s));

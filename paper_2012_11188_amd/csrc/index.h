@@ -116,8 +116,7 @@ struct IntersectPlan {
   IntersectPlan &operator=(const IntersectPlan &) = delete;
 };
 scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, const int64_t *off,
-                           const int32_t *deg, const int32_t *adj, int device, DevArena &arena, hipStream_t s,
-                           void *counts, int32_t words, void *host, hipEvent_t ready, IntersectPlan &plan);
+                           const int32_t *deg, DevArena &arena, hipStream_t s, void *counts, int32_t words, void *host, hipEvent_t ready, IntersectPlan &plan);
 
 // Common neighbours among hubs by matrix product (hubs.hip).
 constexpr int32_t kHubMaxRows = 49152, kHubMaxCols = 65536;  // counts of common columns fit 16 bits

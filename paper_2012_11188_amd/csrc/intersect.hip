@@ -7,18 +7,20 @@
 // neighbour u streams its own, shorter row through it, so an edge costs
 // min-side work and no global atomics.
 //
-//   k_plan          per vertex, by degree: 1..small_max go to the small list,
-//                   larger vertices are cut into chunks of `spc` row slots
-//                   (block-scanned appends, one reservation per tile).
-//   k_small_owner   one workgroup per small vertex: if it owns edges, its row
-//                   goes into an LDS hash table and its wavefronts stream the
-//                   lower neighbours' rows 64 ids at a time through it.
+//   k_plan          per vertex, by degree: 1..small_max go to the lists of
+//                   small vertices, larger ones are cut into chunks of `spc`
+//                   row slots (block-scanned appends, one reservation per tile).
+//   k_small_owner   one workgroup per small vertex: its row goes into an LDS
+//                   hash table, and groups of 8 or 16 lanes stream a lower
+//                   neighbour's row each through it.
 //   k_big_owner     persistent workgroups (1024 threads) holding a bitmap of an
 //                   id window (2^wbits ids) in LDS: the owner's ids in the
 //                   window are set, every lower neighbour's ids in the window
-//                   are tested with one LDS read each, then the bits are
-//                   cleared. Chunks are claimed from a global counter, edges
-//                   inside a chunk by wavefronts from an LDS counter.
+//                   are tested with one LDS read each, and the bitmap is
+//                   cleared as a whole for the next owner or window. Chunks
+//                   are claimed from a global counter, short ranges four at a
+//                   time and pieces of long ones by wavefronts from LDS
+//                   counters.
 //   k_window_table  (ids spanning several windows) the first position of
 //                   every window in every row, so that chunks read each lower
 //                   neighbour's range in a window instead of searching it.
@@ -1125,8 +1127,7 @@ static int window_bits(const IntersectConfig &cfg, int64_t n, int lds_max) {
 }
 
 scan_status intersect_plan(const IntersectConfig &cfg, int64_t n, int64_t nnz, const int64_t *off,
-                           const int32_t *deg, const int32_t *adj, int device, DevArena &arena, hipStream_t s,
-                           void *counts, int32_t words, void *host, hipEvent_t ready, IntersectPlan &p) {
+                           const int32_t *deg, DevArena &arena, hipStream_t s, void *counts, int32_t words, void *host, hipEvent_t ready, IntersectPlan &p) {
   p.n = n;
   p.nnz = nnz;
   if (nnz == 0) return SCAN_OK;
@@ -1185,7 +1186,7 @@ scan_status intersect_all(const IntersectConfig &asked, int64_t n, int64_t nnz, 
     // Ids spanning several windows. A chunk's cost is mostly its work items,
     // and each lower neighbour makes at least one per window, so ids are
     // numbered without the isolated vertices where that saves a window (half
-    // of an R-MAT graph's: R-MAT-23 has 8 windows with them and 5 without, and
+    // of an R-MAT graph's: R-MAT-23 has 8 windows with them and 6 without, and
     // its large owners take 448 ms with them, 400 without; renaming takes 5).
     // Where there is no memory for the second adjacency, they stay.
     const int rbits = window_bits(cfg, h.rows, lds_max);
