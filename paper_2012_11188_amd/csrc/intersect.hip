@@ -237,7 +237,7 @@ constexpr size_t kSmallLdsMax = 32768;
 
 struct LowRow {
   int64_t ou;     // row offset of a lower neighbour (an empty row's: 0, where reads for it go)
-  int32_t du, e;  // its degree, its slot in the vertex's row (-1: none)
+  int32_t du, e;  // its degree, its slot in the vertex's row
 };
 
 // LDS bytes of k_small_owner for a given small_max and spread.
@@ -292,9 +292,9 @@ __global__ __launch_bounds__(WAVES * kWave) void k_small_owner(const SmallOwner 
   __syncthreads();
   const int32_t nlow = uniform(s_nlow);
   // Each group of G lanes takes one lower neighbour (NG per wavefront, the
-  // wavefronts take successive sets); a missing row has length 0, as has an
-  // empty one (of a graph that does not hold every edge in both directions).
-  // Reads past a row's end read its last id again.
+  // wavefronts take successive sets); a missing row has length -1 (an empty one
+  // is met in graphs that do not hold every edge in both directions). Reads
+  // past a row's end read its last id again.
   constexpr int G = WAVES == 1 ? kLightGroup : kHeavyGroup, NG = kWave / G;
   constexpr int L = kSmallLoads, P = kSmallLookups;
   static_assert(G == 8 || G == 16, "sums within a row of 16 lanes");
@@ -305,10 +305,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_small_owner(const SmallOwner 
   };
   auto rows_at = [&](int32_t j) {
     Rows r{j, 0, 0, lows[min(j + grp, nlow - 1)]};
-    if (j + grp >= nlow) {
-      r.q.du = 0;
-      r.q.e = -1;
-    }
+    if (j + grp >= nlow) r.q.du = -1;
 #pragma unroll
     for (int g = 0; g < NG; ++g) r.longest = max(r.longest, __builtin_amdgcn_readlane(r.q.du, g * G));
     return r;
@@ -362,7 +359,7 @@ __global__ __launch_bounds__(WAVES * kWave) void k_small_owner(const SmallOwner 
     t += __builtin_amdgcn_update_dpp(0, t, 0x114, 0xf, 0xf, true);
     if (G == 16) t += __builtin_amdgcn_update_dpp(0, t, 0x118, 0xf, 0xf, true);
     t = __shfl(t, lane | (G - 1), kWave);
-    if (r.q.e >= 0 && (gl == 0 || pos >= 0)) {
+    if (r.q.du >= 0 && (gl == 0 || pos >= 0)) {
       const int64_t c = (int64_t)t + 2;
       const double x = similarity(kind, c, (int64_t)r.q.du + 1, (int64_t)dh + 1);
       if (gl == 0) {

@@ -19,10 +19,11 @@ namespace scan {
 // where the slots end) stands at slot 0.
 SCAN_ROWS_FN int64_t row_start(int64_t off, int32_t deg) { return deg > 0 ? off : 0; }
 
-// Position p of a row; past its end its last one (0 where it has none).
+// Position p >= 0 of a row; past its end its last one (0 where it has none).
+// (In this form one instruction, the middle of three, after the subtraction.)
 SCAN_ROWS_FN int32_t row_position(int32_t p, int32_t deg) {
-  const int32_t top = deg > 0 ? deg - 1 : 0;
-  return p < top ? p : top;
+  const int32_t q = p < deg - 1 ? p : deg - 1;
+  return q > 0 ? q : 0;
 }
 
 // The number of a vertex among the `used` ones with neighbours, from the count

@@ -52,6 +52,8 @@ def test_reads_stay_inside(reads, deg):
     off = np.concatenate([[0], np.cumsum(deg)])
     got = reads(off)
     assert got.min() >= 0 and got.max() < off[-1]
+    missing = reads(np.concatenate([off[:1], off[:1] - 1]))  # a length of -1: the row's first slot
+    assert np.all(missing == off[0])
     for v, d in enumerate(deg):
         if d:  # the row's own positions, then its last one again
             assert np.array_equal(got[v], off[v] + np.minimum(np.arange(300), d - 1))
