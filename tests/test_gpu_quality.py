@@ -76,3 +76,22 @@ def test_quality_errors():
         scan.scan_sweep_modularity(gix, np.array([1], np.int32), np.array([0.5]))  # mu < 2
     with pytest.raises(scan.ScanError):
         scan.scan_sweep_modularity(gix, np.array([2], np.int32), np.array([0.5]), batch=0)
+
+
+# one clustering takes at most 4095 workgroups of 32 vertices a round: a round
+# less one vertex, a round, one more, two and one more; hubs of 2000 at ids that
+# are multiples of 2^14; few and many labels
+@pytest.mark.parametrize("n", [131039, 131040, 131041, 262081])
+@pytest.mark.parametrize("labels", [3, 5000])
+def test_modularity_rounds(n, labels):
+    import torch
+
+    rng = np.random.default_rng(n + labels)
+    hubs = np.arange(0, n, 1 << 14)
+    edges = [rng.integers(0, n, (3 * n, 2))]
+    edges += [np.stack([np.full(2000, h), rng.choice(n, 2000, replace=False)], 1) for h in hubs]
+    g = graphgen.from_edges(n, np.concatenate(edges).astype(np.int32))
+    ix = scan.scan_build_index(torch.from_numpy(g.off.astype(np.int32)).cuda(), torch.from_numpy(g.adj).cuda())
+    memb = rng.integers(-1, labels, n).astype(np.int32)
+    q = scan.scan_query_modularity(ix, torch.from_numpy(memb).cuda())
+    assert np.float64(q).tobytes() == np.float64(oracle.modularity(g, memb)[0]).tobytes()
