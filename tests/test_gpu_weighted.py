@@ -250,3 +250,17 @@ def test_weighted_owner_classes(degree, n):
         assert np.array_equal(bits(scan.scan_index_export(gix, code)), bits(want)), name
     assert np.array_equal(scan.scan_index_export(gix, scan.ARR_NO_IDS), oix.no_ids)
     assert np.array_equal(scan.scan_index_export(gix, scan.ARR_CO_IDS), oix.co_ids)
+
+
+# random graphs, most of whose steps hold no common id, with owners on both
+# sides of the kernels' limits (64, 256); weights of either sign and zeros
+@pytest.mark.parametrize("n,degree", [(3000, 60), (5000, 200), (5000, 256), (4000, 330)])
+def test_weighted_few_common_neighbours(n, degree):
+    rng = np.random.default_rng(n + degree)
+    g = graphgen.from_edges(n, rng.integers(0, n, (n * degree // 2, 2)).astype(np.int32))
+    w = graphgen.edge_weights(g, 9)
+    w[rng.integers(0, g.nnz, g.nnz // 10)] *= -1.0
+    w[rng.integers(0, g.nnz, g.nnz // 10)] *= 0.0
+    gix = weighted_gpu(g, w)
+    oix = oracle.build_index_weighted(g, w, threads=8)
+    assert np.array_equal(bits(scan.scan_index_export(gix, scan.ARR_SIMS)), bits(oix.sim))
