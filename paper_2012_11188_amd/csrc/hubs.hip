@@ -160,8 +160,9 @@ __device__ __forceinline__ i32x8 fp4_of(uint32_t w) {
 // is one contiguous kilobyte, a 16-byte load per lane; the next 256 columns'
 // loads are in flight. The product reads 8 bytes of bits per row and 64
 // columns, so it is bound by the matrix cores and the expansion beside them:
-// R-MAT-20, 5,120 rows by 65,536 columns, 350 us with 210 workgroups on the
-// 256 CUs (5.1 PFLOP/s), and k_big_owner 4.8 -> 3.9 ms beside the small owners.
+// R-MAT-20, 5,008 rows by 51,785 columns, 356 us with 210 workgroups on the
+// 256 CUs (4.0 PFLOP/s; all 256 would reach 4.9). It took k_big_owner, as it
+// was then, from 4.8 to 3.9 ms beside the small owners.
 __global__ __launch_bounds__(256, 1) void k_hub_product(HubView hub, uint16_t *D) {
   const int lane = lane_id(), wave = threadIdx.x / kWave;
   const int t = blockIdx.x;
@@ -237,9 +238,9 @@ __global__ __launch_bounds__(256, 1) void k_hub_product(HubView hub, uint16_t *D
 // edges and ids are within 12% of the counted ones. The rates are the
 // large-owner kernel's time per streamed id and the product's measured one; a
 // gain below 0.1 ms is left alone. Builds without it and with: R-MAT of 60,000
-// vertices (not chosen) 0.53 ms, R-MAT-20 (5,120 rows) 6.98 and 6.80 ms,
+// vertices (not chosen) 0.53 ms, R-MAT-20 (5,008 rows) 6.98 and 6.80 ms,
 // R-MAT-23 417 and 383 ms (11,520 rows); with the faster large-owner kernel,
-// 11,520 and 44,544 rows 305 and 291 ms. kHubMaxRows bounds D to 4.8 GB.
+// 11,520 and 44,418 rows 305 and 291 ms. kHubMaxRows bounds D to 4.8 GB.
 HubShape choose_hubs(const PlanCounts &pc, int64_t nnz, bool one_window) {
   const double per_id = one_window ? 0.5e-12 : 0.6e-12;  // seconds
   const double per_round_col = 8.0 / 2.3e9 / 0.6;        // a round's seconds per column
